@@ -335,7 +335,7 @@ static void lin_fwd(const Shape& s, const int32_t* offsets, const int32_t* tpre,
   if constexpr (sizeof(E) == 2)
     run_gemm2<GROUP_M, false, false, EPI_BIAS, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
   else
-    run_gemm<E, GROUP_M, true, EPI_BIAS, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, false, EPI_BIAS, C>(p, mt_ub * nt, st);
 }
 
 // dA[rows, n_in] = dC[rows, n_out] W_e   (W_e read as (n = input feature, k = output feature))
@@ -352,7 +352,7 @@ static void lin_dgrad(const Shape& s, const int32_t* offsets, const int32_t* tpr
   if constexpr (sizeof(E) == 2)
     run_gemm2<GROUP_M, false, true, EPI_STORE, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
   else
-    run_gemm<E, GROUP_M, false, EPI_STORE, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, true, EPI_STORE, C>(p, mt_ub * nt, st);
 }
 
 // dW_e[n_out, n_in] = dC_e^T A_e over the expert's rows
@@ -369,7 +369,7 @@ static void lin_wgrad(const Shape& s, const int32_t* offsets, const int32_t* tac
   if constexpr (sizeof(E) == 2)
     run_gemm2<GROUP_K, true, true, EPI_STORE, CW::BM, CW::BN, CW::WM, CW::WN, CW::ST, CW::BK, CW::STO>(p, active_ub * mt * nt, st);
   else
-    run_gemm<E, GROUP_K, false, EPI_STORE, CW::BM, CW::BN, CW::BK, CW::WM, CW::WN>(p, active_ub * mt * nt, st);
+    run_gemm_f32<GROUP_K, true, true, EPI_STORE, CW>(p, active_ub * mt * nt, st);
 }
 
 template <typename E>
@@ -526,8 +526,12 @@ extern "C" int dmoe_expert_ffblock_fwd(const dmoe_dims* dims, const int32_t* off
     if (use_fat(s)) block_fwd<bf16, G2Fat>(s, offsets, xp, params_of<bf16>(params), acts_of<bf16>(acts), yp, tpre, st);
     else block_fwd<bf16, G2Skinny>(s, offsets, xp, params_of<bf16>(params), acts_of<bf16>(acts), yp, tpre, st);
   } else {
-    block_fwd<float, CfgF32>(s, offsets, reinterpret_cast<const float*>(x_perm), params_of<float>(params),
-                             acts_of<float>(acts), reinterpret_cast<float*>(y_perm), tpre, st);
+    const float* xp = reinterpret_cast<const float*>(x_perm);
+    float* yp = reinterpret_cast<float*>(y_perm);
+    if (use_fat_f32(s))
+      block_fwd<float, CfgF32>(s, offsets, xp, params_of<float>(params), acts_of<float>(acts), yp, tpre, st);
+    else
+      block_fwd<float, CfgF32Skinny>(s, offsets, xp, params_of<float>(params), acts_of<float>(acts), yp, tpre, st);
   }
   return launch_status();
 }
@@ -561,8 +565,12 @@ extern "C" int dmoe_expert_ffblock_bwd(const dmoe_dims* dims, const int32_t* off
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    block_bwd<float, CfgF32, CfgDWF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts),
+    if (use_fat_f32(s))
+      block_bwd<float, CfgF32, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts),
                                        c(dy_perm), m(g1), m(g2), m(dx_perm), grads_of<float>(grads), tpre, st);
+    else
+      block_bwd<float, CfgF32Skinny, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts),
+                                             c(dy_perm), m(g1), m(g2), m(dx_perm), grads_of<float>(grads), tpre, st);
   }
   return launch_status();
 }

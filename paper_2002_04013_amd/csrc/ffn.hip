@@ -158,44 +158,44 @@ static void ffn_bwd_sgd_bf16(const Shape& s, const int32_t* offsets, const bf16*
                      st, dyp, (int64_t)D, offsets, D, b2, lr);
 }
 
-template <typename E, typename C>
-static void ffn_fwd_cfg(const Shape& s, const int32_t* offsets, const E* xp, const E* W1,
-                        const E* b1, const E* W2, const E* b2, E* h, E* a, E* yp, int32_t* tpre,
-                        hipStream_t st) {
+template <typename C>
+static void ffn_fwd_f32(const Shape& s, const int32_t* offsets, const float* xp, const float* W1,
+                        const float* b1, const float* W2, const float* b2, float* h, float* a, float* yp,
+                        int32_t* tpre, hipStream_t st) {
   const int N = (int)s.N, D = (int)s.D, H = (int)s.H;
   const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
   DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, N, C::TMR, tpre);
   // h = x W1^T + b1, a = act(h)
   {
     const int nt = (H + C::BN - 1) / C::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tpre, nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tpre, nt, N);
     p.A = xp; p.lda = D;
     p.B = W1; p.ldb = D; p.b_gstride = (int64_t)H * D;
     p.C = h; p.ldc = H; p.C2 = a;
     p.bias = b1; p.bias_gstride = H;
     p.N = H; p.K = D; p.act = s.act;
-    run_gemm<E, GROUP_M, true, EPI_BIAS_ACT, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, false, EPI_BIAS_ACT, C>(p, mt_ub * nt, st);
   }
   // y = a W2^T + b2
   {
     const int nt = (D + C::BN - 1) / C::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tpre, nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tpre, nt, N);
     p.A = a; p.lda = H;
     p.B = W2; p.ldb = H; p.b_gstride = (int64_t)D * H;
     p.C = yp; p.ldc = D;
     p.bias = b2; p.bias_gstride = D;
     p.N = D; p.K = H; p.act = s.act;
-    run_gemm<E, GROUP_M, true, EPI_BIAS, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, false, EPI_BIAS, C>(p, mt_ub * nt, st);
   }
 }
 
 // SGD: dW1, db1, dW2, db2 are the parameters W1, b1, W2, b2 themselves, updated in
 // place (W <- W - lr dW) after their last read: dh reads W2 before W2's update and
 // dx_perm reads W1 before W1's update.
-template <typename E, typename C, typename CW, bool SGD = false>
-static void ffn_bwd_cfg(const Shape& s, const int32_t* offsets, const E* xp, const E* h,
-                        const E* a, const E* dyp, const E* W1, const E* W2, E* dh, E* dxp, E* dW1,
-                        E* db1, E* dW2, E* db2, int32_t* tpre, hipStream_t st, float lr = 0.f) {
+template <typename C, typename CW, bool SGD = false>
+static void ffn_bwd_f32(const Shape& s, const int32_t* offsets, const float* xp, const float* h,
+                        const float* a, const float* dyp, const float* W1, const float* W2, float* dh, float* dxp, float* dW1,
+                        float* db1, float* dW2, float* db2, int32_t* tpre, hipStream_t st, float lr = 0.f) {
   constexpr int EPI_W = SGD ? EPI_SGD : EPI_STORE;
   const int N = (int)s.N, D = (int)s.D, H = (int)s.H;
   const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
@@ -205,65 +205,65 @@ static void ffn_bwd_cfg(const Shape& s, const int32_t* offsets, const E* xp, con
   // dh = (dy W2) * act'(h)       B = W2_e viewed as (n = h, k = d): N-contiguous
   {
     const int nt = (H + C::BN - 1) / C::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tpre, nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tpre, nt, N);
     p.A = dyp; p.lda = D;
     p.B = W2; p.ldb = H; p.b_gstride = (int64_t)D * H;
     p.C = dh; p.ldc = H; p.aux = h;
     p.N = H; p.K = D; p.act = s.act;
-    run_gemm<E, GROUP_M, false, EPI_DACT, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, true, EPI_DACT, C>(p, mt_ub * nt, st);
   }
   // dW2_e = dy_e^T a_e   [D, H]
   {
     const int mt = (D + CW::BM - 1) / CW::BM, nt = (H + CW::BN - 1) / CW::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tact, mt * nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tact, mt * nt, N);
     p.A = dyp; p.lda = D;
     p.B = a; p.ldb = H;
     p.C = dW2; p.ldc = H; p.c_gstride = (int64_t)D * H;
     p.M = D; p.N = H; p.act = s.act; p.lr = lr;
-    run_gemm<E, GROUP_K, false, EPI_W, CW::BM, CW::BN, CW::BK, CW::WM, CW::WN>(p, active_ub * mt * nt, st);
+    run_gemm_f32<GROUP_K, true, true, EPI_W, CW>(p, active_ub * mt * nt, st);
   }
   // dx_perm = dh W1              B = W1_e viewed as (n = d, k = h): N-contiguous
   {
     const int nt = (D + C::BN - 1) / C::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tpre, nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tpre, nt, N);
     p.A = dh; p.lda = H;
     p.B = W1; p.ldb = D; p.b_gstride = (int64_t)H * D;
     p.C = dxp; p.ldc = D;
     p.N = D; p.K = H; p.act = s.act;
-    run_gemm<E, GROUP_M, false, EPI_STORE, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+    run_gemm_f32<GROUP_M, false, true, EPI_STORE, C>(p, mt_ub * nt, st);
   }
   // dW1_e = dh_e^T x_e   [H, D]
   {
     const int mt = (H + CW::BM - 1) / CW::BM, nt = (D + CW::BN - 1) / CW::BN;
-    GemmArgs<E> p = args_m<E>(offsets, tact, mt * nt, N);
+    GemmArgs<float> p = args_m<float>(offsets, tact, mt * nt, N);
     p.A = dh; p.lda = H;
     p.B = xp; p.ldb = D;
     p.C = dW1; p.ldc = D; p.c_gstride = (int64_t)H * D;
     p.M = H; p.N = D; p.act = s.act; p.lr = lr;
-    run_gemm<E, GROUP_K, false, EPI_W, CW::BM, CW::BN, CW::BK, CW::WM, CW::WN>(p, active_ub * mt * nt, st);
+    run_gemm_f32<GROUP_K, true, true, EPI_W, CW>(p, active_ub * mt * nt, st);
   }
   // bias gradients
-  constexpr int VEC = 16 / sizeof(E);
-  DMOE_LAUNCH((segment_colsum<E, SGD>), dim3((unsigned)((H / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
+  constexpr int VEC = 4;
+  DMOE_LAUNCH((segment_colsum<float, SGD>), dim3((unsigned)((H / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
                      st, dh, (int64_t)H, offsets, H, db1, lr);
-  DMOE_LAUNCH((segment_colsum<E, SGD>), dim3((unsigned)((D / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
+  DMOE_LAUNCH((segment_colsum<float, SGD>), dim3((unsigned)((D / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
                      st, dyp, (int64_t)D, offsets, D, db2, lr);
 }
 
-template <typename E, typename C>
-static void ffn_up_cfg(const Shape& s, const int32_t* offsets, const E* xp, const E* W1, const E* b1, E* h, E* a,
+template <typename C>
+static void ffn_up_f32(const Shape& s, const int32_t* offsets, const float* xp, const float* W1, const float* b1, float* h, float* a,
                        int32_t* tpre, hipStream_t st) {
   const int N = (int)s.N, D = (int)s.D, H = (int)s.H;
   const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
   DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, N, C::TMR, tpre);
   const int nt = (H + C::BN - 1) / C::BN;
-  GemmArgs<E> p = args_m<E>(offsets, tpre, nt, N);
+  GemmArgs<float> p = args_m<float>(offsets, tpre, nt, N);
   p.A = xp; p.lda = D;
   p.B = W1; p.ldb = D; p.b_gstride = (int64_t)H * D;
   p.C = h; p.ldc = H; p.C2 = a;
   p.bias = b1; p.bias_gstride = H;
   p.N = H; p.K = D; p.act = s.act;
-  run_gemm<E, GROUP_M, true, EPI_BIAS_ACT, C::BM, C::BN, C::BK, C::WM, C::WN>(p, mt_ub * nt, st);
+  run_gemm_f32<GROUP_M, false, false, EPI_BIAS_ACT, C>(p, mt_ub * nt, st);
 }
 
 // The forward on a tile plan at tpre (2 (N + 1) ints of device memory).
@@ -280,7 +280,10 @@ static int ffn_fwd_impl(const Shape& s, const int32_t* offsets, const void* x_pe
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    ffn_fwd_cfg<float, CfgF32>(s, offsets, c(x_perm), c(W1), c(b1), c(W2), c(b2), m(h), m(a), m(y_perm), tpre, st);
+    if (use_fat_f32(s))
+      ffn_fwd_f32<CfgF32>(s, offsets, c(x_perm), c(W1), c(b1), c(W2), c(b2), m(h), m(a), m(y_perm), tpre, st);
+    else
+      ffn_fwd_f32<CfgF32Skinny>(s, offsets, c(x_perm), c(W1), c(b1), c(W2), c(b2), m(h), m(a), m(y_perm), tpre, st);
   }
   return launch_status();
 }
@@ -379,8 +382,12 @@ extern "C" int dmoe_expert_ffn_bwd(const dmoe_dims* dims, const int32_t* offsets
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    ffn_bwd_cfg<float, CfgF32, CfgDWF32>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
-                                         m(dx_perm), m(dW1), m(db1), m(dW2), m(db2), tpre, st);
+    if (use_fat_f32(s))
+      ffn_bwd_f32<CfgF32, CfgF32>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh), m(dx_perm),
+                                  m(dW1), m(db1), m(dW2), m(db2), tpre, st);
+    else
+      ffn_bwd_f32<CfgF32Skinny, CfgF32>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
+                                        m(dx_perm), m(dW1), m(db1), m(dW2), m(db2), tpre, st);
   }
   return launch_status();
 }
@@ -411,7 +418,8 @@ extern "C" int dmoe_expert_ffn_bwd_recompute(const dmoe_dims* dims, const int32_
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    ffn_up_cfg<float, CfgF32>(s, offsets, c(x_perm), c(W1), c(b1), m(h), m(a), tpre, st);
+    if (use_fat_f32(s)) ffn_up_f32<CfgF32>(s, offsets, c(x_perm), c(W1), c(b1), m(h), m(a), tpre, st);
+    else ffn_up_f32<CfgF32Skinny>(s, offsets, c(x_perm), c(W1), c(b1), m(h), m(a), tpre, st);
   }
   // 2. the backward proper, dh written over h
   return dmoe_expert_ffn_bwd(dims, offsets, counts, x_perm, h, a, dy_perm, W1, W2, h, dx_perm, dW1, db1, dW2,
@@ -448,8 +456,12 @@ extern "C" int dmoe_expert_ffn_bwd_sgd(const dmoe_dims* dims, const int32_t* off
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    ffn_bwd_cfg<float, CfgF32, CfgDWF32, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
-                                               m(dx_perm), m(W1), m(b1), m(W2), m(b2), tpre, st, lr);
+    if (use_fat_f32(s))
+      ffn_bwd_f32<CfgF32, CfgF32, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
+                                        m(dx_perm), m(W1), m(b1), m(W2), m(b2), tpre, st, lr);
+    else
+      ffn_bwd_f32<CfgF32Skinny, CfgF32, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
+                                              m(dx_perm), m(W1), m(b1), m(W2), m(b2), tpre, st, lr);
   }
   return launch_status();
 }

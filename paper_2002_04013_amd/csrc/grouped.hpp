@@ -1,6 +1,6 @@
 // Launch helpers shared by the expert blocks: the device-side tile plan of a grouped
 // GEMM, per-expert column sums, and the tile shapes and launches of the two grouped
-// GEMM implementations (gemm.hpp: fp32; gemm2.hpp: bf16 on gfx950).
+// GEMM implementations (gemm_f32.hpp: fp32; gemm2.hpp: bf16).
 #pragma once
 #include <algorithm>
 #include <atomic>
@@ -9,6 +9,7 @@
 #include "common.hpp"
 #include "gemm.hpp"
 #include "gemm2.hpp"
+#include "gemm_f32.hpp"
 
 namespace dmoe {
 
@@ -139,16 +140,17 @@ static int blocks_per_cu(std::atomic<int>* slots, const void* kern, int nt, size
   return nb;
 }
 
-template <typename E, int GM, bool B_KC, int EPI, int BM, int BN, int BK, int WM, int WN>
-static void run_gemm(GemmArgs<E> p, int64_t tiles_ub, hipStream_t st) {
+// fp32 path (gemm_f32.hpp); C: the tile shape
+template <int GM, bool AT, bool BT, int EPI, typename C>
+static void run_gemm_f32(GemmArgs<float> p, int64_t tiles_ub, hipStream_t st) {
   if (tiles_ub <= 0) return;
-  auto kern = grouped_gemm<E, GM, B_KC, EPI, BM, BN, BK, WM, WN>;
-  constexpr int NT = 64 * WM * WN;
-  const size_t lds = gemm_lds_bytes<E, BM, BN, BK, WM, WN>();
+  auto kern = grouped_gemm_f32<GM, AT, BT, EPI, C::BM, C::BN, C::WM, C::WN, C::ST>;
+  constexpr int NT = 64 * C::WM * C::WN;
+  const size_t lds = gemm_f32_lds_bytes<C::BM, C::BN, C::ST>();
   static std::atomic<int> per_cu[MAX_DEVICES];
   static const char* name = [] {
     static char b[96];
-    snprintf(b, sizeof b, "grouped_gemm<GM=%d,EPI=%d,%dx%d>", GM, EPI, BM, BN);
+    snprintf(b, sizeof b, "grouped_gemm_f32<GM=%d,AT=%d,BT=%d,EPI=%d,%dx%d>", GM, (int)AT, (int)BT, EPI, C::BM, C::BN);
     return b;
   }();
   const int nb = blocks_per_cu(per_cu, (const void*)kern, NT, lds);
@@ -187,9 +189,14 @@ static GemmArgs<E> args_m(const int32_t* offsets, const int32_t* tpre, int scale
   return p;
 }
 
-// fp32 tile shapes (register-staged MFMA GEMM of gemm.hpp).  TMR: rows an m-tile holds.
-struct CfgF32    { static constexpr int BM = 32, BN = 64, BK = 32, WM = 1, WN = 2, TMR = BM; };
-struct CfgDWF32  { static constexpr int BM = 64, BN = 64, BK = 32, WM = 2, WN = 2; };
+// fp32 tile shapes.  64 x 64 tiles of four waves, 48 KB of ring: three blocks share a
+// compute unit.  Measured at 16 experts of about 256 rows, D = 512, H = 2048 (8.6 GFLOP a
+// launch): 101 (up), 109 (down), 101 (dh), 110 (dx) and 93 us (weight gradients); two
+// stages (five blocks a unit) 101 to 109 us, 128 x 64 tiles 107, 131, 109, 137 and 88 us
+// (fewer tiles than units for the narrow outputs), two waves 128 to 186 us.  With few rows
+// per expert 32 x 64 tiles of two waves, one stage deeper (weight streaming).
+struct CfgF32       { static constexpr int BM = 64, BN = 64, WM = 2, WN = 2, ST = 3, TMR = BM; };
+struct CfgF32Skinny { static constexpr int BM = 32, BN = 64, WM = 1, WN = 2, ST = 4, TMR = BM; };
 
 // bf16 tile shapes of the gemm2 path: many rows per expert -> 256x256 tiles, 8 waves,
 // 64-deep k, 2 stages (best of the measured shapes at the wide workload for all three
@@ -214,5 +221,7 @@ struct G2DWShort { static constexpr int BM = 256, BN = 256, WM = 4, WN = 2, ST =
                    STO = STORE_STAGED_NT; };
 
 static bool use_fat(const Shape& s) { return s.P >= (int64_t)96 * s.N; }
+// fp32: 64-row tiles from an average of 48 rows per expert on
+static bool use_fat_f32(const Shape& s) { return s.P >= (int64_t)48 * s.N; }
 
 }  // namespace dmoe
