@@ -98,10 +98,7 @@ static void ffn_bwd_bf16(const Shape& s, const int32_t* offsets, const bf16* xp,
     p.M = H; p.N = D; p.act = s.act;
     run_gemm2<GROUP_K, true, true, EPI_STORE, CW::BM, CW::BN, CW::WM, CW::WN, CW::ST, CW::BK, CW::STO>(p, active_ub * mt * nt, st);
   }
-  DMOE_LAUNCH(segment_colsum<bf16>, dim3((unsigned)((H / 8 + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dh, (int64_t)H, offsets, H, db1);
-  DMOE_LAUNCH(segment_colsum<bf16>, dim3((unsigned)((D / 8 + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dyp, (int64_t)D, offsets, D, db2);
+  run_colsum<bf16>(s, offsets, dh, H, db1, dyp, D, db2, 0.f, st);
 }
 
 // Backward with the expert parameters updated in place (W <- W - lr dW, b <- b - lr db),
@@ -152,10 +149,7 @@ static void ffn_bwd_sgd_bf16(const Shape& s, const int32_t* offsets, const bf16*
     p.M = H; p.N = D; p.act = s.act; p.lr = lr;
     run_gemm2<GROUP_K, true, true, EPI_SGD, CW::BM, CW::BN, CW::WM, CW::WN, CW::ST, CW::BK, CW::STO>(p, active_ub * mt * nt, st);
   }
-  DMOE_LAUNCH((segment_colsum<bf16, true>), dim3((unsigned)((H / 8 + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dh, (int64_t)H, offsets, H, b1, lr);
-  DMOE_LAUNCH((segment_colsum<bf16, true>), dim3((unsigned)((D / 8 + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dyp, (int64_t)D, offsets, D, b2, lr);
+  run_colsum<bf16, true>(s, offsets, dh, H, b1, dyp, D, b2, lr, st);
 }
 
 template <typename C>
@@ -242,12 +236,7 @@ static void ffn_bwd_f32(const Shape& s, const int32_t* offsets, const float* xp,
     p.M = H; p.N = D; p.act = s.act; p.lr = lr;
     run_gemm_f32<GROUP_K, true, true, EPI_W, CW>(p, active_ub * mt * nt, st);
   }
-  // bias gradients
-  constexpr int VEC = 4;
-  DMOE_LAUNCH((segment_colsum<float, SGD>), dim3((unsigned)((H / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dh, (int64_t)H, offsets, H, db1, lr);
-  DMOE_LAUNCH((segment_colsum<float, SGD>), dim3((unsigned)((D / VEC + 255) / 256), (unsigned)N), dim3(256), 0,
-                     st, dyp, (int64_t)D, offsets, D, db2, lr);
+  run_colsum<float, SGD>(s, offsets, dh, H, db1, dyp, D, db2, lr, st);   // bias gradients
 }
 
 template <typename C>
