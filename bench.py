@@ -135,7 +135,7 @@ def kernel_algorithmic(name, wl, counts, sgd=False):
 
 def _routing_kernel_algorithmic(name, wl, rows, e):
     T, D, k, dM = wl.T, wl.D, wl.k, wl.dM
-    if name.startswith("gate_topk_mfma"):
+    if name.startswith(("gate_topk_mfma", "gate_topk_f64")):
         return "gate scores + TopK (MFMA)", 2 * T * D * dM, T * D * e + dM * D * e + T * k * 12
     if name.startswith("gather_rows"):
         return "dispatch row gather", 0, T * D * e + rows * D * e
@@ -537,7 +537,7 @@ def run_workload(name, steps, warmup, recompute=False, sgd=False, alive_topk=Fal
         ck = {}
         for ctr in ctrs:
             for kname, t in ctr.kernels():
-                if kname.startswith("gate_topk_mfma") or kname.startswith("gather_rows"):
+                if kname.startswith(("gate_topk_mfma", "gate_topk_f64", "gather_rows")):
                     ck.setdefault(kname, []).append(t)
         cold = {}
         for n in ("gate_topk", "dispatch"):

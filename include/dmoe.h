@@ -77,7 +77,7 @@ typedef struct {
 } dmoe_dims;
 
 /* dmoe_dims.flags: DMOE_FLAG_GATE_EXACT makes dmoe_gate_topk compute every token's
- * bf16 gate scores with exact fp64 accumulation (the path it otherwise takes only
+ * bf16 gate scores with exact fp64 accumulation (the path large calls otherwise take only
  * for tokens whose MFMA-computed decision is not certified).  Results are the same;
  * only the speed differs. */
 /* DMOE_FLAG_ALIVE_TOPK makes TopK choose among the alive experts only (the partially

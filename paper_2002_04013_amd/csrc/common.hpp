@@ -35,6 +35,8 @@ __device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
 }
 __device__ __forceinline__ bf16 f2bf(float f) { return (bf16)(f2bf2(f, 0.f) & 0xffffu); }
 
+template <typename T> struct type_tag { using type = T; };
+
 template <typename E> __device__ __forceinline__ float ldf(const E* p);
 template <> __device__ __forceinline__ float ldf<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float ldf<bf16>(const bf16* p) { return bf2f(*p); }

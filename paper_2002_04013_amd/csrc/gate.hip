@@ -1,5 +1,6 @@
 // Structured gate, exact TopK over the expert grid and Eq. 1 weights
 // (Sec. 3.2, Eq. 1, App. C), plus the gate's backward pass.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -8,17 +9,14 @@
 
 namespace dmoe {
 
-constexpr int GATE_TB = 32;     // tokens per block
-constexpr int GATE_KC = 16;     // k chunk staged in LDS
-constexpr int GATE_NT = 256;
-
 struct GateArgs {
   const void* x; const void* Wg; const void* bg; const uint8_t* alive;
   int32_t* idx; float* w; float* g; float* scores;
   int T, D, d, M, k, dM, N;
 };
 
-// One token's selection from its fp64 gate scores s64[d*M] (Sec. 3.2, Eq. 1, App. C):
+// One token's certified selection by one lane, from its MFMA scores s64[d*M] (Sec. 3.2,
+// Eq. 1, App. C):
 //  * decision scores are the fp32 roundings of the scores;
 //  * per dimension, the best min(K1, M) indices by (score desc, index asc), kept in
 //    registers by an insertion network (ties keep the earlier, lower index);
@@ -27,29 +25,29 @@ struct GateArgs {
 //    prod(r_i + 1) - 1 cells taking an equal or better index in every dimension),
 //    ranked by their fp64 total of d fp32 values in dimension order, ties to the
 //    lower flat index;
+//  * K1 = k+1 cells (k if k = N) are ranked, and the selection is kept only if their
+//    totals are separated by more than 2E, E = d (delta_max + amax 2^-23) with
+//    delta = gam * ab[c] the bound on the score's accumulation error, and if the nonzero
+//    scores span less than 2^25 in magnitude (beyond it an fp64 total of d fp32 values may
+//    round and the dominance argument no longer holds exactly).  Returns false (nothing
+//    written) otherwise;
 //  * Eq. 1 weights over the chosen experts that are alive, from fp64 totals.
-// When the nonzero scores span more than 2^26 in magnitude, an fp64 total of d fp32
-// values may round and the dominance argument no longer holds exactly; then every
-// cell of the grid is ranked.
-// CERT (bf16 MFMA scores): K1 = k+1 cells (k if k = N) are ranked, and the selection
-// is kept only if their totals are separated by more than 2E, E = d (delta_max +
-// amax 2^-23) with delta = gam * ab[c] the bound on the score's accumulation error;
-// the span must stay below 2^25.  Returns false (nothing written) otherwise.
 // CAP: list capacity, at least K1 (the callers pick 5 when K1 <= 5, else KMAX + 1;
 // for ALIVE 7 when k <= 4, else KMAX + 3).
-// ALIVE (TopK among the alive experts, with CERT): the K1 = min(N, CAP) best cells are
+// ALIVE (TopK among the alive experts): the K1 = min(N, CAP) best cells are
 // ranked the same way; walking them in order, the first k alive ones are the k best
 // alive experts of the whole grid as soon as the k-th of them lies within those K1 (a
 // cell outside the K1 best is beaten by all of them).  The selection is kept if the
 // k-th alive cell is found there, the totals up to the cell after it are separated by
 // more than 2E (or every cell was ranked), and the span condition holds; otherwise
 // nothing is written (the token goes to the exact alive-first path).
-template <bool CERT, int CAP, bool ALIVE = false>
+// One lane per token is the form with the least work per token; the exact kernels below
+// select with a wave per token, which has the lower latency.
+template <int CAP, bool ALIVE>
 __device__ __forceinline__ bool select_token_cap(const double* s64, const float* ab, const uint8_t* alive, int d,
                                                  int M, int k, int N, float gam, int32_t* idx_out, float* w_out,
                                                  float* g_out) {
-  static_assert(!ALIVE || CERT, "alive-first selection on certified MFMA scores");
-  const int K1 = ALIVE ? (N < CAP ? N : CAP) : (CERT && k < N ? k + 1 : k);
+  const int K1 = ALIVE ? (N < CAP ? N : CAP) : (k < N ? k + 1 : k);
   const int L = K1 < M ? K1 : M;
   float lv[DMAX][CAP];
   int li[DMAX][CAP];
@@ -64,7 +62,7 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
         int id = u;
         const float av = fabsf(v);
         if (av > 0.f) { amax = fmaxf(amax, av); amin = fminf(amin, av); }
-        if constexpr (CERT) dmax = fmaxf(dmax, gam * ab[i * M + u]);
+        dmax = fmaxf(dmax, gam * ab[i * M + u]);
 #pragma unroll
         for (int p = 0; p < CAP; ++p) {
           const bool sw = v > lv[i][p];
@@ -91,9 +89,8 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
       v = sw ? ov : v; f = sw ? of : f; uu = sw ? ou : uu;
     }
   };
-  const bool narrow = !(amax > 0.f) || amax <= amin * (CERT ? 33554432.f : 67108864.f);   // 2^25 / 2^26
-  if (CERT && !narrow) return false;
-  if (narrow) {
+  if (amax > 0.f && !(amax <= amin * 33554432.f)) return false;   // span 2^25
+  {
     // odometer over the rank digits r_0 .. r_{d-1} (last digit fastest), visiting only
     // the tuples with prod(r_i + 1) <= K1: a digit whose prefix product would exceed
     // K1 carries into the previous digit at once
@@ -138,24 +135,6 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
       }
       if (carry) break;                  // every digit wrapped: done
     }
-  } else {
-    int u[DMAX];
-#pragma unroll
-    for (int i = 0; i < DMAX; ++i) u[i] = 0;
-    for (int f = 0; f < N; ++f) {
-      double tot = 0.0;
-      int uu = 0;
-#pragma unroll
-      for (int i = 0; i < DMAX; ++i) if (i < d) { tot += (double)(float)s64[i * M + u[i]]; uu |= u[i] << (8 * i); }
-      insert(tot, f, uu);
-#pragma unroll
-      for (int i = DMAX - 1; i >= 0; --i) {        // next flat index: last dim fastest
-        if (i < d) {
-          if (++u[i] < M) break;
-          u[i] = 0;
-        }
-      }
-    }
   }
   if constexpr (ALIVE) {
     // the first k alive cells among the K1 best; position of the k-th
@@ -190,7 +169,7 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
         ++w;
       }
     }
-  } else if constexpr (CERT) {
+  } else {
     const double E = (double)d * ((double)dmax + (double)amax * 1.1920928955078125e-7);
     bool sep = true;
 #pragma unroll
@@ -235,90 +214,15 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
   return true;
 }
 
-template <bool CERT, bool ALIVE = false>
+template <bool ALIVE>
 __device__ __forceinline__ bool select_token(const double* s64, const float* ab, const uint8_t* alive, int d, int M,
                                              int k, int N, float gam, int32_t* idx_out, float* w_out, float* g_out) {
   if constexpr (ALIVE) {      // k + 3 cells ranked: up to two dead ones ahead of the k-th alive
-    if (k <= 4) return select_token_cap<true, 7, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
-    return select_token_cap<true, KMAX + 3, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+    if (k <= 4) return select_token_cap<7, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+    return select_token_cap<KMAX + 3, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
   }
-  const int K1 = CERT && k < N ? k + 1 : k;
-  if (K1 <= 5) return select_token_cap<CERT, 5>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
-  return select_token_cap<CERT, KMAX + 1>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
-}
-
-template <typename E>
-__global__ void __launch_bounds__(GATE_NT) gate_topk_kernel(GateArgs a) {
-  extern __shared__ __align__(16) unsigned char sm[];
-  const int dM = a.dM;
-  double* xs = reinterpret_cast<double*>(sm);                         // [TB][KC]
-  double* wsT = xs + GATE_TB * GATE_KC;                               // [KC][dM]
-  double* s64 = wsT + GATE_KC * dM;                                   // [TB][dM + 1]
-
-  const int tid = threadIdx.x;
-  const int t0 = blockIdx.x * GATE_TB;
-  const E* x = reinterpret_cast<const E*>(a.x);
-  const E* W = reinterpret_cast<const E*>(a.Wg);
-  constexpr int TG = GATE_TB / 8;            // token groups of 8
-  const int items = dM * TG;                 // (column, token group) work items
-  constexpr int IPT = DM_MAX * TG / GATE_NT;
-  double acc[IPT][8];
-#pragma unroll
-  for (int it = 0; it < IPT; ++it)
-#pragma unroll
-    for (int r = 0; r < 8; ++r) acc[it][r] = 0.0;
-
-  for (int k0 = 0; k0 < a.D; k0 += GATE_KC) {
-    for (int q = tid; q < GATE_TB * GATE_KC; q += GATE_NT) {
-      const int tt = q / GATE_KC, kk = q % GATE_KC;
-      const int t = t0 + tt;
-      xs[q] = t < a.T ? (double)ldf(x + (int64_t)t * a.D + k0 + kk) : 0.0;
-    }
-    for (int q = tid; q < GATE_KC * dM; q += GATE_NT) {
-      const int c = q / GATE_KC, kk = q % GATE_KC;
-      wsT[kk * dM + c] = (double)ldf(W + (int64_t)c * a.D + k0 + kk);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < IPT; ++it) {
-      const int item = tid + it * GATE_NT;
-      if (item < items) {
-        const int c = item % dM, tg = item / dM;
-        for (int kk = 0; kk < GATE_KC; ++kk) {
-          const double wv = wsT[kk * dM + c];
-#pragma unroll
-          for (int r = 0; r < 8; ++r) acc[it][r] = fma(xs[(tg * 8 + r) * GATE_KC + kk], wv, acc[it][r]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int it = 0; it < IPT; ++it) {
-    const int item = tid + it * GATE_NT;
-    if (item < items) {
-      const int c = item % dM, tg = item / dM;
-      const double b = a.bg ? (double)ldf(reinterpret_cast<const E*>(a.bg) + c) : 0.0;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const double v = acc[it][r] + b;
-        const int tt = tg * 8 + r;
-        s64[tt * (dM + 1) + c] = v;
-      }
-    }
-  }
-  __syncthreads();
-  if (a.scores) {
-    for (int q = tid; q < GATE_TB * dM; q += GATE_NT) {
-      const int t = t0 + q / dM;
-      if (t < a.T) a.scores[(int64_t)t * dM + q % dM] = (float)s64[(q / dM) * (dM + 1) + q % dM];
-    }
-  }
-  if (tid < GATE_TB && t0 + tid < a.T) {
-    const int t = t0 + tid;
-    select_token<false>(s64 + tid * (dM + 1), nullptr, a.alive, a.d, a.M, a.k, a.N, 0.f,
-                        a.idx + (int64_t)t * a.k, a.w + (int64_t)t * a.k, a.g ? a.g + (int64_t)t * a.k : nullptr);
-  }
+  if (k + 1 <= 5) return select_token_cap<5, false>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+  return select_token_cap<KMAX + 1, false>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
 }
 
 // ---------------------------------------------------------------- bf16: MFMA scores + certificate
@@ -333,7 +237,7 @@ __global__ void __launch_bounds__(GATE_NT) gate_topk_kernel(GateArgs a) {
 // each, a cell total by at most d (delta + ulp) =: E.  If the k+1 best cells (k when
 // k = N) are separated by gaps larger than 2E, the exact scores give the same TopK in
 // the same order; such tokens are certified.  The others are appended to a device
-// queue and recomputed with exact fp64 accumulation by gate_exact_kernel.
+// queue and recomputed with exact fp64 accumulation by gate_exact_sparse_kernel.
 
 constexpr int GM_TOK = 32;        // tokens per block (one MFMA row block)
 constexpr int GM_RING = 2;        // x groups (32 tokens x 64 d_model, 4 KB) in flight per wave
@@ -346,7 +250,6 @@ constexpr int GX_NT = 512;        // exact recomputation: threads per token
 
 struct GateMfmaArgs {
   GateArgs a;
-  int flags;
   float gam;                       // gamma_32 + (D/32+8) 2^-52, times 1/(1 - gamma_D)
   int32_t* queue;                  // [0] count, [GQ_HEAD + i] token ids
 };
@@ -377,12 +280,6 @@ __global__ void __launch_bounds__(64 * KW) gate_topk_mfma(GateMfmaArgs ga) {
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int t0 = blockIdx.x * GM_TOK;
-  const bool exact_all = (ga.flags & DMOE_FLAG_GATE_EXACT) != 0;
-  if (exact_all) {                       // every token goes to the exact path
-    if (threadIdx.x < GM_TOK && t0 + threadIdx.x < a.T)
-      ga.queue[GQ_HEAD + atomicAdd(ga.queue, 1)] = t0 + threadIdx.x;
-    return;
-  }
   const bf16* x = reinterpret_cast<const bf16*>(a.x);
   const bf16* W = reinterpret_cast<const bf16*>(a.Wg);
   const bf16* bg = reinterpret_cast<const bf16*>(a.bg);
@@ -491,7 +388,7 @@ __global__ void __launch_bounds__(64 * KW) gate_topk_mfma(GateMfmaArgs ga) {
   }
   if (threadIdx.x < GM_TOK && t0 + (int)threadIdx.x < a.T) {
     const int t = t0 + threadIdx.x;
-    const bool ok = select_token<true, ALIVE>(s64 + lane * SLD, ab + lane * SLD, a.alive, a.d, a.M, a.k, a.N, ga.gam,
+    const bool ok = select_token<ALIVE>(s64 + lane * SLD, ab + lane * SLD, a.alive, a.d, a.M, a.k, a.N, ga.gam,
                                        a.idx + (int64_t)t * a.k, a.w + (int64_t)t * a.k,
                                        a.g ? a.g + (int64_t)t * a.k : nullptr);
     if (!ok) ga.queue[GQ_HEAD + atomicAdd(ga.queue, 1)] = t;
@@ -512,18 +409,6 @@ __device__ __forceinline__ bool cell_gt(uint32_t al, uint64_t at, uint32_t an, u
   return (al > bl) | ((al == bl) & ((at > bt) | ((at == bt) & (an > bn))));
 }
 
-// Exact path for the queued tokens: fp64 scores S[c] = sum_k x_k W[c][k] + b[c], then the
-// selection.  Persistent blocks over the queue; a pass takes TB tokens: GX_TB = 8 where
-// every token is queued (alive-first TopK, or exact scores asked for: the tokens of a
-// pass share each load of Wg, and one wave selects for each), 1 for the few tokens the
-// certificate rejects (lowest latency, two blocks per compute unit).  Wave w owns the gate columns
-// [w cpw, (w+1) cpw), cpw = ceil(dM / 8), GX_CT at a time; lane l sums the 16-byte
-// vectors l, l + 64, ... of the rows (each wave load is 1 KB of one row) with fp64
-// FMAs of the exact element values, P vectors' loads issued before any is used; a
-// shuffle tree adds the 64 lane sums.
-constexpr int GX_CT = 4;          // gate columns per wave pass of the exact scores
-constexpr int GX_TB = 8;          // tokens per pass when every token is queued (one per wave)
-
 // Element q (compile-time after unrolling) of a 16-byte vector, as a float.
 template <typename E> __device__ __forceinline__ float vec_elem(const uint4& v, int q);
 template <> __device__ __forceinline__ float vec_elem<float>(const uint4& v, int q) {
@@ -534,8 +419,345 @@ template <> __device__ __forceinline__ float vec_elem<bf16>(const uint4& v, int 
   return __uint_as_float((q & 1) ? (w & 0xffff0000u) : (w << 16));
 }
 
-template <typename E, int TB, int P>
-__device__ __forceinline__ void exact_scores(const GateArgs& a, const int* tok, double (*s64)[DM_MAX]) {
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t u64_max_dpp(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(v >> 32), (int)(uint32_t)(v >> 32), CTRL,
+                                                            ROWS, 0xf, false);
+  const uint64_t o = ((uint64_t)hi << 32) | lo;
+  return o > v ? o : v;
+}
+
+// Maximum of a 64-bit value over the wave (every lane gets it): within each row of 16
+// lanes by DPP exchanges (lane i with i^1, i^2, 7-i, 15-i), then row r-1's last lane into
+// row r (rows 1 and 3) and lane 31 into rows 2 and 3, so that lane 63 holds the maximum.
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+  v = u64_max_dpp<0xB1, 0xf>(v);       // quad_perm [1,0,3,2]
+  v = u64_max_dpp<0x4E, 0xf>(v);       // quad_perm [2,3,0,1]
+  v = u64_max_dpp<0x141, 0xf>(v);      // row_half_mirror
+  v = u64_max_dpp<0x140, 0xf>(v);      // row_mirror
+  v = u64_max_dpp<0x142, 0xa>(v);      // row_bcast:15
+  v = u64_max_dpp<0x143, 0xc>(v);      // row_bcast:31
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+}
+
+// The rank tuples (r_0 .. r_{d-1}) with prod(r_i + 1) <= K1, in order of the product: the
+// cells of a grid that can be among its K1 best (a cell with per-dimension ranks r_i is
+// beaten by the prod(r_i + 1) - 1 cells that take an equal or better index in every
+// dimension).  Those of a smaller K1 are a prefix.  4 bits per digit.
+constexpr int RANK_KMAX = KMAX + 3;      // largest K1
+constexpr int RANK_TUPLES = 96;          // 93 tuples for d = 4, K1 = 11
+struct RankTable {
+  uint16_t tup[DMAX][RANK_TUPLES];
+  uint8_t cnt[DMAX][RANK_KMAX + 1];
+};
+constexpr RankTable make_rank_table() {
+  RankTable q{};
+  for (int d = 1; d <= DMAX; ++d) {
+    int n = 0;
+    for (int prod = 1; prod <= RANK_KMAX; ++prod) {
+      for (int r0 = 0; r0 < prod; ++r0)
+        for (int r1 = 0; r1 < (d > 1 ? prod : 1); ++r1)
+          for (int r2 = 0; r2 < (d > 2 ? prod : 1); ++r2)
+            for (int r3 = 0; r3 < (d > 3 ? prod : 1); ++r3)
+              if ((r0 + 1) * (r1 + 1) * (r2 + 1) * (r3 + 1) == prod)
+                q.tup[d - 1][n++] = (uint16_t)(r0 | (r1 << 4) | (r2 << 8) | (r3 << 12));
+      q.cnt[d - 1][prod] = (uint8_t)n;
+    }
+  }
+  return q;
+}
+static __device__ const RankTable rank_table = make_rank_table();
+
+// Orders the LDS operations of one wave for the compiler; the hardware keeps their order.
+__device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// This lane's candidate tuples (the cells ranked for K1) and how many there are.
+struct RankTuples { int cnt, tup[2]; };
+template <bool ALIVE> __device__ __forceinline__ int rank_k1(const GateArgs& a) {
+  return ALIVE ? min(a.N, RANK_KMAX) : a.k;
+}
+template <bool ALIVE> __device__ __forceinline__ RankTuples rank_tuples(const GateArgs& a) {
+  const int lane = threadIdx.x & 63;
+  RankTuples r;
+  r.cnt = rank_table.cnt[a.d - 1][rank_k1<ALIVE>(a)];
+  r.tup[0] = rank_table.tup[a.d - 1][lane];
+  r.tup[1] = rank_table.tup[a.d - 1][min(lane + 64, RANK_TUPLES - 1)];
+  return r;
+}
+
+// Per-wave LDS of the selection.
+constexpr int RANK_LIVE = 1 << 30;       // N <= 16384
+struct SelectScratch {
+  float dec[DM_MAX + 4 * DMAX];          // decision scores, each dimension padded to 4 with -inf
+  float lv[DMAX][RANK_KMAX + 1];         // per dimension, the best indices: score and index
+  int li[DMAX][RANK_KMAX + 1];
+  double tot[RANK_TUPLES];               // candidate cells: total, flat index
+  int flat[RANK_TUPLES];
+  int rf[RANK_KMAX + 1], ru[RANK_KMAX + 1];   // by rank: flat index (bit 30: the expert responds), grid indices (8 bits each)
+  int own[RANK_KMAX + 1];                     // by rank: the candidate that wrote it
+};
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t u32_max_dpp(uint32_t v) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+  return o > v ? o : v;
+}
+// As wave_max_u64, of 32 bits.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = u32_max_dpp<0xB1, 0xf>(v);
+  v = u32_max_dpp<0x4E, 0xf>(v);
+  v = u32_max_dpp<0x141, 0xf>(v);
+  v = u32_max_dpp<0x140, 0xf>(v);
+  v = u32_max_dpp<0x142, 0xa>(v);
+  v = u32_max_dpp<0x143, 0xc>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// TopK by its definition for one token, by one wave: k rounds over every cell of the grid
+// (lane l scans the cells l, l + 64, ..., mixed-radix digits advanced by 64 per cell), each
+// taking the best cell after the one taken before: (alive first when ALIVE, total desc, flat
+// asc), the totals adding the d fp32 decision scores in fp64 in dimension order.  Rarely
+// reached, and written for few registers: it shares the kernels' budget.
+template <bool ALIVE>
+__device__ __forceinline__ void rank_all_wave(const GateArgs& a, const double* sc, int* rf, int* ru) {
+  const int lane = threadIdx.x & 63;
+  const int d = a.d, M = a.M, N = a.N;
+  uint32_t pl = 2u;                                                  // above every cell
+  uint64_t pt = 0ull;
+  uint32_t pn = 0u;
+  for (int r = 0; r < a.k; ++r) {
+    int u[DMAX], st[DMAX];
+    {
+      int rl = lane, rs = 64;
+#pragma unroll
+      for (int i = DMAX - 1; i >= 0; --i) {
+        u[i] = 0; st[i] = 0;
+        if (i < d) { u[i] = rl % M; rl /= M; st[i] = rs % M; rs /= M; }
+      }
+    }
+    uint32_t bl = 0u, bn = 0u;                                       // below every cell (keys > 0)
+    uint64_t bt = 0ull;
+    int bu = 0;
+    for (int f = lane; f < N; f += 64) {
+      double tot = 0.0;
+      int uu = 0, carry = 0;
+#pragma unroll
+      for (int i = 0; i < DMAX; ++i)
+        if (i < d) { tot += (double)(float)sc[i * M + u[i]]; uu |= u[i] << (8 * i); }
+      const uint32_t l = !ALIVE || a.alive == nullptr || a.alive[f] != 0 ? 1u : 0u;
+      const uint64_t tt = ord64(tot + 0.0);                          // -0 and +0 are one value
+      const uint32_t n = ~(uint32_t)f;
+      if (cell_gt(pl, pt, pn, l, tt, n) && cell_gt(l, tt, n, bl, bt, bn)) { bl = l; bt = tt; bn = n; bu = uu; }
+#pragma unroll
+      for (int i = DMAX - 1; i >= 0; --i) {                          // digits of f + 64
+        if (i < d) {
+          u[i] += st[i] + carry;
+          carry = u[i] >= M;
+          u[i] -= carry ? M : 0;
+        }
+      }
+    }
+    const uint32_t lmax = __ballot(bl != 0u) != 0ull ? 1u : 0u;
+    const uint64_t tmax = wave_max_u64(bl == lmax ? bt : 0ull);
+    const uint64_t nmax = wave_max_u64(bl == lmax && bt == tmax ? (uint64_t)bn : 0ull);
+    pl = lmax; pt = tmax; pn = (uint32_t)nmax;
+    if (bl == lmax && bt == tmax && bn == pn) {
+      const int f = (int)~bn;
+      rf[r] = f | (a.alive == nullptr || a.alive[f] != 0 ? RANK_LIVE : 0);
+      ru[r] = bu;
+    }
+  }
+  wave_lds_sync();
+}
+
+// One token's exact selection by one wave from its fp64 scores sc[d*M] in LDS: the same
+// definition as select_token_cap without a certificate (the scores are exact).  Nothing is
+// serial in k or M: a lane holds one or two gate columns and counts the columns of its
+// dimension that beat it, which is the column's rank; a lane holds one or two candidate
+// tuples and counts the candidates that beat its total.  Equal values are found by reading
+// the rank slots back, and ranked again by (value desc, index asc).
+// ALIVE: K1 = min(N, 11) cells are ranked and the first k alive ones taken; with
+// fewer alive among them, or where fp64 totals may round (nonzero scores spanning more than
+// 2^26), every cell of the grid is ranked.
+template <bool ALIVE>
+__device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples& rt, const double* sc,
+                                            SelectScratch& q, int t) {
+  const int lane = threadIdx.x & 63;
+  const int d = a.d, M = a.M, k = a.k, N = a.N, dM = a.dM;
+  const int M4 = (M + 3) & ~3;
+  const int K1 = rank_k1<ALIVE>(a);
+  const int L = min(K1, M);
+  // decision scores, their span, and safe contents for the rank slots (NaN scores leave
+  // slots unwritten: the choice is then unspecified but valid)
+  int ci[2], cu[2];
+  float cv[2];
+  float amax = 0.f, amin = 3.4e38f;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int c = lane + 64 * h;
+    ci[h] = (c >= M) + (c >= 2 * M) + (c >= 3 * M);
+    cu[h] = c - ci[h] * M;
+    cv[h] = 0.f;
+    if (c < dM) {
+      cv[h] = (float)sc[c];
+      q.dec[ci[h] * M4 + cu[h]] = cv[h];
+      const float av = fabsf(cv[h]);
+      if (av > 0.f) { amax = fmaxf(amax, av); amin = fminf(amin, av); }
+    }
+  }
+  for (int p = lane; p < d * (M4 - M); p += 64) q.dec[(p / (M4 - M)) * M4 + M + p % (M4 - M)] = -INFINITY;
+  if (lane < DMAX * (RANK_KMAX + 1)) { (&q.lv[0][0])[lane] = -INFINITY; (&q.li[0][0])[lane] = 0; }
+  if (lane <= RANK_KMAX) { q.rf[lane] = min(lane, N - 1); q.ru[lane] = 0; q.own[lane] = -1; }
+  // magnitudes are not negative, so their bit patterns are ordered as they are
+  amax = __uint_as_float(wave_max_u32(__float_as_uint(amax)));
+  amin = __uint_as_float(~wave_max_u32(~__float_as_uint(amin)));
+  bool full = amax > 0.f && !(amax <= amin * 67108864.f);            // span 2^26
+  wave_lds_sync();
+  // rank of each column in its dimension
+  int rk[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    rk[h] = L;
+    if (lane + 64 * h < dM) {
+      const float* dv = q.dec + ci[h] * M4;
+      int r = 0;
+      for (int u = 0; u < M4; u += 4) {
+        const float4 o = *reinterpret_cast<const float4*>(dv + u);
+        r += (o.x > cv[h]) + (o.y > cv[h]) + (o.z > cv[h]) + (o.w > cv[h]);
+      }
+      rk[h] = r;
+    }
+  }
+  auto put_lists = [&]() {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (rk[h] < L) { q.lv[ci[h]][rk[h]] = cv[h]; q.li[ci[h]][rk[h]] = cu[h]; }
+    wave_lds_sync();
+  };
+  put_lists();
+  bool clash = false;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) clash |= rk[h] < L && q.li[ci[h]][rk[h]] != cu[h];
+  if (__ballot(clash)) {                                             // equal scores: by index
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (rk[h] < L) {
+        const float* dv = q.dec + ci[h] * M4;
+        for (int u = 0; u < cu[h]; ++u) rk[h] += dv[u] == cv[h];
+      }
+    put_lists();
+  }
+  // candidate cells
+  const int cnt = rt.cnt;
+  double tv[2];
+  int tf[2], tu[2];
+  bool tk[2], lv[2] = {false, false};   // lv: alive, loaded while the ranks are counted
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int p = lane + 64 * h;
+    tv[h] = -INFINITY; tf[h] = 0x7fffffff; tu[h] = 0; tk[h] = p < cnt;
+    if (p < cnt) {
+      const int tup = rt.tup[h];
+      double tot = 0.0;
+      int flat = 0, uu = 0;
+#pragma unroll
+      for (int i = 0; i < DMAX; ++i) {
+        if (i < d) {
+          const int r = (tup >> (4 * i)) & 15;
+          if (r >= L) { tk[h] = false; continue; }
+          const int u = q.li[i][r];
+          tot += (double)q.lv[i][r];
+          flat = flat * M + u;
+          uu |= u << (8 * i);
+        }
+      }
+      if (tk[h]) {
+        tv[h] = tot; tf[h] = flat; tu[h] = uu;
+        lv[h] = a.alive == nullptr || a.alive[flat] != 0;
+      }
+      q.tot[p] = tv[h];
+      q.flat[p] = tf[h];
+    }
+  }
+  wave_lds_sync();
+  int rc[2] = {0, 0};
+  for (int o = 0; o < cnt; ++o) {
+    const double v = q.tot[o];
+    rc[0] += v > tv[0];
+    if (cnt > 64) rc[1] += v > tv[1];
+  }
+  auto put_cells = [&]() {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (tk[h] && rc[h] < K1) {
+        q.rf[rc[h]] = tf[h] | (lv[h] ? RANK_LIVE : 0);
+        q.ru[rc[h]] = tu[h];
+        q.own[rc[h]] = lane + 64 * h;
+      }
+    wave_lds_sync();
+  };
+  put_cells();
+  clash = false;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) clash |= tk[h] && rc[h] < K1 && q.own[rc[h]] != lane + 64 * h;
+  if (__ballot(clash)) {                                             // equal totals: by flat index
+    for (int o = 0; o < cnt; ++o) {
+      const double v = q.tot[o];
+      const int fo = q.flat[o];
+      rc[0] += (v == tv[0]) & (fo < tf[0]);
+      rc[1] += (v == tv[1]) & (fo < tf[1]);
+    }
+    put_cells();
+  }
+  if constexpr (ALIVE) {
+    // the first k alive of the K1 ranked cells, in order
+    const int cf = lane < K1 ? q.rf[lane] : 0, cuu = lane < K1 ? q.ru[lane] : 0;
+    const uint64_t am = __ballot(lane < K1 && (cf & RANK_LIVE));
+    full |= __popcll(am) < k;
+    const int pos = __popcll(am & ((1ull << lane) - 1ull));
+    if ((am >> lane) & 1ull) { q.rf[pos] = cf; q.ru[pos] = cuu; }
+    wave_lds_sync();
+  }
+  if (full) rank_all_wave<ALIVE>(a, sc, q.rf, q.ru);
+  const int fl = lane < k ? q.rf[lane] : 0, uu = lane < k ? q.ru[lane] : 0;
+  const int f = fl & (RANK_LIVE - 1);
+  // Eq. 1 weights from the fp64 totals of the chosen experts, over the alive ones: lane j
+  // holds the j-th, sums in slot order
+  const bool live = (fl & RANK_LIVE) != 0;
+  double gx = 0.0;
+#pragma unroll
+  for (int i = 0; i < DMAX; ++i) if (i < d) gx += sc[i * M + ((uu >> (8 * i)) & 0xff)];
+  double m = live ? gx : -1.0e308;
+#pragma unroll
+  for (int o = 1; o < KMAX; o <<= 1) {
+    const double om = __shfl_xor(m, o, 64);
+    m = om > m ? om : m;
+  }
+  const float ex = live ? expf((float)(gx - m)) : 0.f;
+  float sum = 0.f;
+#pragma unroll
+  for (int j = 0; j < KMAX; ++j) sum += __shfl(ex, j, 64);
+  const bool any = (__ballot(live) & 0xffull) != 0ull;
+  if (lane < k) {
+    a.idx[(int64_t)t * k + lane] = f;
+    a.w[(int64_t)t * k + lane] = any ? ex / sum : 0.f;
+    if (a.g) a.g[(int64_t)t * k + lane] = (float)gx;
+  }
+}
+
+// Exact fp64 scores S[c] = sum_k x_k W[c][k] + b[c] of one bf16 token by a block of GX_NT
+// threads.  Wave w owns the gate columns [w cpw, (w+1) cpw), cpw = ceil(dM / 8), GX_CT at a
+// time; lane l sums the 16-byte vectors l, l + 64, ... of the rows (each wave load is 1 KB
+// of one row) with fp64 FMAs of the exact element values, GX_P vectors' loads issued before
+// any is used; a shuffle tree adds the 64 lane sums.
+constexpr int GX_CT = 4;          // gate columns per wave pass
+constexpr int GX_P = 3;           // 16-byte vectors in flight
+__device__ __forceinline__ void exact_scores(const GateArgs& a, int t, double* s64) {
+  using E = bf16;
+  constexpr int TB = 1, P = GX_P;
+  const int tok[1] = {t};
   constexpr int VEC = 16 / sizeof(E);
   constexpr int NW = GX_NT / 64;
   const int lane = threadIdx.x & 63;
@@ -595,245 +817,142 @@ __device__ __forceinline__ void exact_scores(const GateArgs& a, const int* tok, 
         double v = acc[t][c];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0 && c0 + c < cend) s64[t][c0 + c] = v + (bg ? (double)ldf(bg + c0 + c) : 0.0);
+        if (lane == 0 && c0 + c < cend) s64[c0 + c] = v + (bg ? (double)ldf(bg + c0 + c) : 0.0);
       }
     }
   }
 }
 
-// Cell key (live, ord64(total), ~flat): the lexicographic maximum is the best cell.
-struct CellKey { uint32_t l; uint64_t t; uint32_t n; };
-
-__device__ __forceinline__ bool key_gt(const CellKey& a, const CellKey& b) {
-  return cell_gt(a.l, a.t, a.n, b.l, b.t, b.n);
-}
-__device__ __forceinline__ CellKey key_sel(bool c, const CellKey& a, const CellKey& b) {
-  return CellKey{c ? a.l : b.l, c ? a.t : b.t, c ? a.n : b.n};
-}
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t u64_max_dpp(uint64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(v >> 32), (int)(uint32_t)(v >> 32), CTRL,
-                                                            ROWS, 0xf, false);
-  const uint64_t o = ((uint64_t)hi << 32) | lo;
-  return o > v ? o : v;
-}
-
-// Maximum of a 64-bit value over the wave (every lane gets it): within each row of 16
-// lanes by DPP exchanges (lane i with i^1, i^2, 7-i, 15-i), then row r-1's last lane into
-// row r (rows 1 and 3) and lane 31 into rows 2 and 3, so that lane 63 holds the maximum.
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-  v = u64_max_dpp<0xB1, 0xf>(v);       // quad_perm [1,0,3,2]
-  v = u64_max_dpp<0x4E, 0xf>(v);       // quad_perm [2,3,0,1]
-  v = u64_max_dpp<0x141, 0xf>(v);      // row_half_mirror
-  v = u64_max_dpp<0x140, 0xf>(v);      // row_mirror
-  v = u64_max_dpp<0x142, 0xa>(v);      // row_bcast:15
-  v = u64_max_dpp<0x143, 0xc>(v);      // row_bcast:31
-  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
-         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
-}
-
-// TopK by its definition for one token, by one wave: every cell of the grid is ranked by
-// (alive first when ALIVE, total desc, flat asc), the totals adding the d fp32 decision
-// scores sd (as fp64) in fp64 in dimension order.  Lane l scans the cells l, l + 64, ...
-// (mixed-radix digits advanced by 64 per cell, four cells per step) into its own sorted
-// list of the LK >= k best, then k rounds take the best list head of the wave: the
-// largest live flag, then the largest total among those heads, ties to the larger
-// ~flat; the owner drops it.  Eq. 1 weights over the chosen experts that are alive;
-// lane j writes entry j.
-template <bool ALIVE, int LK>
-__device__ __forceinline__ void exact_select_wave(const GateArgs& a, const double* sc, const double* sd,
-                                                  const uint8_t* alv, int t) {
-  const int lane = threadIdx.x & 63;
-  const int d = a.d, M = a.M, k = a.k, N = a.N;
-  const CellKey none{0u, 0ull, 0u};                                 // below every real key
-  CellKey L[LK];
-#pragma unroll
-  for (int j = 0; j < LK; ++j) L[j] = none;
-  int u[DMAX], st[DMAX];
-  {
-    int rl = lane, rs = 64;
-#pragma unroll
-    for (int i = DMAX - 1; i >= 0; --i) {
-      u[i] = 0; st[i] = 0;
-      if (i < d) { u[i] = rl % M; rl /= M; st[i] = rs % M; rs /= M; }
-    }
-  }
-  for (int f0 = lane; f0 < N; f0 += 4 * 64) {
-    CellKey c[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int f = f0 + 64 * q;
-      double tot = 0.0;
-#pragma unroll
-      for (int i = 0; i < DMAX; ++i) if (i < d) tot += sd[i * M + u[i]];   // digits stay in [0, M)
-      const uint32_t live = !ALIVE || alv[min(f, N - 1)] != 0 ? 1u : 0u;
-      c[q] = key_sel(f < N, CellKey{live, ord64(tot + 0.0), ~(uint32_t)f}, none);   // -0 and +0 are one value
-      int carry = 0;                                                  // digits of f + 64
-#pragma unroll
-      for (int i = DMAX - 1; i >= 0; --i) {
-        if (i < d) {
-          u[i] += st[i] + carry;
-          carry = u[i] >= M;
-          u[i] -= carry ? M : 0;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {                                     // sorted insertion, no branches
-      CellKey cur = c[q];
-      bool go = false;
-#pragma unroll
-      for (int j = 0; j < LK; ++j) {
-        const bool gt = go || key_gt(cur, L[j]);
-        const CellKey old = L[j];
-        L[j] = key_sel(gt, cur, old);
-        cur = key_sel(gt, old, cur);
-        go = gt;
-      }
-    }
-  }
-  int chosen[KMAX];
-#pragma unroll
-  for (int r = 0; r < KMAX; ++r) {
-    chosen[r] = 0;
-    if (r < k) {
-      const CellKey h = L[0];
-      uint32_t lmax = 1u;
-      if (ALIVE) lmax = __ballot(h.l != 0u) != 0ull ? 1u : 0u;
-      const uint64_t tt = h.l == lmax ? h.t : 0ull;                  // real totals have keys > 0
-      const uint64_t tmax = wave_max_u64(tt);
-      const uint64_t mask = __ballot(tt == tmax && h.l == lmax);
-      int wl;
-      if (__popcll(mask) == 1) {
-        wl = __ffsll((unsigned long long)mask) - 1;
-      } else {                                                       // equal totals: larger ~flat
-        const uint64_t nn = (mask >> lane) & 1ull ? (uint64_t)h.n : 0ull;
-        const uint64_t nmax = wave_max_u64(nn);
-        wl = __ffsll((unsigned long long)__ballot(nn == nmax && ((mask >> lane) & 1ull))) - 1;
-      }
-      wl = __builtin_amdgcn_readfirstlane(wl);
-      chosen[r] = (int)~(uint32_t)__builtin_amdgcn_readlane((int)h.n, wl);
-      const bool pop = lane == wl;
-#pragma unroll
-      for (int j = 0; j < LK - 1; ++j) L[j] = key_sel(pop, L[j + 1], L[j]);
-      L[LK - 1] = key_sel(pop, none, L[LK - 1]);
-    }
-  }
-  // Eq. 1 weights from the fp64 totals of the chosen experts, over the alive ones
-  // (uniform over the wave; lane j stores entry j)
-  double gx[KMAX];
-  bool lv[KMAX];
-  double m = -1.0e308;
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    gx[j] = 0.0;
-    lv[j] = false;
-    if (j < k) {
-      int rem = chosen[j], v[DMAX];
-#pragma unroll
-      for (int i = DMAX - 1; i >= 0; --i) { v[i] = 0; if (i < d) { v[i] = rem % M; rem /= M; } }
-      double tt = 0.0;
-#pragma unroll
-      for (int i = 0; i < DMAX; ++i) if (i < d) tt += sc[i * M + v[i]];
-      gx[j] = tt;
-      lv[j] = a.alive == nullptr || a.alive[chosen[j]] != 0;
-      if (lv[j]) { any = true; m = tt > m ? tt : m; }
-    }
-  }
-  float ex[KMAX];
-  float sum = 0.f;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    ex[j] = lv[j] ? expf((float)(gx[j] - m)) : 0.f;
-    sum += ex[j];
-  }
-  int my_idx = 0;
-  float my_w = 0.f, my_g = 0.f;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (lane == j) { my_idx = chosen[j]; my_w = any ? ex[j] / sum : 0.f; my_g = (float)gx[j]; }
-  }
-  if (lane < k) {
-    a.idx[(int64_t)t * k + lane] = my_idx;
-    a.w[(int64_t)t * k + lane] = my_w;
-    if (a.g) a.g[(int64_t)t * k + lane] = my_g;
-  }
-  if (a.scores)
-    for (int c = lane; c < a.dM; c += 64) a.scores[(int64_t)t * a.dM + c] = (float)sc[c];
-}
-
-template <typename E, bool ALIVE, int TB, int P>
-__device__ __forceinline__ void exact_pass(const GateArgs& a, const int32_t* queue, int n, int qg,
-                                           double (*s64)[DM_MAX], double (*sd)[DM_MAX], const uint8_t* alv) {
-  const int nt = min(TB, n - qg * TB);
-  int tok[TB];
-#pragma unroll
-  for (int j = 0; j < TB; ++j) tok[j] = queue[GQ_HEAD + qg * TB + min(j, nt - 1)];   // pads repeat a token
-  exact_scores<E, TB, P>(a, tok, s64);
-  __syncthreads();
-  for (int q = threadIdx.x; q < nt * a.dM; q += GX_NT)
-    sd[q / a.dM][q % a.dM] = (double)(float)s64[q / a.dM][q % a.dM];
-  __syncthreads();
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (w < nt) {
-    if (a.k <= 4) exact_select_wave<ALIVE, 4>(a, s64[w], sd[w], alv, tok[w]);
-    else exact_select_wave<ALIVE, KMAX>(a, s64[w], sd[w], alv, tok[w]);
-  }
-  __syncthreads();                                                   // s64, sd reused by the next pass
-}
-
-template <typename E, bool ALIVE, int TB>
-__device__ __forceinline__ void exact_body(const GateArgs& a, const int32_t* queue, double (*s64)[DM_MAX],
-                                           double (*sd)[DM_MAX], uint8_t* alv) {
-  const int n = queue[0];
-  const int ngrp = (n + TB - 1) / TB;
-  if ((int)blockIdx.x >= ngrp) return;
-  if (ALIVE) {
-    for (int f = threadIdx.x; f < a.N; f += GX_NT) alv[f] = a.alive == nullptr || a.alive[f] != 0 ? 1 : 0;
-    __syncthreads();
-  }
-  for (int qg = blockIdx.x; qg < ngrp; qg += gridDim.x)
-    exact_pass<E, ALIVE, TB, TB == 1 ? 3 : 2>(a, queue, n, qg, s64, sd, alv);
-}
-
-// Every token queued (alive-first TopK, or exact scores asked for): GX_TB tokens a pass.
-template <typename E, bool ALIVE>
-__global__ void __launch_bounds__(GX_NT) gate_exact_kernel(GateArgs a, const int32_t* queue) {
-  __shared__ double s64[GX_TB][DM_MAX];
-  __shared__ double sd[GX_TB][DM_MAX];
-  __shared__ uint8_t alv[ALIVE ? NMAX : 1];                          // alive flags (ALIVE ranking)
-  exact_body<E, ALIVE, GX_TB>(a, queue, s64, sd, alv);
-}
-
-// The tokens the certificate rejects (bf16 MFMA scores): one token a pass, two blocks
-// per compute unit.  ALIVE: ranked alive first.
+// The tokens the certificate rejects (bf16 MFMA scores): persistent blocks over the queue,
+// one token a pass (lowest latency), two blocks per compute unit.
 template <bool ALIVE>
 __global__ void __launch_bounds__(GX_NT) __attribute__((amdgpu_waves_per_eu(4)))
 gate_exact_sparse_kernel(GateArgs a, const int32_t* queue) {
-  __shared__ double s64[1][DM_MAX];
-  __shared__ double sd[1][DM_MAX];
-  __shared__ uint8_t alv[ALIVE ? NMAX : 1];
-  exact_body<bf16, ALIVE, 1>(a, queue, s64, sd, ALIVE ? alv : nullptr);
+  __shared__ double s64[DM_MAX];
+  __shared__ SelectScratch scratch;
+  const int n = queue[0];
+  for (int qg = blockIdx.x; qg < n; qg += gridDim.x) {
+    const int t = queue[GQ_HEAD + qg];
+    exact_scores(a, t, s64);
+    __syncthreads();
+    if (threadIdx.x < 64) select_wave<ALIVE>(a, rank_tuples<ALIVE>(a), s64, scratch, t);
+    else if (threadIdx.x < 128 && a.scores)
+      for (int c = threadIdx.x - 64; c < a.dM; c += 64) a.scores[(int64_t)t * a.dM + c] = (float)s64[c];
+    __syncthreads();                                                 // s64 reused by the next pass
+  }
 }
 
-// every token into the queue (the exact path for all of them)
-__global__ void gate_queue_all(int32_t* queue, int T) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) queue[0] = T;
-  if (i < T) queue[GQ_HEAD + i] = i;
+// ---------------------------------------------------------------- exact scores of every token
+//
+// fp64 scores on v_mfma_f64_16x16x4_f64: the products of fp32 (or bf16) values are exact in
+// fp64 and are summed there.  A block scores GF_TOK tokens against all d*M columns: wave wv
+// takes the 16 columns of tile wv % CTN over slice wv / CTN of d_model, the slices' sums meet
+// in LDS in slice order, and then each wave selects for its tokens.  Lane (r = lane % 16,
+// g = lane / 16) loads 16 bytes of row r at vector g of a chunk (4 vectors: 32 bf16 or 16
+// fp32 values), for x and Wg alike, and MFMA j of the chunk contracts element j of the four
+// vectors; GF_P chunks are loaded one step ahead.  Operands go from memory to registers; the
+// tiles' waves share a row of x through the caches, Wg comes from L2 once per 16 tokens.
+// Bound by the f64 matrix rate (78.6 TFLOP/s nominal; one MFMA 64 cycles) when T d M D is
+// large, else by latency: the first loads, then the selection.  Measured against the scalar
+// fp64 kernel it replaces (operands as fp64 in LDS, one lane per token selecting): T = 16384,
+// D = 1024, 128 columns, k = 8 355 -> 124 us (55 us of MFMAs); fp32 T = 2048, D = 512, 8
+// columns 53 -> 11 us.
+constexpr int GF_TOK = 16;        // tokens per block (one MFMA tile)
+constexpr int GF_P = 4;           // chunks per step
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+template <typename E, bool ALIVE>
+__global__ void __launch_bounds__(512) gate_topk_f64(GateArgs a, int CTN) {
+  extern __shared__ __align__(16) unsigned char sm[];
+  constexpr int VEC = 16 / sizeof(E), CHUNK = 4 * VEC;
+  const int dM = a.dM, SLD = dM + 1;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NWV = blockDim.x >> 6, S = NWV / CTN;
+  double* s64 = reinterpret_cast<double*>(sm);                                   // [GF_TOK][SLD]
+  // the waves' partial sums, and in their place afterwards the waves' selection scratch
+  double (*part)[GF_TOK][17] = reinterpret_cast<double (*)[GF_TOK][17]>(s64 + GF_TOK * SLD);
+  SelectScratch& scratch = reinterpret_cast<SelectScratch*>(s64 + GF_TOK * SLD)[wv];
+  const int t0 = blockIdx.x * GF_TOK;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int ct = wv % CTN, sl = wv / CTN;
+  const RankTuples tup = rank_tuples<ALIVE>(a);
+  const E* xr = reinterpret_cast<const E*>(a.x) + (int64_t)min(t0 + r16, a.T - 1) * a.D + g * VEC;
+  const E* wr = reinterpret_cast<const E*>(a.Wg) + (int64_t)min(16 * ct + r16, dM - 1) * a.D + g * VEC;
+  const int nc = a.D / CHUNK;                          // D is a multiple of 64
+  const int c0 = nc * sl / S, c1 = nc * (sl + 1) / S;  // this wave's chunks
+  f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+  uint4 cx[GF_P], cw[GF_P], nx[GF_P], nw[GF_P];
+  auto load = [&](uint4 (&fx)[GF_P], uint4 (&fw)[GF_P], int cc) {
+#pragma unroll
+    for (int p = 0; p < GF_P; ++p)
+      if (cc + p < c1) {
+        fx[p] = *reinterpret_cast<const uint4*>(xr + (int64_t)(cc + p) * CHUNK);
+        fw[p] = *reinterpret_cast<const uint4*>(wr + (int64_t)(cc + p) * CHUNK);
+      }
+  };
+  load(cx, cw, c0);
+  for (int cc = c0; cc < c1; cc += GF_P) {
+    load(nx, nw, cc + GF_P);
+#pragma unroll
+    for (int p = 0; p < GF_P; ++p) {
+      if (cc + p < c1) {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vec_elem<E>(cw[p], j), (double)vec_elem<E>(cx[p], j), acc,
+                                                     0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < GF_P; ++p) { cx[p] = nx[p]; cw[p] = nw[p]; }
+  }
+  // element v of the accumulator: column 4 v + lane / 16 of the tile, token lane % 16
+#pragma unroll
+  for (int v = 0; v < 4; ++v) part[wv][r16][4 * v + g] = acc[v];
+  __syncthreads();
+  const int nt = min(GF_TOK, a.T - t0);
+  {
+    const E* bg = reinterpret_cast<const E*>(a.bg);
+    const int tok = threadIdx.x & 15;
+    for (int c = threadIdx.x >> 4; c < dM; c += NWV * 4) {
+      double v = bg ? (double)ldf(bg + c) : 0.0;
+      for (int q = 0; q < S; ++q) v += part[(c >> 4) + CTN * q][tok][c & 15];
+      s64[tok * SLD + c] = v;
+      if (a.scores && tok < nt) a.scores[(int64_t)(t0 + tok) * dM + c] = (float)v;
+    }
+  }
+  __syncthreads();
+  for (int tt = wv; tt < nt; tt += NWV) select_wave<ALIVE>(a, tup, s64 + tt * SLD, scratch, t0 + tt);
 }
 
+// 16-column tiles of the gate columns (at most 8), and waves per block: every tile over as
+// many d_model slices as 8 waves allow.
+static int gate_f64_tiles(const Shape& s) { return (int)((s.dM + 15) / 16); }
+static int gate_f64_waves(const Shape& s) {
+  const int n = gate_f64_tiles(s);
+  return n * (8 / n);
+}
+static size_t gate_f64_lds_bytes(const Shape& s) {
+  static_assert(GF_TOK % 2 == 0 && alignof(SelectScratch) <= 16, "s64 rows end on 16 bytes");
+  const size_t part = GF_TOK * 17 * sizeof(double);
+  return GF_TOK * (s.dM + 1) * sizeof(double) + gate_f64_waves(s) * std::max(part, sizeof(SelectScratch));
+}
+// bf16 gates with at most 96 columns: exact scores for every token, or the certified route
+// (three launches: queue clearing, scoring, recomputation).  In microseconds the exact route
+// takes about its padded matrix flops at 70 TFLOP/s plus T / 1500 of selection, above the
+// launch; the certified one starts at about 36 and follows the read of x.  Measured, exact
+// against certified: T = 4096, D = 1024, 64 columns 24 / 58; T = 8192, D = 4096, 32 columns
+// 40 / 55; T = 32768, D = 1024, 32 columns 59 / 50; T = 32768, D = 4096, 32 columns
+// 193 / 97.  So exact up to 48 us by that estimate.
+static bool gate_f64_pays(const Shape& s) {
+  const double flops = 2.0 * (double)s.T * (double)s.D * 16.0 * gate_f64_tiles(s);
+  return flops / 70e6 + (double)s.T / 1500.0 <= 48.0;
+}
 static size_t gate_mfma_lds_bytes(int dM, int kw) {
   const size_t ring = (size_t)kw * GM_RING * 4096 * (1 + (dM + 31) / 32);
   const size_t scores = (sizeof(double) + sizeof(float)) * GM_TOK * (dM + 1);
   return ring > scores ? ring : scores;
-}
-
-static size_t gate_lds_bytes(int dM) {
-  return sizeof(double) * (GATE_TB * GATE_KC + GATE_KC * dM + GATE_TB * (dM + 1));
 }
 
 // ---------------------------------------------------------------- backward
@@ -974,60 +1093,49 @@ extern "C" int dmoe_gate_topk(const dmoe_dims* dims, const void* x, const void* 
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool alive_first = (s.flags & DMOE_FLAG_ALIVE_TOPK) != 0;
   const bool mfma = s.dtype == DMOE_BF16 && s.dM <= 3 * 32;
-  if (alive_first && (!mfma || (s.flags & DMOE_FLAG_GATE_EXACT))) {
-    // TopK among the alive experts: exact scores and a ranking of every cell
+  if (mfma || alive_first) {
     if (!ws) return DMOE_EINVAL;
     if (!aligned16(ws)) return DMOE_EUNSUPPORTED;
-    int32_t* queue = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).gq_off);
-    DMOE_LAUNCH(gate_queue_all, dim3((unsigned)((s.T + 255) / 256)), dim3(256), 0, st, queue, (int)s.T);
-    const int xgrid = (int)std::min<int64_t>((s.T + GX_TB - 1) / GX_TB, 1024);
-    if (s.dtype == DMOE_BF16)
-      DMOE_LAUNCH((gate_exact_kernel<bf16, true>), dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
-    else
-      DMOE_LAUNCH((gate_exact_kernel<float, true>), dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
+  }
+  if (!mfma || (s.flags & DMOE_FLAG_GATE_EXACT) || gate_f64_pays(s)) {
+    // exact fp64 scores for every token
+    const dim3 grid((unsigned)((s.T + GF_TOK - 1) / GF_TOK));
+    auto go = [&](auto EK) {
+      using E = typename decltype(EK)::type;
+      auto kern = alive_first ? gate_topk_f64<E, true> : gate_topk_f64<E, false>;
+      DMOE_LAUNCH_NAMED("gate_topk_f64", kern, grid, dim3(64 * gate_f64_waves(s)), gate_f64_lds_bytes(s), st, a,
+                        gate_f64_tiles(s));
+    };
+    if (s.dtype == DMOE_BF16) go(type_tag<bf16>{});
+    else go(type_tag<float>{});
     return launch_status();
   }
-  if (mfma) {
-    if (!ws) return DMOE_EINVAL;
-    if (!aligned16(ws)) return DMOE_EUNSUPPORTED;
-    // error factor of the MFMA scores (see the certificate above gate_topk_mfma)
-    const double u = 1.0 / 8388608.0;
-    const double g32 = 32 * u / (1 - 32 * u) + (s.D / 32 + 8) * 2.220446049250313e-16;
-    const double gD = (double)s.D * u / (1 - (double)s.D * u);
-    int32_t* queue = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).gq_off);
-    GateMfmaArgs ga{a, s.flags, (float)(g32 / (1 - gD) * 1.0001), queue};
-    const int KW = gm_kw(s.D);
-    const size_t lds = gate_mfma_lds_bytes((int)s.dM, KW);
-    const int CB = (int)((s.dM + 31) / 32);
-    auto pick = [&](auto AL) {
-      constexpr bool A = decltype(AL)::value;
-      return KW == 2 ? (CB == 1 ? gate_topk_mfma<1, 2, A> : CB == 2 ? gate_topk_mfma<2, 2, A> : gate_topk_mfma<3, 2, A>)
-                     : (CB == 1 ? gate_topk_mfma<1, 1, A> : CB == 2 ? gate_topk_mfma<2, 1, A> : gate_topk_mfma<3, 1, A>);
-    };
-    auto kern = alive_first ? pick(std::true_type{}) : pick(std::false_type{});
-    if (lds > 65536) {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipGetLastError();
-    }
-    fill_zero(queue, sizeof(int32_t), st);
-    const dim3 grid((unsigned)((s.T + GM_TOK - 1) / GM_TOK));
-    DMOE_LAUNCH_NAMED("gate_topk_mfma", kern, grid, dim3(64 * KW), lds, st, ga);
-    // exact recomputation of the queued tokens: persistent blocks over the queue
-    if (s.flags & DMOE_FLAG_GATE_EXACT) {
-      const int xgrid = (int)std::min<int64_t>((s.T + GX_TB - 1) / GX_TB, 1024);
-      DMOE_LAUNCH((gate_exact_kernel<bf16, false>), dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
-    } else {
-      const int xgrid = (int)std::min<int64_t>(s.T, 1024);
-      if (alive_first) DMOE_LAUNCH(gate_exact_sparse_kernel<true>, dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
-      else DMOE_LAUNCH(gate_exact_sparse_kernel<false>, dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
-    }
-  } else {
-    // fp32, and bf16 with more than 96 gate columns: exact fp64 scores for every token
-    const dim3 grid((unsigned)((s.T + GATE_TB - 1) / GATE_TB));
-    const size_t lds = gate_lds_bytes((int)s.dM);
-    if (s.dtype == DMOE_BF16) DMOE_LAUNCH(gate_topk_kernel<bf16>, grid, dim3(GATE_NT), lds, st, a);
-    else DMOE_LAUNCH(gate_topk_kernel<float>, grid, dim3(GATE_NT), lds, st, a);
+  // error factor of the MFMA scores (see the certificate above gate_topk_mfma)
+  const double u = 1.0 / 8388608.0;
+  const double g32 = 32 * u / (1 - 32 * u) + (s.D / 32 + 8) * 2.220446049250313e-16;
+  const double gD = (double)s.D * u / (1 - (double)s.D * u);
+  int32_t* queue = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).gq_off);
+  GateMfmaArgs ga{a, (float)(g32 / (1 - gD) * 1.0001), queue};
+  const int KW = gm_kw(s.D);
+  const size_t lds = gate_mfma_lds_bytes((int)s.dM, KW);
+  const int CB = (int)((s.dM + 31) / 32);
+  auto pick = [&](auto AL) {
+    constexpr bool A = decltype(AL)::value;
+    return KW == 2 ? (CB == 1 ? gate_topk_mfma<1, 2, A> : CB == 2 ? gate_topk_mfma<2, 2, A> : gate_topk_mfma<3, 2, A>)
+                   : (CB == 1 ? gate_topk_mfma<1, 1, A> : CB == 2 ? gate_topk_mfma<2, 1, A> : gate_topk_mfma<3, 1, A>);
+  };
+  auto kern = alive_first ? pick(std::true_type{}) : pick(std::false_type{});
+  if (lds > 65536) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipGetLastError();
   }
+  fill_zero(queue, sizeof(int32_t), st);
+  const dim3 grid((unsigned)((s.T + GM_TOK - 1) / GM_TOK));
+  DMOE_LAUNCH_NAMED("gate_topk_mfma", kern, grid, dim3(64 * KW), lds, st, ga);
+  // exact recomputation of the queued tokens: persistent blocks over the queue
+  const int xgrid = (int)std::min<int64_t>(s.T, 1024);
+  if (alive_first) DMOE_LAUNCH(gate_exact_sparse_kernel<true>, dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
+  else DMOE_LAUNCH(gate_exact_sparse_kernel<false>, dim3(xgrid), dim3(GX_NT), 0, st, a, queue);
   return launch_status();
 }
 

@@ -16,8 +16,6 @@ namespace dmoe {
 
 constexpr int RT_NT = 256;
 
-template <typename T> struct type_tag { using type = T; };
-
 __global__ void __launch_bounds__(RT_NT)
 dispatch_hist(const int32_t* idx, const uint8_t* alive, int P, int N, int32_t* block_hist) {
   extern __shared__ int hist[];

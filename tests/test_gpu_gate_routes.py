@@ -1,0 +1,109 @@
+"""The two gate routes against the definition and against each other.
+
+Exact route (fp64 matrix products, a wave per token selecting): gate columns at the edges
+of the 16-column tiles and of the 64 lanes, ragged token counts, tied scores and totals
+(small integers: every score is exact), scores of very different magnitude (every cell is
+then ranked), sparse alive sets with TopK among the alive experts.  The reference ranks
+every cell in fp64 by (alive first, total desc, flat index asc).
+
+Certified route (bf16 matrix products plus recomputation of the rejected tokens): sizes
+above the line where it is taken, for each column-block count, wave count and alive mode,
+against the exact route on the same inputs (DMOE_FLAG_GATE_EXACT): the same experts in the
+same order, and weights within the error the score bound allows (a few fp32 ulp)."""
+import pytest
+import torch
+
+from paper_2002_04013_amd import abi
+
+pytestmark = pytest.mark.gpu
+
+
+def gate(dims, x, Wg, bg, alive, T, k, dM):
+    dev = x.device
+    idx = torch.full((T, k), -1, dtype=torch.int32, device=dev)
+    w, g = (torch.full((T, k), -1.0, device=dev) for _ in range(2))
+    sc = torch.empty((T, dM), device=dev)
+    ws = torch.empty(abi.workspace_bytes(dims), dtype=torch.uint8, device=dev)
+    abi.dmoe_gate_topk(dims, x, Wg, bg, alive, idx, w, g, sc, ws)
+    torch.cuda.synchronize()
+    return idx.cpu().long(), w.cpu(), g.cpu(), sc.cpu()
+
+
+def reference(x, Wg, bg, alive, d, M, k, alive_first):
+    S = x.double().cpu() @ Wg.double().cpu().t() + bg.double().cpu()
+    dec = S.float().double().view(-1, d, M)
+    tot = dec[:, 0]
+    for i in range(1, d):
+        tot = (tot[:, :, None] + dec[:, i][:, None, :]).reshape(tot.shape[0], -1)
+    key = tot.clone()
+    order = torch.sort(key, dim=1, descending=True, stable=True)[1]
+    if alive_first:                       # stable: alive ones first, each kind in order
+        dead = (alive.cpu()[order] == 0).to(torch.uint8)
+        order = order.gather(1, torch.sort(dead, dim=1, stable=True)[1])
+    idx = order[:, :k]
+    g = sum(S.gather(1, idx // M ** (d - 1 - i) % M + i * M) for i in range(d))
+    live = alive.cpu()[idx] != 0
+    ex = torch.where(live, torch.exp(g - torch.where(live, g, torch.full_like(g, -1e300)).max(1, keepdim=True)[0]),
+                     torch.zeros_like(g))
+    w = torch.where(live, ex / ex.sum(1, keepdim=True), torch.zeros_like(ex))
+    return S, idx, g, w
+
+
+# dtype, T, D, d, M, k, inputs, p_alive, alive_first
+EXACT = [
+    ("f32", 1, 64, 1, 2, 1, "normal", 1.0, False), ("f32", 31, 64, 1, 16, 8, "ties", 1.0, False),
+    ("f32", 33, 192, 1, 17, 5, "normal", 0.8, False), ("f32", 100, 128, 1, 128, 8, "ties", 0.9, False),
+    ("f32", 64, 64, 2, 4, 8, "ties", 0.5, True), ("f32", 70, 256, 4, 3, 8, "ties", 0.6, True),
+    ("f32", 65, 64, 4, 11, 8, "normal", 0.3, True), ("f32", 40, 64, 3, 5, 4, "span", 0.9, False),
+    ("f32", 40, 64, 3, 5, 4, "span", 0.2, True), ("f32", 96, 1024, 2, 33, 4, "normal", 0.95, False),
+    ("bf16", 130, 512, 2, 64, 8, "ties", 0.9, False), ("bf16", 63, 64, 2, 49, 8, "normal", 0.02, True),
+    ("bf16", 200, 320, 3, 16, 4, "ties", 0.9, True), ("bf16", 77, 64, 2, 8, 3, "span", 0.9, False),
+    ("bf16", 300, 128, 4, 8, 8, "ties", 0.9, False), ("bf16", 50, 2112, 3, 25, 8, "normal", 0.5, True),
+]
+
+
+@pytest.mark.parametrize("dtype,T,D,d,M,k,inputs,p_alive,alive_first", EXACT)
+def test_exact_route_matches_the_definition(dtype, T, D, d, M, k, inputs, p_alive, alive_first):
+    gen = torch.Generator().manual_seed(T * 131 + D + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dM, N = d * M, M ** d
+    if inputs == "normal":
+        x, Wg, bg = (torch.randn(*s, generator=gen) for s in ((T, D), (dM, D), (dM,)))
+        Wg *= D ** -0.5
+    else:                                 # small integers: exact scores, many of them equal
+        x = torch.randint(-1, 2, (T, D), generator=gen).float()
+        Wg = torch.randint(-1, 2, (dM, D), generator=gen).float() * (torch.rand(dM, D, generator=gen) < 8.0 / D)
+        bg = torch.randint(-1, 2, (dM,), generator=gen).float()
+        if inputs == "span":              # one column of each dimension 2^30 times the others
+            Wg[::M] *= 2.0 ** 30
+    x, Wg, bg = x.to(dt).cuda(), Wg.to(dt).cuda(), bg.to(dt).cuda()
+    alive = (torch.rand(N, generator=gen) < p_alive).to(torch.uint8)
+    dims = abi.make_dims(T, D, 64, d, M, k, dtype, "relu", abi.DMOE_FLAG_ALIVE_TOPK if alive_first else 0)
+    idx, w, g, sc = gate(dims, x, Wg, bg, alive.cuda(), T, k, dM)
+    S, ridx, rg, rw = reference(x, Wg, bg, alive, d, M, k, alive_first)
+    assert torch.equal(idx, ridx)
+    assert torch.equal(sc, S.float()) or float((sc - S).abs().max()) <= 2.0 ** -23 * float(S.abs().max())
+    assert float((g - rg).abs().max()) <= 2.0 ** -23 * float(rg.abs().max())
+    assert float((w - rw).abs().max()) <= 2e-6       # fp32 exp and division of exact totals
+
+
+@pytest.mark.parametrize("T,D,d,M,k,p_alive,alive_first", [
+    (33000, 2048, 2, 16, 4, 1.0, False), (40001, 2112, 2, 16, 8, 0.9, False), (40000, 1024, 2, 32, 4, 0.9, True),
+    (16400, 2048, 2, 48, 8, 0.8, True), (30000, 1088, 3, 25, 4, 0.95, False), (50003, 1024, 3, 16, 4, 0.9, True),
+])
+def test_certified_route_matches_the_exact_one(T, D, d, M, k, p_alive, alive_first):
+    g = torch.Generator(device="cuda").manual_seed(T)
+    dM, N = d * M, M ** d
+    x = torch.randn(T, D, generator=g, device="cuda").to(torch.bfloat16)
+    Wg = (torch.randn(dM, D, generator=g, device="cuda") * D ** -0.5).to(torch.bfloat16)
+    bg = torch.randn(dM, generator=g, device="cuda").to(torch.bfloat16)
+    alive = (torch.rand(N, generator=g, device="cuda") < p_alive).to(torch.uint8)
+    fl = abi.DMOE_FLAG_ALIVE_TOPK if alive_first else 0
+    out = [gate(abi.make_dims(T, D, 64, d, M, k, "bf16", "relu", f), x, Wg, bg, alive, T, k, dM)
+           for f in (fl, fl | abi.DMOE_FLAG_GATE_EXACT)]
+    assert torch.equal(out[0][0], out[1][0])
+    # |score error| <= gamma_32 sum |x w| (about 4e-6 * 0.64 sqrt(D)); a weight moves by at most 2 w d times that
+    lim = 4.1e-6 * float((x[:64].float().abs() @ Wg.float().abs().t()).max()) * 1.5 + 2.0 ** -22 * float(out[1][3].abs().max())
+    assert float((out[0][3] - out[1][3]).abs().max()) <= lim
+    assert float((out[0][2] - out[1][2]).abs().max()) <= d * lim
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 2 * d * lim + 1e-6
