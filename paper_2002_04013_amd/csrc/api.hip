@@ -41,25 +41,21 @@ Workspace workspace_layout(const Shape& s) {
   w.hist_off = off;
   w.hist_bytes = align256((size_t)(w.disp_blocks > 0 ? w.disp_blocks : 1) * s.N * sizeof(int32_t));
   off += w.hist_bytes;
-  // token splits of the dWg GEMM: >= 512 tokens each, at most 32 splits
-  int64_t split = (s.T + 31) / 32;
-  split = split < 512 ? 512 : split;
-  split = (split + 31) / 32 * 32;
+  // token splits of the gate's dWg product: enough for about 512 blocks of 128 columns, but
+  // at least 256 tokens, and 4 d*M so that the partial sums stay below the read of x
+  const int64_t col_blocks = (s.D + 127) / 128;
+  int64_t split = (s.T * col_blocks + 511) / 512;
+  split = std::max<int64_t>(split, std::max<int64_t>(256, 4 * s.dM));
+  split = (split + 63) / 64 * 64;
   w.gsplit_tokens = split;
   w.gsplit = s.T > 0 ? (s.T + split - 1) / split : 0;
-  // tile bookkeeping: GEMM tile prefix [N+1] (+ split offsets/prefix of the gate GEMM)
-  const int64_t tiles_ints = 2 * (s.N + 1) + 2 * (w.gsplit + 1);
+  // tile bookkeeping: GEMM tile prefix [N+1], and of the experts with rows
+  const int64_t tiles_ints = 2 * (s.N + 1);
   w.tiles_off = off;
   w.tiles_bytes = align256((size_t)tiles_ints * sizeof(int32_t));
   off += w.tiles_bytes;
-  // ds rows: bf16 keeps hi and lo parts; padded to the 16-byte vector width
-  if (s.dtype == DMOE_BF16) w.ds_ld = (2 * s.dM + 7) / 8 * 8;
-  else w.ds_ld = (s.dM + 3) / 4 * 4;
-  w.ds_off = off;
-  w.ds_bytes = align256((size_t)s.T * w.ds_ld * s.esz);
-  off += w.ds_bytes;
   w.part_off = off;
-  w.part_bytes = align256((size_t)w.gsplit * w.ds_ld * s.D * sizeof(float));
+  w.part_bytes = align256((size_t)w.gsplit * s.dM * s.D * sizeof(float));
   off += w.part_bytes;
   w.gq_off = off;
   w.gq_bytes = align256((size_t)(GQ_HEAD + s.T) * sizeof(int32_t));

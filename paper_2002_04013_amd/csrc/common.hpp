@@ -174,13 +174,11 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 struct Workspace {
   size_t hist_off, hist_bytes;     // dispatch: per-block expert histograms
   size_t tiles_off, tiles_bytes;   // grouped GEMM: tile prefix [N+1] + per-expert m-tiles
-  size_t ds_off, ds_bytes;         // gate backward: dense ds (bf16 hi/lo or fp32)
   size_t part_off, part_bytes;     // gate backward: dWg partial sums per token split
   size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute
   size_t total;
   int64_t disp_blocks;             // dispatch blocks (pairs per block = DISP_CHUNK)
   int64_t gsplit, gsplit_tokens;   // gate backward token splits
-  int64_t ds_ld;                   // ds row stride (elements)
 };
 
 constexpr int DISP_CHUNK = 1024;   // pairs per dispatch block

@@ -4,8 +4,8 @@
 #include <type_traits>
 
 #include "common.hpp"
-#include "gemm.hpp"
 #include "gemm2.hpp"
+#include "gemm_f32.hpp"
 
 namespace dmoe {
 
@@ -956,116 +956,311 @@ static size_t gate_mfma_lds_bytes(int dM, int kw) {
 }
 
 // ---------------------------------------------------------------- backward
+//
+// dg[t,j] = w (dw - sum_l w_l dw_l) over alive chosen experts; ds row t gets dg at column
+// i*M + u_i for every dimension i; dWg = ds^T x, dbg = sum_t ds.  Two launches: one kernel
+// whose blocks either write dg and the bias gradient's partial sums (GD_TOK tokens each) or
+// multiply a token split by GB_BN columns of x into a partial dWg, and a reduction of the
+// partials in split order.  ds is never stored: a block expands the k terms per token and
+// dimension of the tokens of its next stage in LDS, column-major like an MFMA operand.  A
+// thread owns one token's entries of one dimension: it clears those it wrote two stages ago
+// and writes the new ones, so the expansion needs no barrier of its own.  bf16: ds as hi and
+// lo bf16 parts, both multiplied into the same fp32 accumulator (about 16 mantissa bits).
+// Bound by latency: a stage's expansion, barrier and loads follow one another, two blocks to
+// a compute unit (T = 32768, D = 4096, 32 columns: 92 us for 268 MB, 2.9 TB/s).  Five
+// launches before (dg and dense ds; split offsets; a register-staged GEMM over ds in memory;
+// two reductions), measured before -> now per call: that shape 170 -> 97 us; T = 16384,
+// D = 1024, 128 columns, k = 8 130 -> 48 us; T = 4096, D = 1024, 64 columns 67 -> 18 us;
+// fp32 T = 2048, D = 512, 8 columns 79 -> 19 us.
 
-constexpr int GD_NT = 128;         // gate backward: tokens per block
+constexpr int GD_TOK = 128;        // tokens per dg block
+constexpr int GB_NT = 256;
+constexpr int GB_BN = 128;         // x columns per block, 32 per wave
+constexpr int GB_ST = 3;           // x stages in LDS
+constexpr int GB_XB = 16384;       // bytes of an x stage: 64 bf16 or 32 fp32 rows
 
-// dg[t,j] = w (dw - sum_l w_l dw_l) over alive chosen experts; ds row t gets dg at
-// column i*M + u_i for every dimension i.  bf16: ds stores hi and lo bf16 parts
-// (columns [0, dM) and [dM, 2dM)) so the MFMA product keeps ~16 mantissa bits.
+struct GateBwdArgs {
+  const void* x; const int32_t* idx; const float* w; const float* dw; const uint8_t* alive;
+  float* dg; float* dbg_part; float* part;
+  int T, D, d, M, k, dM;
+  int gblk, nb, split;             // dg blocks; column blocks; tokens per split
+};
 
-template <typename E>
-__global__ void __launch_bounds__(GD_NT)
-gate_dg_kernel(const int32_t* idx, const float* w, const float* dw, const uint8_t* alive, float* dg, E* ds,
-               int64_t ds_ld, int T, int d, int M, int k, int dM, float* dbg_part) {
-  // One thread per token builds its ds row (fp32, in LDS: rows of dM + 1 words); the
-  // block then writes its rows (consecutive tokens, one contiguous range) in 16-byte
-  // chunks, and adds each column over its rows in row order for the bias gradient.
-  extern __shared__ float rowbuf[];
-  constexpr int VEC = 16 / sizeof(E);
-  const int tl = threadIdx.x;
-  const int t0 = blockIdx.x * GD_NT, t = t0 + tl;
-  const int nt = min(GD_NT, T - t0);
-  const int SR = dM + 1;
-  float* row = rowbuf + tl * SR;
-  for (int c = 0; c < dM; ++c) row[c] = 0.f;
-  if (t < T) {
-    float wv[KMAX], dv[KMAX];
-    int id[KMAX];
+// The k terms of token t: dg and the grid indices (8 bits per dimension); zeros past `end`.
+struct GateTerms {
+  int id[KMAX];
+  float wv[KMAX], dv[KMAX];
+  uint8_t live[KMAX];
+  // the slots' loads; the alive flags, which need the ids, are loaded by a second call
+  __device__ __forceinline__ void load(const GateBwdArgs& p, int t, int end) {
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+      id[j] = 0; wv[j] = 0.f; dv[j] = 0.f;
+      if (j < p.k && t < end) {
+        id[j] = p.idx[(int64_t)t * p.k + j];
+        wv[j] = p.w[(int64_t)t * p.k + j];
+        dv[j] = p.dw[(int64_t)t * p.k + j];
+      }
+    }
+  }
+  __device__ __forceinline__ void load_alive(const GateBwdArgs& p) {
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+      live[j] = 1;
+      if (j < p.k && p.alive != nullptr) live[j] = p.alive[id[j]];
+    }
+  }
+  // f(j, dg, indices) for each slot
+  template <typename F> __device__ __forceinline__ void each(const GateBwdArgs& p, F&& f) {
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      wv[j] = 0.f; dv[j] = 0.f; id[j] = 0;
-      if (j < k) {
-        id[j] = idx[(int64_t)t * k + j];
-        const bool live = alive == nullptr || alive[id[j]] != 0;
-        wv[j] = live ? w[(int64_t)t * k + j] : 0.f;
-        dv[j] = dw[(int64_t)t * k + j];
+    for (int j = 0; j < KMAX; ++j)
+      if (j < p.k) {
+        if (live[j] == 0) wv[j] = 0.f;
         s = fmaf(wv[j], dv[j], s);
       }
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+      if (j < p.k) {
+        int rem = id[j];
+        uint32_t dig = 0;
+#pragma unroll
+        for (int i = DMAX - 1; i >= 0; --i)
+          if (i < p.d) { dig |= (uint32_t)(rem % p.M) << (8 * i); rem /= p.M; }
+        f(j, wv[j] * (dv[j] - s), dig);
+      }
+  }
+};
+
+// dg of GD_TOK tokens, and their sums per gate column (rows in order, in two halves)
+__device__ __forceinline__ void gate_dg_block(const GateBwdArgs& p, int blk, float* rows) {
+  const int SR = p.dM + 1;
+  const int t0 = blk * GD_TOK, nt = min(GD_TOK, p.T - t0);
+  for (int q = threadIdx.x; q < GD_TOK * SR; q += GB_NT) rows[q] = 0.f;
+  __syncthreads();
+  if ((int)threadIdx.x < nt) {
+    const int t = t0 + threadIdx.x;
+    GateTerms v;
+    v.load(p, t, p.T);
+    v.load_alive(p);
+    float* row = rows + threadIdx.x * SR;
+    v.each(p, [&](int j, float g, uint32_t dig) {
+      p.dg[(int64_t)t * p.k + j] = g;
+      for (int i = 0; i < p.d; ++i) row[i * p.M + ((dig >> (8 * i)) & 0xff)] += g;
+    });
+  }
+  if (!p.dbg_part) return;
+  __syncthreads();
+  const int c = threadIdx.x >> 1;                        // dM <= 128 = GB_NT / 2
+  float s = 0.f;
+  if (c < p.dM) {
+    const float* col = rows + (threadIdx.x & 1) * (GD_TOK / 2) * SR + c;
+#pragma unroll 8
+    for (int r = 0; r < GD_TOK / 2; ++r) s += col[r * SR];
+  }
+  s += __shfl_xor(s, 1, 64);
+  if (c < p.dM && (threadIdx.x & 1) == 0) p.dbg_part[(int64_t)blk * p.dM + c] = s;
+}
+
+template <typename E> struct GbTile;     // the x stage: [tokens][GB_BN columns]
+template <> struct GbTile<bf16> { using X = NcTile<GB_BN, GB_NT / 64, 64>; static constexpr int TOK = 64, PARTS = 2; };
+template <> struct GbTile<float> { using X = NcTileF32<GB_BN, GB_NT / 64>; static constexpr int TOK = 32, PARTS = 1; };
+
+template <typename E, int CB>      // CB: 32-column blocks of the d*M gate columns
+__global__ void __launch_bounds__(GB_NT) gate_bwd_kernel(GateBwdArgs p) {
+  using X = typename GbTile<E>::X;
+  using KC = KcTile<32, 4, 1, 64>;                       // fragment layout of a 128-byte ds row
+  constexpr int TOK = GbTile<E>::TOK, PARTS = GbTile<E>::PARTS;
+  constexpr int SPC = GB_NT / TOK;                       // stages per GB_NT tokens
+  constexpr int DSB = 32 * CB * 128;                     // bytes of one ds part: [32 CB][TOK]
+  static_assert(X::BYTES == GB_XB && X::INSTR % (GB_NT / 64) == 0, "x stage");
+  extern __shared__ __align__(1024) char smem[];
+  if ((int)blockIdx.x < p.gblk) {
+    gate_dg_block(p, blockIdx.x, reinterpret_cast<float*>(smem));
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.x - p.gblk;
+  const int n0 = (b % p.nb) * GB_BN, sp = b / p.nb;
+  const int tb = sp * p.split, te = min(p.T, tb + p.split);
+  const int nk = (te - tb + TOK - 1) / TOK;
+  const E* x = reinterpret_cast<const E*>(p.x) + (int64_t)tb * p.D + n0;
+  char* dsb = smem + GB_ST * GB_XB;                      // 2 x PARTS x DSB
+  uint2* terms = reinterpret_cast<uint2*>(dsb + 2 * PARTS * DSB);   // [k][GB_NT]: dg, indices
+  for (int q = tid; q < 2 * PARTS * DSB / 16; q += GB_NT) reinterpret_cast<uint4*>(dsb)[q] = make_uint4(0, 0, 0, 0);
+
+  auto issue = [&](int kt) {
+    X::load(x + (int64_t)kt * TOK * p.D, p.D, p.D - n0, te - tb - kt * TOK, smem + (kt % GB_ST) * GB_XB, wave, lane);
+  };
+  GateTerms v;
+  auto put_terms = [&]() {
+    v.each(p, [&](int j, float g, uint32_t dig) { terms[j * GB_NT + tid] = make_uint2(__float_as_uint(g), dig); });
+  };
+  // this thread's token and dimension of a stage, and the column of each slot it wrote last
+  // into either ds buffer
+  const int bt = tid % TOK, bi = tid / TOK;
+  const bool builder = bi < p.d;
+  uint8_t old[2][KMAX];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) old[q][j] = 0;
+  auto ds_at = [&](char* base, int c) -> E* {            // element (column c, token bt)
+    constexpr int PER = 16 / (int)sizeof(E);
+    return reinterpret_cast<E*>(base + c * 128 + (((bt / PER) ^ ((c >> 1) & 7)) << 4)) + bt % PER;
+  };
+  auto build = [&](int kt, auto BUFc) {
+    constexpr int BUF = decltype(BUFc)::value;
+    if (!builder) return;
+    char* hi = dsb + BUF * PARTS * DSB;
+    const uint2* tt = terms + (kt % SPC) * TOK + bt;
+    float g[KMAX];
+    int c[KMAX];
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+      g[j] = 0.f;
+      c[j] = -1;
+      if (j < p.k) {
+        const uint2 q = tt[j * GB_NT];
+        g[j] = __uint_as_float(q.x);
+        c[j] = bi * p.M + (int)((q.y >> (8 * bi)) & 0xff);
+        *ds_at(hi, old[BUF][j]) = 0;
+        if constexpr (PARTS == 2) *ds_at(hi + DSB, old[BUF][j]) = 0;
+      }
     }
 #pragma unroll
     for (int j = 0; j < KMAX; ++j) {
-      if (j < k) {
-        const float gj = wv[j] * (dv[j] - s);
-        dg[(int64_t)t * k + j] = gj;
-        int rem = id[j];
-        for (int i = d - 1; i >= 0; --i) { row[i * M + rem % M] += gj; rem /= M; }
-      }
-    }
-  }
-  __syncthreads();
-  // bf16: hi parts in columns [0, dM), lo parts in [dM, 2 dM), zeros up to ds_ld
-  const int cpr = (int)(ds_ld / VEC);
-  for (int q = tl; q < nt * cpr; q += GD_NT) {
-    const int r = q / cpr, cb = q % cpr;
-    const float* src = rowbuf + r * SR;
-    alignas(16) E v[VEC];
+      if (j >= p.k) continue;
+      float s = 0.f;                                     // every slot of the column, in slot order
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int c = cb * VEC + e;
-      if constexpr (sizeof(E) == 2) {
-        if (c < dM) v[e] = f2bf(src[c]);
-        else if (c < 2 * dM) { const float a = src[c - dM]; v[e] = f2bf(a - bf2f(f2bf(a))); }
-        else v[e] = 0;
+      for (int l = 0; l < KMAX; ++l) s += c[l] == c[j] ? g[l] : 0.f;
+      if constexpr (PARTS == 2) {
+        const bf16 h = f2bf(s);
+        *ds_at(hi, c[j]) = h;
+        *ds_at(hi + DSB, c[j]) = f2bf(s - bf2f(h));
       } else {
-        v[e] = c < dM ? src[c] : 0.f;
+        *ds_at(hi, c[j]) = s;
+      }
+      old[BUF][j] = (uint8_t)c[j];
+    }
+  };
+  uint32_t kc_off[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) kc_off[q] = KC::lane_off(2 * q, lane);
+  const uint32_t x_off = X::lane_off(wave, lane);
+  f32x16_t acc[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+
+  v.load(p, tb + tid, te);
+  v.load_alive(p);
+  put_terms();
+#pragma unroll
+  for (int st = 0; st < GB_ST - 1; ++st)
+    if (st < nk) issue(st);
+  block_sync_lds();
+  // the old columns start as column 0 of dimension 0, which only its own builder may write:
+  // clears before the first build of a buffer must not race with it
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) old[q][j] = (uint8_t)(builder ? bi * p.M : 0);
+  build(0, std::integral_constant<int, 0>{});
+  if (SPC < nk) v.load(p, tb + GB_NT + tid, te);
+
+  auto stage = [&](int kt, auto BUFc) {
+    constexpr int BUF = decltype(BUFc)::value;           // kt % 2
+    if (kt + GB_ST - 2 < nk) wait_vmcnt<(GB_ST - 2) * X::PER_WAVE>();
+    else wait_vmcnt<0>();
+    block_sync_lds();              // x and ds of stage kt are whole; every wave is done with stage kt - 1
+    // The terms of the next GB_NT tokens: slots loaded SPC stages ahead, their alive flags two
+    // stages later, put in LDS when the tokens' first stage is to be built.  These come before
+    // the stage's own loads: a wait for a register load also waits for every load before it.
+    if (kt % SPC == 1 && kt - 1 + SPC < nk) v.load_alive(p);
+    if ((kt + 1) % SPC == 0 && kt + 1 < nk) {
+      put_terms();                 // every build of the previous tokens is done
+      block_sync_lds();
+      if (kt + 1 + SPC < nk) v.load(p, tb + (kt + 1 + SPC) * TOK + tid, te);
+    }
+    if (kt + GB_ST - 1 < nk) issue(kt + GB_ST - 1);
+    if (kt + 1 < nk) build(kt + 1, std::integral_constant<int, 1 - BUF>{});
+    const char* xs = smem + (kt % GB_ST) * GB_XB;
+    const char* ds = dsb + BUF * PARTS * DSB;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if constexpr (sizeof(E) == 2) {
+        const bf16x8_t fx = X::frag_at(xs, q * 16, x_off);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx, KC::frag_at(ds, cb * 32, kc_off[q]), acc[cb], 0, 0, 0);
+          acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx, KC::frag_at(ds + DSB, cb * 32, kc_off[q]), acc[cb], 0, 0, 0);
+        }
+      } else {
+        const f32x4_t fx = frag_f32<true, X>(xs, q, 0, x_off);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          const f32x4_t fd = frag_f32<false, KC>(ds, q, cb * 32, kc_off[q]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(fx[r], fd[r], acc[cb], 0, 0, 0);
+        }
       }
     }
-    *reinterpret_cast<uint4*>(ds + (int64_t)(t0 + r) * ds_ld + cb * VEC) = *reinterpret_cast<const uint4*>(v);
+  };
+  for (int kt = 0; kt < nk; kt += 2) {
+    stage(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < nk) stage(kt + 1, std::integral_constant<int, 1>{});
   }
-  if (dbg_part) {
-    for (int c = tl; c < dM; c += GD_NT) {
-      float a = 0.f;
-      for (int r = 0; r < nt; ++r) a += rowbuf[r * SR + c];
-      dbg_part[(int64_t)blockIdx.x * dM + c] = a;
+  // lane (column l % 32 of each block, half l / 32) holds x columns 8 g + 4 (l / 32) .. + 3
+  const int l32 = lane & 31, lhi = lane >> 5;
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    const int c = cb * 32 + l32;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = n0 + wave * 32 + 8 * g + 4 * lhi;
+      if (c < p.dM && n < p.D)
+        *reinterpret_cast<float4*>(p.part + ((int64_t)sp * p.dM + c) * p.D + n) =
+            make_float4(acc[cb][4 * g], acc[cb][4 * g + 1], acc[cb][4 * g + 2], acc[cb][4 * g + 3]);
     }
   }
 }
 
-// offsets of the token splits and the GROUP_K tile prefix for the dWg GEMM
-__global__ void gate_split_prep(int32_t* offs, int32_t* tprefix, int nsplit, int split, int T) {
-  for (int s = threadIdx.x; s <= nsplit; s += blockDim.x) {
-    const int o = s * split;
-    offs[s] = o < T ? o : T;
-    tprefix[s] = s;
-  }
+static size_t gate_bwd_lds_bytes(const Shape& s) {
+  const int parts = s.dtype == DMOE_BF16 ? 2 : 1;
+  const size_t ds = (size_t)2 * parts * ((s.dM + 31) / 32) * 32 * 128;
+  const size_t mm = (size_t)GB_ST * GB_XB + ds + (size_t)s.k * GB_NT * sizeof(uint2);
+  const size_t rows = (size_t)GD_TOK * (s.dM + 1) * sizeof(float);
+  return mm > rows ? mm : rows;
 }
 
-// dWg[c][n] = sum over splits of the partial products (hi + lo parts for bf16)
+// dWg = sum of the splits' partials in split order (4 values a thread); the blocks past
+// nred: dbg[c] = sum over the dg blocks of their partial column sums, thread i adding a
+// contiguous run of blocks, then a tree over the threads.
 template <typename E>
-__global__ void gate_reduce_kernel(const float* part, int nsplit, int64_t rows, int dM, int D,
-                                   E* dWg) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)dM * D) return;
-  const int c = (int)(q / D), n = (int)(q % D);
-  float s = 0.f;
-  for (int sp = 0; sp < nsplit; ++sp) {
-    const float* P = part + (int64_t)sp * rows * D;
-    s += P[(int64_t)c * D + n];
-    if constexpr (sizeof(E) == 2) s += P[(int64_t)(dM + c) * D + n];
+__global__ void __launch_bounds__(256)
+gate_reduce_kernel(const float* part, int nsplit, int64_t n, E* dWg, int nred, const float* dbg_part, int nblk, int dM,
+                   E* dbg) {
+  if ((int)blockIdx.x < nred) {
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (q >= n) return;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int sp = 0; sp < nsplit; ++sp) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)sp * n + q);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    // dWg needs no alignment beyond its elements'
+    dWg[q] = cvt<E>(s.x); dWg[q + 1] = cvt<E>(s.y); dWg[q + 2] = cvt<E>(s.z); dWg[q + 3] = cvt<E>(s.w);
+    return;
   }
-  dWg[q] = cvt<E>(s);
-}
-
-// dbg[c] = sum over the token blocks of their partial column sums, in block order:
-// thread i adds a contiguous run of blocks, then a tree over the threads.
-template <typename E>
-__global__ void __launch_bounds__(256) gate_dbg_kernel(const float* part, int nblk, int dM, E* dbg) {
-  const int c = blockIdx.x;
+  const int c = blockIdx.x - nred;
   const int per = (nblk + 255) / 256;
   const int b0 = threadIdx.x * per, b1 = min(nblk, b0 + per);
   float s = 0.f;
-  for (int b = b0; b < b1; ++b) s += part[(int64_t)b * dM + c];
+  for (int b = b0; b < b1; ++b) s += dbg_part[(int64_t)b * dM + c];
   __shared__ float red[256];
   red[threadIdx.x] = s;
   __syncthreads();
@@ -1145,46 +1340,33 @@ static int gate_bwd_impl(const Shape& s, const void* x, const int32_t* idx, cons
                          void* ws, hipStream_t st) {
   const Workspace L = workspace_layout(s);
   unsigned char* base = reinterpret_cast<unsigned char*>(ws);
-  E* ds = reinterpret_cast<E*>(base + L.ds_off);
-  float* part = reinterpret_cast<float*>(base + L.part_off);
-  int32_t* offs = reinterpret_cast<int32_t*>(base + L.tiles_off);
-  int32_t* tpre = offs + (L.gsplit + 1);
-  const int T = (int)s.T, D = (int)s.D, dM = (int)s.dM;
+  GateBwdArgs p{x, idx, w, dw, alive, dg, nullptr, reinterpret_cast<float*>(base + L.part_off),
+                (int)s.T, (int)s.D, s.d, s.M, s.k, (int)s.dM,
+                (int)((s.T + GD_TOK - 1) / GD_TOK), (int)((s.D + GB_BN - 1) / GB_BN), (int)L.gsplit_tokens};
   // the bias gradient's per-block column sums use the forward pass's queue region
   // (calls on one stream do not overlap): ceil(T / 128) x dM floats <= 4 T bytes
-  const int gblk = (T + GD_NT - 1) / GD_NT;
-  float* dbg_part = dbg ? reinterpret_cast<float*>(base + L.gq_off) : nullptr;
-  const size_t dg_lds = (size_t)GD_NT * (dM + 1) * sizeof(float);
-  if (dg_lds > 65536) {
-    (void)hipFuncSetAttribute((const void*)gate_dg_kernel<E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dg_lds);
-    (void)hipGetLastError();
+  if (dbg) p.dbg_part = reinterpret_cast<float*>(base + L.gq_off);
+  const size_t lds = gate_bwd_lds_bytes(s);
+  auto go = [&](auto CBc) {
+    auto kern = gate_bwd_kernel<E, decltype(CBc)::value>;
+    if (lds > 65536) {
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      (void)hipGetLastError();
+    }
+    DMOE_LAUNCH_NAMED("gate_bwd_kernel (dg, dWg per token split)", kern,
+                      dim3((unsigned)(p.gblk + p.nb * (int)L.gsplit)), dim3(GB_NT), lds, st, p);
+  };
+  switch ((s.dM + 31) / 32) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    default: go(std::integral_constant<int, 4>{}); break;
   }
-  DMOE_LAUNCH(gate_dg_kernel<E>, dim3(gblk), dim3(GD_NT), dg_lds, st, idx, w, dw, alive, dg, ds, L.ds_ld, T,
-                     s.d, s.M, s.k, dM, dbg_part);
-  // dWg partials: one GROUP_K GEMM group per token split, C[split] = ds_split^T x_split
-  constexpr int BM = 64, BN = 128, BK = 32, WM = 2, WN = 2;
-  const int rows = (int)L.ds_ld;                     // GEMM M (ds columns incl. lo part/padding)
-  const int mt = (rows + BM - 1) / BM, nt = (D + BN - 1) / BN;
-  DMOE_LAUNCH(gate_split_prep, dim3(1), dim3(256), 0, st, offs, tpre, (int)L.gsplit,
-                     (int)L.gsplit_tokens, T);
-  GemmArgs<E> p{};
-  p.A = ds; p.lda = L.ds_ld;
-  p.B = reinterpret_cast<const E*>(x); p.ldb = D;
-  p.C = part; p.ldc = D; p.c_gstride = (int64_t)rows * D;
-  p.offsets = offs; p.tprefix = tpre; p.tscale = mt * nt; p.groups = (int)L.gsplit;
-  p.M = rows; p.N = D; p.K = 0; p.act = s.act;
-  const int tiles = (int)L.gsplit * mt * nt;
-  auto kern = grouped_gemm<E, GROUP_K, false, EPI_F32, BM, BN, BK, WM, WN>;
-  const size_t lds = gemm_lds_bytes<E, BM, BN, BK, WM, WN>();
-  int grid = tiles < 2048 ? tiles : 2048;
-  p.chunked = grid >= 8;
-  DMOE_LAUNCH_NAMED("grouped_gemm<GROUP_K,EPI_F32> (gate dWg per token split)", kern, dim3(grid),
-                    dim3(64 * WM * WN), lds, st, p);
-  const int64_t outs = (int64_t)dM * D;
-  DMOE_LAUNCH(gate_reduce_kernel<E>, dim3((unsigned)((outs + 255) / 256)), dim3(256), 0, st,
-                     part, (int)L.gsplit, (int64_t)rows, dM, D, reinterpret_cast<E*>(dWg));
-  if (dbg)
-    DMOE_LAUNCH(gate_dbg_kernel<E>, dim3(dM), dim3(256), 0, st, dbg_part, gblk, dM, reinterpret_cast<E*>(dbg));
+  const int64_t n = s.dM * s.D;                          // a multiple of 64
+  const int nred = (int)((n / 4 + 255) / 256);
+  DMOE_LAUNCH_NAMED("gate_reduce_kernel", gate_reduce_kernel<E>, dim3((unsigned)(nred + (dbg ? s.dM : 0))), dim3(256), 0,
+                    st, p.part, (int)L.gsplit, n, reinterpret_cast<E*>(dWg), nred, p.dbg_part, p.gblk, (int)s.dM,
+                    reinterpret_cast<E*>(dbg));
   return launch_status();
 }
 

@@ -3,7 +3,7 @@
 // layouts, and MFMA operand fragments read with ds_read_b128 (K-contiguous
 // tiles) or with the transposing ds_read_b64_tr_b16 (N-contiguous tiles).
 //
-// Same problem statement and tile schedule as grouped_gemm in gemm.hpp:
+// Problem statement of gemm.hpp:
 //   C[m][n] = sum_k A[m][k] B[n][k] per expert; GROUP_M groups rows (tokens),
 //   GROUP_K groups the contraction (tokens) for weight gradients.
 // Operand storage:
@@ -289,20 +289,20 @@ grouped_gemm2(GemmArgs<bf16> p) {
   constexpr int LPS = TA::PER_WAVE + TB::PER_WAVE;   // load instructions per stage per wave
   // (with XB, waves 0..3 load one more: the extra block's 32 rows, 8 rows each)
   // store instructions of a full tile's epilogue, per wave
-  constexpr int SFULL = EPI == EPI_F32 ? TM * TN * 4 : TM * TN * 2 * (EPI == EPI_BIAS_ACT ? 2 : 1);
+  constexpr int SFULL = TM * TN * 2 * (EPI == EPI_BIAS_ACT ? 2 : 1);
   static_assert(TM >= 1 && TM <= 5 && TN >= 1, "tile");
   // GROUP_M tiles taller than 256 rows split each expert's rows evenly (in 32-row
   // blocks) over its m-tiles, so an expert slightly above a multiple of the tile height
   // gets no nearly empty last tile
   constexpr bool BAL = GM == GROUP_M && (BM > 256 || XB);
   static_assert(!XB || (GM == GROUP_M && !A_T && BM == 256 && BN == 256 && WM == 4 && WN == 2 && STAGES == 2 &&
-                        STO == STORE_DIRECT && EPI != EPI_F32 && EPI != EPI_SGD),
+                        STO == STORE_DIRECT && EPI != EPI_SGD),
                 "extra block: GROUP_M 256 x 256 tiles of 8 waves, 2 stages, direct stores");
   static_assert(KK % 2 == 0, "fragment slots alternate over an even number of steps");
   static_assert(TA::INSTR % NW == 0 && TB::INSTR % NW == 0, "equal load counts per wave");
   static_assert(GM == GROUP_M || (A_T && B_T), "GROUP_K takes both operands stored per token");
   static_assert(STAGES * LPS <= 63, "vmcnt range");
-  static_assert(STO == STORE_DIRECT || (EPI != EPI_F32 && WTN % 64 == 0), "staged stores: bf16 output, 64-col pieces");
+  static_assert(STO == STORE_DIRECT || WTN % 64 == 0, "staged stores: 64-column pieces");
 
   extern __shared__ __align__(1024) char smem[];
   const int tid = threadIdx.x;
@@ -699,7 +699,7 @@ grouped_gemm2(GemmArgs<bf16> p) {
         if (st < nxt.nk) issue(nxt, st);
     }
 
-    // epilogue (same accumulator layout as grouped_gemm); stores issued by this wave
+    // epilogue; stores issued by this wave
     // number SFULL exactly when every row and column of its part of the tile is valid
     constexpr int SXB = 2 * (EPI == EPI_BIAS_ACT ? 2 : 1);   // stores of the extra block's piece
     const bool full = nl == TM && mvalid >= (xl ? BMT : BM) && nvalid >= BN;
@@ -713,8 +713,6 @@ grouped_gemm2(GemmArgs<bf16> p) {
       uint32_t pk[4][2], pa[4][2];      // bf16 pairs of column group g (output, activation)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int nl_ = cb + 8 * g + 4 * lhi;
-        const int n = n0 + nl_;
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = a[4 * g + r];
@@ -737,47 +735,40 @@ grouped_gemm2(GemmArgs<bf16> p) {
           v[2] = __uint_as_float(wv.y << 16) - p.lr * v[2];
           v[3] = __uint_as_float(wv.y & 0xffff0000u) - p.lr * v[3];
         }
-        if constexpr (EPI == EPI_F32) {
-          if (mok && nl_ < nvalid)
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + crow + n) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-          pk[g][0] = f2bf2(v[0], v[1]);
-          pk[g][1] = f2bf2(v[2], v[3]);
-          if constexpr (EPI == EPI_BIAS_ACT) {
-            float ac[4];
+        pk[g][0] = f2bf2(v[0], v[1]);
+        pk[g][1] = f2bf2(v[2], v[3]);
+        if constexpr (EPI == EPI_BIAS_ACT) {
+          float ac[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ac[r] = act_fwd_fast(v[r], p.act);
-            pa[g][0] = f2bf2(ac[0], ac[1]);
-            pa[g][1] = f2bf2(ac[2], ac[3]);
-          }
+          for (int r = 0; r < 4; ++r) ac[r] = act_fwd_fast(v[r], p.act);
+          pa[g][0] = f2bf2(ac[0], ac[1]);
+          pa[g][1] = f2bf2(ac[2], ac[3]);
         }
       }
-      if constexpr (EPI != EPI_F32) {
-        // Lanes l and l + 32 hold the two 4-column halves of each 8-column group of one
-        // row.  Swapping the upper lanes of group 2h with the lower lanes of group 2h+1
-        // leaves lane l with columns 16h .. 16h+7 and lane l + 32 with 16h+8 .. 16h+15,
-        // so each lane writes 16 contiguous bytes (all lanes take part in the swaps).
+      // Lanes l and l + 32 hold the two 4-column halves of each 8-column group of one
+      // row.  Swapping the upper lanes of group 2h with the lower lanes of group 2h+1
+      // leaves lane l with columns 16h .. 16h+7 and lane l + 32 with 16h+8 .. 16h+15,
+      // so each lane writes 16 contiguous bytes (all lanes take part in the swaps).
 #pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
+      for (int h2 = 0; h2 < 2; ++h2) {
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const auto r = __builtin_amdgcn_permlane32_swap(pk[2 * h2][q], pk[2 * h2 + 1][q], false, false);
-            pk[2 * h2][q] = r[0];
-            pk[2 * h2 + 1][q] = r[1];
-            if constexpr (EPI == EPI_BIAS_ACT) {
-              const auto ra = __builtin_amdgcn_permlane32_swap(pa[2 * h2][q], pa[2 * h2 + 1][q], false, false);
-              pa[2 * h2][q] = ra[0];
-              pa[2 * h2 + 1][q] = ra[1];
-            }
+        for (int q = 0; q < 2; ++q) {
+          const auto r = __builtin_amdgcn_permlane32_swap(pk[2 * h2][q], pk[2 * h2 + 1][q], false, false);
+          pk[2 * h2][q] = r[0];
+          pk[2 * h2 + 1][q] = r[1];
+          if constexpr (EPI == EPI_BIAS_ACT) {
+            const auto ra = __builtin_amdgcn_permlane32_swap(pa[2 * h2][q], pa[2 * h2 + 1][q], false, false);
+            pa[2 * h2][q] = ra[0];
+            pa[2 * h2 + 1][q] = ra[1];
           }
-          const int c = cb + 16 * h2 + 8 * lhi;
-          if (mok && c < nvalid) {
-            *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(p.C) + crow + n0 + c) =
-                make_uint4(pk[2 * h2][0], pk[2 * h2][1], pk[2 * h2 + 1][0], pk[2 * h2 + 1][1]);
-            if constexpr (EPI == EPI_BIAS_ACT)
-              *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(p.C2) + crow + n0 + c) =
-                  make_uint4(pa[2 * h2][0], pa[2 * h2][1], pa[2 * h2 + 1][0], pa[2 * h2 + 1][1]);
-          }
+        }
+        const int c = cb + 16 * h2 + 8 * lhi;
+        if (mok && c < nvalid) {
+          *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(p.C) + crow + n0 + c) =
+              make_uint4(pk[2 * h2][0], pk[2 * h2][1], pk[2 * h2 + 1][0], pk[2 * h2 + 1][1]);
+          if constexpr (EPI == EPI_BIAS_ACT)
+            *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(p.C2) + crow + n0 + c) =
+                make_uint4(pa[2 * h2][0], pa[2 * h2][1], pa[2 * h2 + 1][0], pa[2 * h2 + 1][1]);
         }
       }
     };

@@ -1,7 +1,7 @@
 // Grouped fp32 GEMM on v_mfma_f32_32x32x2_f32, fed by the direct global->LDS loads of
 // gemm2.hpp (16 bytes per lane, no staging registers) through a ring of STAGES buffers.
 //
-// Same problem statement, tile plan and accumulator layout as grouped_gemm in gemm.hpp:
+// Problem statement of gemm.hpp, accumulator layout of gemm2.hpp:
 //   C[m][n] = sum_k A[m][k] B[n][k] per expert; GROUP_M groups rows (tokens), GROUP_K
 //   groups the contraction (tokens) for weight gradients.
 //   A_T / B_T: the operand is stored with m (n) contiguous, one row per k.
