@@ -10,6 +10,14 @@
 //      rank from one ballot per bit of the expert id, waves taken in order) and
 //      writes pos/row_token;
 //   4. each token's row of x is copied to its alive pairs' rows of x_perm.
+// These are small kernels whose cost is mostly their launches (about 4.6 us each in a
+// stream), so how many there are follows the size (launches / call, measured):
+//   * few pairs: steps 1 to 3 in one block, and step 4 too when it is a few rows
+//     (32 pairs over 1024 experts 23 us in five launches -> 7 us in one; 1000 pairs over 256
+//     experts 26 us -> 13 us in two);
+//   * histograms of few entries: step 2 in every block of step 3, which reads them all
+//     (16384 pairs over 1024 experts, steps 1 to 3 21.5 us in four launches -> 14 us in two);
+//   * else four launches for steps 1 to 3 (a scatter block would read megabytes).
 #include "common.hpp"
 
 namespace dmoe {
@@ -88,44 +96,112 @@ dispatch_scan_offsets(const int32_t* counts, int N, int32_t* offsets) {
   if (q == 1023) offsets[N] = sums[1023];
 }
 
-__global__ void __launch_bounds__(RT_NT)
-dispatch_scatter(const int32_t* idx, const uint8_t* alive, int P, int N, int k,
-                 const int32_t* block_hist, const int32_t* offsets, int32_t* pos, int32_t* row_token) {
-  extern __shared__ int base[];
-  const int32_t* bh = block_hist + (int64_t)blockIdx.x * N;
-  for (int e = threadIdx.x; e < N; e += RT_NT) base[e] = offsets[e] + bh[e];
-  __syncthreads();
+// Stable ranks of the pairs [p0, p0 + NT) of one block round (thread i holds pair p0 + i):
+// base[e] in LDS is the next row of expert e; waves take their turns in order.  Returns the
+// pair's row, or -1.
+template <int NT>
+__device__ __forceinline__ int rank_pairs(int e, int nbits, int waves, int* base) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // lanes of this wave holding the same id (or both none): the intersection, over the
+  // id's bits and its sign, of the ballots of lanes that agree with this lane's bit
+  uint64_t same = ~0ull;
+  for (int b = 0; b < nbits; ++b) {
+    const bool bit = (e >> b) & 1;
+    const uint64_t on = __ballot(bit);
+    same &= bit ? on : ~on;
+  }
+  {
+    const uint64_t neg = __ballot(e < 0);
+    same &= e < 0 ? neg : ~neg;
+  }
+  const int rank = __popcll(same & ((1ull << lane) - 1ull));
+  const bool last = ((same >> lane) >> 1) == 0ull;
+  int row = -1;
+  for (int w = 0; w < waves; ++w) {
+    if (wave == w && e >= 0) {
+      row = base[e] + rank;
+      if (last) base[e] = row + 1;
+    }
+    __syncthreads();
+  }
+  return row;
+}
+
+__device__ __forceinline__ int pair_expert(const int32_t* idx, const uint8_t* alive, int p, int P) {
+  if (p >= P) return -1;
+  const int e = idx[p];
+  return alive == nullptr || alive[e] ? e : -1;
+}
+
+// Exclusive scan of cnt[0 .. N) in LDS by a block of NT threads, in place; returns the total.
+// part: NT / 64 ints of LDS.
+template <int NT>
+__device__ __forceinline__ int scan_lds(int* cnt, int N, int* part) {
+  const int q = threadIdx.x, lane = q & 63, wave = q >> 6;
+  const int per = (N + NT - 1) / NT;
+  const int e0 = min(N, q * per), e1 = min(N, e0 + per);
+  int mine = 0;
+  for (int e = e0; e < e1; ++e) mine += cnt[e];
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  if (lane == 63) part[wave] = incl;
+  __syncthreads();
+  int run = incl - mine, total = 0;
+  for (int w = 0; w < NT / 64; ++w) {
+    if (w < wave) run += part[w];
+    total += part[w];
+  }
+  for (int e = e0; e < e1; ++e) {
+    const int c = cnt[e];
+    cnt[e] = run;
+    run += c;
+  }
+  __syncthreads();
+  return total;
+}
+
+// FOLD: the block's starting rows come from the histograms of all nb blocks (step 2 here;
+// block 0 writes counts and offsets); else from block_hist, already scanned, and offsets.
+template <bool FOLD>
+__global__ void __launch_bounds__(RT_NT)
+dispatch_scatter(const int32_t* idx, const uint8_t* alive, int P, int N, int k, int nb,
+                 const int32_t* block_hist, int32_t* counts, int32_t* offsets, int32_t* pos, int32_t* row_token) {
+  extern __shared__ int base[];
+  if constexpr (FOLD) {
+    __shared__ int part[RT_NT / 64];
+    int* before = base + N;
+    for (int e = threadIdx.x; e < N; e += RT_NT) {
+      int tot = 0, mine = 0;
+#pragma unroll 8
+      for (int b = 0; b < nb; ++b) {
+        const int v = block_hist[(int64_t)b * N + e];
+        tot += v;
+        mine += b < (int)blockIdx.x ? v : 0;
+      }
+      base[e] = tot;
+      before[e] = mine;
+      if (blockIdx.x == 0) counts[e] = tot;
+    }
+    __syncthreads();
+    const int total = scan_lds<RT_NT>(base, N, part);
+    for (int e = threadIdx.x; e < N; e += RT_NT) {
+      if (blockIdx.x == 0) offsets[e] = base[e];
+      base[e] += before[e];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) offsets[N] = total;
+  } else {
+    const int32_t* bh = block_hist + (int64_t)blockIdx.x * N;
+    for (int e = threadIdx.x; e < N; e += RT_NT) base[e] = offsets[e] + bh[e];
+  }
+  __syncthreads();
   const int nbits = 32 - __builtin_clz((unsigned)N);              // bits of the largest expert id
   for (int r = 0; r < DISP_CHUNK / RT_NT; ++r) {
     const int p = blockIdx.x * DISP_CHUNK + r * RT_NT + threadIdx.x;
-    int e = -1;
-    if (p < P) {
-      const int e0 = idx[p];
-      if (alive == nullptr || alive[e0]) e = e0;
-    }
-    // lanes of this wave holding the same id (or both none): the intersection, over the
-    // id's bits and its sign, of the ballots of lanes that agree with this lane's bit
-    uint64_t same = ~0ull;
-    for (int b = 0; b < nbits; ++b) {
-      const bool bit = (e >> b) & 1;
-      const uint64_t on = __ballot(bit);
-      same &= bit ? on : ~on;
-    }
-    {
-      const uint64_t neg = __ballot(e < 0);
-      same &= e < 0 ? neg : ~neg;
-    }
-    const int rank = __popcll(same & ((1ull << lane) - 1ull));
-    const bool last = ((same >> lane) >> 1) == 0ull;
-    int row = -1;
-    for (int w = 0; w < RT_NT / 64; ++w) {
-      if (wave == w && e >= 0) {
-        row = base[e] + rank;
-        if (last) base[e] = row + 1;
-      }
-      __syncthreads();
-    }
+    const int row = rank_pairs<RT_NT>(pair_expert(idx, alive, p, P), nbits, RT_NT / 64, base);
     if (p < P) {
       pos[p] = row;
       if (row >= 0) row_token[row] = p / k;
@@ -162,6 +238,65 @@ gather_rows(const E* x, const int32_t* pos, int T, int k, int D, E* xp) {
     }
   }
 }
+
+// Steps 1 to 3 by one block, for at most SMALL_PAIRS pairs; ROWS: step 4 as well.
+constexpr int SMALL_NT = 1024, SMALL_PAIRS = 2048;
+template <typename E, bool ROWS>
+__global__ void __launch_bounds__(SMALL_NT)
+dispatch_small(const int32_t* idx, const uint8_t* alive, int P, int N, int k, int32_t* counts, int32_t* offsets,
+               int32_t* pos, int32_t* row_token, const E* x, int T, int D, E* xp) {
+  extern __shared__ int base[];
+  __shared__ int part[SMALL_NT / 64];
+  __shared__ int spos[ROWS ? SMALL_PAIRS : 1];
+  const int tid = threadIdx.x;
+  constexpr int R = SMALL_PAIRS / SMALL_NT;
+  int e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) e[r] = pair_expert(idx, alive, r * SMALL_NT + tid, P);
+  for (int f = tid; f < N; f += SMALL_NT) base[f] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (e[r] >= 0) atomicAdd(&base[e[r]], 1);
+  __syncthreads();
+  for (int f = tid; f < N; f += SMALL_NT) counts[f] = base[f];
+  __syncthreads();
+  const int total = scan_lds<SMALL_NT>(base, N, part);
+  for (int f = tid; f < N; f += SMALL_NT) offsets[f] = base[f];
+  if (tid == 0) offsets[N] = total;
+  __syncthreads();
+  const int nbits = 32 - __builtin_clz((unsigned)N);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int p = r * SMALL_NT + tid;
+    const int left = P - r * SMALL_NT;
+    const int row = rank_pairs<SMALL_NT>(e[r], nbits, left <= 0 ? 0 : min(SMALL_NT / 64, (left + 63) / 64), base);
+    if (p < P) {
+      pos[p] = row;
+      if (row >= 0) row_token[row] = p / k;
+      if constexpr (ROWS) spos[p] = row;
+    }
+  }
+  if constexpr (ROWS) {
+    __syncthreads();
+    constexpr int VEC = 16 / sizeof(E);
+    const int CPR = D / VEC;
+    for (int q = tid; q < T * CPR; q += SMALL_NT) {
+      const int t = q / CPR, c = q % CPR;
+      const uint4 v = *reinterpret_cast<const uint4*>(x + (int64_t)t * D + c * VEC);
+      for (int j = 0; j < k; ++j) {
+        const int r = spos[t * k + j];
+        if (r >= 0) *reinterpret_cast<uint4*>(xp + (int64_t)r * D + c * VEC) = v;
+      }
+    }
+  }
+}
+// one block's histogram and token rows stay within 64 KB of LDS
+constexpr int64_t SMALL_EXPERTS = 8192;
+// the rows step 4 writes when one block may do it too
+constexpr int64_t SMALL_ROW_BYTES = 128 * 1024;
+// steps 2 and 3 in one launch up to this many histogram entries (read by every block)
+constexpr int64_t FOLD_ENTRIES = 32768, FOLD_EXPERTS = 4096;
 
 // y[t] = sum_j w[t,j] y_perm[pos[t,j]]; one wave per token (KM >= k slots held in
 // registers, each chunk's row loads issued before they are added in slot order).
@@ -374,14 +509,32 @@ extern "C" int dmoe_dispatch(const dmoe_dims* dims, const void* x, const int32_t
   int32_t* bh = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + L.hist_off);
   const int N = (int)s.N, P = (int)s.P;
   const int nb = (int)L.disp_blocks;
-  if (nb > 0)
-    DMOE_LAUNCH(dispatch_hist, dim3(nb), dim3(RT_NT), N * sizeof(int), st, idx, alive, P, N, bh);
-  DMOE_LAUNCH(dispatch_scan_cols, dim3((N + SCAN_E - 1) / SCAN_E), dim3(SCAN_E * SCAN_S), 0, st, bh, nb,
-                     N, counts);
-  DMOE_LAUNCH(dispatch_scan_offsets, dim3(1), dim3(1024), 0, st, counts, N, offsets);
-  if (nb == 0) return launch_status();
-  DMOE_LAUNCH(dispatch_scatter, dim3(nb), dim3(RT_NT), N * sizeof(int), st, idx, alive, P, N,
-                     s.k, bh, offsets, pos, row_token);
+  if (P > 0 && P <= SMALL_PAIRS && N <= SMALL_EXPERTS) {
+    const bool rows = s.P * s.D * (int64_t)s.esz <= SMALL_ROW_BYTES;
+    auto go = [&](auto EK, auto RC) {
+      using E = typename decltype(EK)::type;
+      DMOE_LAUNCH_NAMED("dispatch_small", (dispatch_small<E, decltype(RC)::value>), dim3(1), dim3(SMALL_NT),
+                        N * sizeof(int), st, idx, alive, P, N, s.k, counts, offsets, pos, row_token,
+                        reinterpret_cast<const E*>(x), (int)s.T, (int)s.D, reinterpret_cast<E*>(x_perm));
+    };
+    if (s.dtype == DMOE_BF16) rows ? go(type_tag<bf16>{}, std::true_type{}) : go(type_tag<bf16>{}, std::false_type{});
+    else rows ? go(type_tag<float>{}, std::true_type{}) : go(type_tag<float>{}, std::false_type{});
+    if (rows) return launch_status();
+  } else {
+    if (nb > 0)
+      DMOE_LAUNCH(dispatch_hist, dim3(nb), dim3(RT_NT), N * sizeof(int), st, idx, alive, P, N, bh);
+    if (nb > 0 && (int64_t)nb * N <= FOLD_ENTRIES && N <= FOLD_EXPERTS) {
+      DMOE_LAUNCH_NAMED("dispatch_scatter", dispatch_scatter<true>, dim3(nb), dim3(RT_NT), 2 * N * sizeof(int), st, idx,
+                        alive, P, N, s.k, nb, bh, counts, offsets, pos, row_token);
+    } else {
+      DMOE_LAUNCH(dispatch_scan_cols, dim3((N + SCAN_E - 1) / SCAN_E), dim3(SCAN_E * SCAN_S), 0, st, bh, nb,
+                         N, counts);
+      DMOE_LAUNCH(dispatch_scan_offsets, dim3(1), dim3(1024), 0, st, counts, N, offsets);
+      if (nb == 0) return launch_status();
+      DMOE_LAUNCH_NAMED("dispatch_scatter", dispatch_scatter<false>, dim3(nb), dim3(RT_NT), N * sizeof(int), st, idx,
+                        alive, P, N, s.k, nb, bh, counts, offsets, pos, row_token);
+    }
+  }
   const int64_t chunks = s.T * (s.D * (int64_t)s.esz / 16);
   const int grid = (int)std::min<int64_t>((chunks + RT_NT - 1) / RT_NT, 256 * 16);
   if (s.dtype == DMOE_BF16)
