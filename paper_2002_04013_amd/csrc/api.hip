@@ -49,8 +49,8 @@ Workspace workspace_layout(const Shape& s) {
   split = (split + 63) / 64 * 64;
   w.gsplit_tokens = split;
   w.gsplit = s.T > 0 ? (s.T + split - 1) / split : 0;
-  // tile bookkeeping: GEMM tile prefix [N+1], and of the experts with rows
-  const int64_t tiles_ints = 2 * (s.N + 1);
+  // tile bookkeeping: GEMM tile prefixes [N+1] for two tile heights, and of the experts with rows
+  const int64_t tiles_ints = 3 * (s.N + 1);
   w.tiles_off = off;
   w.tiles_bytes = align256((size_t)tiles_ints * sizeof(int32_t));
   off += w.tiles_bytes;

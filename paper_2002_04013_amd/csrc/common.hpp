@@ -173,7 +173,7 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // Workspace regions (byte offsets into the caller's ws buffer).
 struct Workspace {
   size_t hist_off, hist_bytes;     // dispatch: per-block expert histograms
-  size_t tiles_off, tiles_bytes;   // grouped GEMM: tile prefix [N+1] + per-expert m-tiles
+  size_t tiles_off, tiles_bytes;   // grouped GEMM: two tile prefixes [N+1] + prefix of experts with rows
   size_t part_off, part_bytes;     // gate backward: dWg partial sums per token split
   size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute
   size_t total;

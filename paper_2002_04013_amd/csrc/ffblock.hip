@@ -315,39 +315,57 @@ static void ln_bwd(const Shape& s, const int32_t* offsets, const E* h, const flo
 // ---------------------------------------------------------------- linear layers
 // Row-major operands: a layer's weight W [N, n_out, n_in], rows grouped by expert.
 
+// Tile shape of an fp32 layer's row-grouped GEMMs (bf16 ones are picked per GEMM).
+template <typename F> static void with_f32_tile(const Shape& s, F&& f) {
+  if (use_fat_f32(s)) f(CfgF32{});
+  else f(CfgF32Skinny{});
+}
+// the tile plan of a pass: heights for the F columns (a) and the D columns (b)
+template <typename E>
+static void block_plan(const Shape& s, const int32_t* offsets, const Plan& pl, hipStream_t st) {
+  if constexpr (sizeof(E) == 2) {
+    run_tile_plan(s, offsets, row_tile_rows(s, s.H), row_tile_rows(s, s.D), pl, st);
+  } else {
+    with_f32_tile(s, [&](auto cfg) { run_tile_plan(s, offsets, decltype(cfg)::TMR, decltype(cfg)::TMR, pl, st); });
+  }
+}
+template <bool BT, int EPI, typename E>
+static void lin_rows(const Shape& s, GemmArgs<E> p, hipStream_t st) {
+  if constexpr (sizeof(E) == 2) {
+    run_gemm2_rows<BT, EPI>(s, p, st);
+  } else {
+    with_f32_tile(s, [&](auto cfg) {
+      using C = decltype(cfg);
+      const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
+      p.tscale = (p.N + C::BN - 1) / C::BN;
+      run_gemm_f32<GROUP_M, false, BT, EPI, C>(p, mt_ub * p.tscale, st);
+    });
+  }
+}
+
 // C[rows, n_out] = A[rows, n_in] W_e^T + b_e
-template <typename E, typename C>
+template <typename E>
 static void lin_fwd(const Shape& s, const int32_t* offsets, const int32_t* tpre, const E* A, int n_in,
                     const E* W, const E* b, int n_out, E* Cp, hipStream_t st) {
-  const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
-  const int nt = (n_out + C::BN - 1) / C::BN;
-  GemmArgs<E> p = args_m<E>(offsets, tpre, nt, (int)s.N);
+  GemmArgs<E> p = args_m<E>(offsets, tpre, 0, (int)s.N);
   p.A = A; p.lda = n_in;
   p.B = W; p.ldb = n_in; p.b_gstride = (int64_t)n_out * n_in;
   p.C = Cp; p.ldc = n_out;
   p.bias = b; p.bias_gstride = n_out;
   p.N = n_out; p.K = n_in; p.act = s.act;
-  if constexpr (sizeof(E) == 2)
-    run_gemm2<GROUP_M, false, false, EPI_BIAS, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
-  else
-    run_gemm_f32<GROUP_M, false, false, EPI_BIAS, C>(p, mt_ub * nt, st);
+  lin_rows<false, EPI_BIAS>(s, p, st);
 }
 
 // dA[rows, n_in] = dC[rows, n_out] W_e   (W_e read as (n = input feature, k = output feature))
-template <typename E, typename C>
+template <typename E>
 static void lin_dgrad(const Shape& s, const int32_t* offsets, const int32_t* tpre, const E* dC, int n_out,
                       const E* W, int n_in, E* dA, hipStream_t st) {
-  const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
-  const int nt = (n_in + C::BN - 1) / C::BN;
-  GemmArgs<E> p = args_m<E>(offsets, tpre, nt, (int)s.N);
+  GemmArgs<E> p = args_m<E>(offsets, tpre, 0, (int)s.N);
   p.A = dC; p.lda = n_out;
   p.B = W; p.ldb = n_in; p.b_gstride = (int64_t)n_out * n_in;
   p.C = dA; p.ldc = n_in;
   p.N = n_in; p.K = n_out; p.act = s.act;
-  if constexpr (sizeof(E) == 2)
-    run_gemm2<GROUP_M, false, true, EPI_STORE, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
-  else
-    run_gemm_f32<GROUP_M, false, true, EPI_STORE, C>(p, mt_ub * nt, st);
+  lin_rows<true, EPI_STORE>(s, p, st);
 }
 
 // dW_e[n_out, n_in] = dC_e^T A_e over the expert's rows
@@ -383,36 +401,36 @@ template <typename E> struct BlockA {
   float *st1, *st2;
 };
 
-template <typename E, typename C>
+template <typename E>
 static void block_fwd(const Shape& s, const int32_t* offsets, const E* xp, const BlockP<E>& q, const BlockA<E>& t,
-                      E* yp, int32_t* tpre, hipStream_t st) {
+                      E* yp, const Plan& pl, hipStream_t st) {
   const int D = (int)s.D, F = (int)s.H;
-  DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, (int)s.N, C::TMR, tpre);
-  lin_fwd<E, C>(s, offsets, tpre, xp, D, q.W1, q.b1, F, t.h1, st);
+  block_plan<E>(s, offsets, pl, st);
+  lin_fwd<E>(s, offsets, pl.a, xp, D, q.W1, q.b1, F, t.h1, st);
   ln_fwd<E>(s, offsets, t.h1, q.g1, q.be1, t.a1, t.st1, st);
-  lin_fwd<E, C>(s, offsets, tpre, t.a1, F, q.W2, q.b2, F, t.h2, st);
+  lin_fwd<E>(s, offsets, pl.a, t.a1, F, q.W2, q.b2, F, t.h2, st);
   ln_fwd<E>(s, offsets, t.h2, q.g2, q.be2, t.a2, t.st2, st);
-  lin_fwd<E, C>(s, offsets, tpre, t.a2, F, q.W3, q.b3, D, yp, st);
+  lin_fwd<E>(s, offsets, pl.b, t.a2, F, q.W3, q.b3, D, yp, st);
 }
 
 // g2 holds da2 then dh2, g1 holds da1 then dh1 (each normalisation backward in place).
-template <typename E, typename C, typename CW>
+template <typename E, typename CW>
 static void block_bwd(const Shape& s, const int32_t* offsets, const E* xp, const BlockP<E>& q, const BlockA<E>& t,
-                      const E* dyp, E* g1, E* g2, E* dxp, const BlockG<E>& d, int32_t* tpre, hipStream_t st) {
+                      const E* dyp, E* g1, E* g2, E* dxp, const BlockG<E>& d, const Plan& pl, hipStream_t st) {
   const int D = (int)s.D, F = (int)s.H;
-  const int32_t* tact = tpre + s.N + 1;
-  DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, (int)s.N, C::TMR, tpre);
+  const int32_t* tact = pl.act;
+  block_plan<E>(s, offsets, pl, st);
   lin_wgrad<E, CW>(s, offsets, tact, dyp, D, t.a2, F, d.W3, st);     // dW3 = dy^T a2
   colsum<E>(s, offsets, dyp, D, d.b3, st);                            // db3
-  lin_dgrad<E, C>(s, offsets, tpre, dyp, D, q.W3, F, g2, st);        // da2 = dy W3
+  lin_dgrad<E>(s, offsets, pl.a, dyp, D, q.W3, F, g2, st);            // da2 = dy W3
   ln_bwd<E>(s, offsets, t.h2, t.st2, q.g2, q.be2, g2, g2, d.g2, d.be2, st);
   colsum<E>(s, offsets, g2, F, d.b2, st);                             // db2
   lin_wgrad<E, CW>(s, offsets, tact, g2, F, t.a1, F, d.W2, st);       // dW2 = dh2^T a1
-  lin_dgrad<E, C>(s, offsets, tpre, g2, F, q.W2, F, g1, st);         // da1 = dh2 W2
+  lin_dgrad<E>(s, offsets, pl.a, g2, F, q.W2, F, g1, st);             // da1 = dh2 W2
   ln_bwd<E>(s, offsets, t.h1, t.st1, q.g1, q.be1, g1, g1, d.g1, d.be1, st);
   colsum<E>(s, offsets, g1, F, d.b1, st);                             // db1
   lin_wgrad<E, CW>(s, offsets, tact, g1, F, xp, D, d.W1, st);         // dW1 = dh1^T x
-  lin_dgrad<E, C>(s, offsets, tpre, g1, F, q.W1, D, dxp, st);        // dx_perm = dh1 W1
+  lin_dgrad<E>(s, offsets, pl.b, g1, F, q.W1, D, dxp, st);            // dx_perm = dh1 W1
 }
 
 template <typename E> static BlockP<E> params_of(const dmoe_ffblock_params* p) {
@@ -511,20 +529,17 @@ extern "C" int dmoe_expert_ffblock_fwd(const dmoe_dims* dims, const int32_t* off
   if (!ln_width_supported(s)) return DMOE_EUNSUPPORTED;
   if (!aligned16(x_perm) || !aligned16(y_perm) || !aligned16(ws) || !params_aligned(params) || !acts_aligned(acts))
     return DMOE_EUNSUPPORTED;
-  int32_t* tpre = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).tiles_off);
+  const Plan pl =
+      plan_at(reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).tiles_off), s.N, true);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (s.dtype == DMOE_BF16) {
     const bf16* xp = reinterpret_cast<const bf16*>(x_perm);
     bf16* yp = reinterpret_cast<bf16*>(y_perm);
-    if (use_fat(s)) block_fwd<bf16, G2Fat>(s, offsets, xp, params_of<bf16>(params), acts_of<bf16>(acts), yp, tpre, st);
-    else block_fwd<bf16, G2Skinny>(s, offsets, xp, params_of<bf16>(params), acts_of<bf16>(acts), yp, tpre, st);
+    block_fwd<bf16>(s, offsets, xp, params_of<bf16>(params), acts_of<bf16>(acts), yp, pl, st);
   } else {
     const float* xp = reinterpret_cast<const float*>(x_perm);
     float* yp = reinterpret_cast<float*>(y_perm);
-    if (use_fat_f32(s))
-      block_fwd<float, CfgF32>(s, offsets, xp, params_of<float>(params), acts_of<float>(acts), yp, tpre, st);
-    else
-      block_fwd<float, CfgF32Skinny>(s, offsets, xp, params_of<float>(params), acts_of<float>(acts), yp, tpre, st);
+    block_fwd<float>(s, offsets, xp, params_of<float>(params), acts_of<float>(acts), yp, pl, st);
   }
   return launch_status();
 }
@@ -544,26 +559,23 @@ extern "C" int dmoe_expert_ffblock_bwd(const dmoe_dims* dims, const int32_t* off
   for (const void* q : {x_perm, dy_perm, (const void*)g1, (const void*)g2, (const void*)dx_perm, (const void*)ws})
     if (!aligned16(q)) return DMOE_EUNSUPPORTED;
   if (!params_aligned(params) || !params_aligned(grads) || !acts_aligned(acts)) return DMOE_EUNSUPPORTED;
-  int32_t* tpre = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).tiles_off);
+  const Plan pl =
+      plan_at(reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).tiles_off), s.N, true);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (s.dtype == DMOE_BF16) {
     auto c = [](const void* q) { return reinterpret_cast<const bf16*>(q); };
     auto m = [](void* q) { return reinterpret_cast<bf16*>(q); };
-    if (use_fat(s))
-      block_bwd<bf16, G2Fat, G2DW>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts), c(dy_perm),
-                                   m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), tpre, st);
+    if (deep_wgrad(s))
+      block_bwd<bf16, G2DW>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts), c(dy_perm),
+                            m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, st);
     else
-      block_bwd<bf16, G2Skinny, G2DWShort>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts),
-                                      c(dy_perm), m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), tpre, st);
+      block_bwd<bf16, G2DWShort>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts), c(dy_perm),
+                                 m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, st);
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    if (use_fat_f32(s))
-      block_bwd<float, CfgF32, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts),
-                                       c(dy_perm), m(g1), m(g2), m(dx_perm), grads_of<float>(grads), tpre, st);
-    else
-      block_bwd<float, CfgF32Skinny, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts),
-                                             c(dy_perm), m(g1), m(g2), m(dx_perm), grads_of<float>(grads), tpre, st);
+    block_bwd<float, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts), c(dy_perm),
+                             m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, st);
   }
   return launch_status();
 }

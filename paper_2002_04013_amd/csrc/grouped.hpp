@@ -4,6 +4,7 @@
 #pragma once
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 
 #include "common.hpp"
@@ -13,45 +14,61 @@
 
 namespace dmoe {
 
-// Tile plan of one FFN call, from the expert row offsets:
-//   plan[e]         = sum over experts before e of ceil(rows / BM)   (GROUP_M m-tiles)
-//   plan[N + 1 + e] = number of experts before e that have rows      (GROUP_K experts)
-// A GEMM with NT n-tiles (GROUP_M) or MT*NT tiles per expert (GROUP_K) scales these.
+// Tile plans of one FFN call, from the expert row offsets:
+//   plan_a[e], plan_b[e] = sum over experts before e of ceil(rows / BM) for two tile heights
+//                          (GROUP_M m-tiles; the GEMMs of a call use at most two)
+//   act[e]               = number of experts before e that have rows (GROUP_K experts)
+// with the totals at [N]; act may be null.  A GEMM with NT n-tiles (GROUP_M) or MT*NT tiles
+// per expert (GROUP_K) scales these.
 static __global__ void __launch_bounds__(1024)
-tile_plan(const int32_t* offsets, int N, int BM, int32_t* plan) {
-  __shared__ int s_mt[1024], s_ac[1024];
+tile_plan(const int32_t* offsets, int N, int BMa, int BMb, int32_t* plan_a, int32_t* plan_b, int32_t* act) {
+  __shared__ int s_a[1024], s_b[1024], s_ac[1024];
   const int q = threadIdx.x;
   const int EPT = (N + 1023) / 1024;
   const int e0 = min(N, q * EPT), e1 = min(N, e0 + EPT);
-  int mt = 0, ac = 0;
+  int ma = 0, mb = 0, ac = 0;
   for (int e = e0; e < e1; ++e) {
     const int c = offsets[e + 1] - offsets[e];
-    mt += (c + BM - 1) / BM;
+    ma += (c + BMa - 1) / BMa;
+    mb += (c + BMb - 1) / BMb;
     ac += c > 0;
   }
-  s_mt[q] = mt;
+  s_a[q] = ma;
+  s_b[q] = mb;
   s_ac[q] = ac;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
-    const int a = q >= o ? s_mt[q - o] : 0, b = q >= o ? s_ac[q - o] : 0;
+    const int va = q >= o ? s_a[q - o] : 0, vb = q >= o ? s_b[q - o] : 0, vc = q >= o ? s_ac[q - o] : 0;
     __syncthreads();
-    s_mt[q] += a;
-    s_ac[q] += b;
+    s_a[q] += va;
+    s_b[q] += vb;
+    s_ac[q] += vc;
     __syncthreads();
   }
-  int bm = s_mt[q] - mt, ba = s_ac[q] - ac;
-  int32_t* act = plan + N + 1;
+  int ba = s_a[q] - ma, bb = s_b[q] - mb, bc = s_ac[q] - ac;
   for (int e = e0; e < e1; ++e) {
-    plan[e] = bm;
-    act[e] = ba;
     const int c = offsets[e + 1] - offsets[e];
-    bm += (c + BM - 1) / BM;
-    ba += c > 0;
+    plan_a[e] = ba;
+    plan_b[e] = bb;
+    if (act) act[e] = bc;
+    ba += (c + BMa - 1) / BMa;
+    bb += (c + BMb - 1) / BMb;
+    bc += c > 0;
   }
   if (q == 1023) {
-    plan[N] = s_mt[1023];
-    act[N] = s_ac[1023];
+    plan_a[N] = s_a[1023];
+    plan_b[N] = s_b[1023];
+    if (act) act[N] = s_ac[1023];
   }
+}
+
+// The plans in a call's scratch: tile heights for outputs of H (a) and D (b) columns.
+struct Plan { int32_t *a, *b, *act; };
+static Plan plan_at(int32_t* mem, int64_t N, bool with_act) {
+  return {mem, mem + N + 1, with_act ? mem + 2 * (N + 1) : nullptr};
+}
+static void run_tile_plan(const Shape& s, const int32_t* offsets, int BMa, int BMb, const Plan& pl, hipStream_t st) {
+  DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, (int)s.N, BMa, BMb, pl.a, pl.b, pl.act);
 }
 
 // Column sums over each expert's rows, for the bias gradients (and the LayerNorm scale and
@@ -274,12 +291,77 @@ struct CfgF32Skinny { static constexpr int BM = 32, BN = 64, WM = 1, WN = 2, ST 
 struct G2Fat     { static constexpr int BM = 256, BN = 256, WM = 4, WN = 2, ST = 2, BK = 64, XB = 1,
                    TMR = BM + 32 * XB; };
 struct G2Skinny  { static constexpr int BM = 32, BN = 256, WM = 1, WN = 4, ST = 4, BK = 64, XB = 0, TMR = BM; };
+// Between the two, and for few weights:
+// G2Narrow: half the columns of G2Skinny, two blocks to a compute unit: twice the tiles.
+// G2Mid64, G2Mid: 64 or 128 rows by 128 columns, two blocks to a unit.
+struct G2Narrow  { static constexpr int BM = 32, BN = 128, WM = 1, WN = 4, ST = 4, BK = 64, XB = 0, TMR = BM; };
+struct G2Mid64   { static constexpr int BM = 64, BN = 128, WM = 2, WN = 2, ST = 3, BK = 64, XB = 0, TMR = BM; };
+struct G2Mid     { static constexpr int BM = 128, BN = 128, WM = 4, WN = 2, ST = 2, BK = 64, XB = 0, TMR = BM; };
 struct G2DW      { static constexpr int BM = 256, BN = 256, WM = 4, WN = 2, ST = 2, BK = 64,
                    STO = STORE_STAGED_NT; };
 struct G2DWShort { static constexpr int BM = 256, BN = 256, WM = 4, WN = 2, ST = 4, BK = 32,
                    STO = STORE_STAGED_NT; };
 
-static bool use_fat(const Shape& s) { return s.P >= (int64_t)96 * s.N; }
+// weight gradients: 64-deep k-steps from an average of 96 rows per expert on
+static bool deep_wgrad(const Shape& s) { return s.P >= (int64_t)96 * s.N; }
+
+// The row-grouped tile shape for an output of n columns and a contraction over K, from the
+// average number of rows per expert r = P / N and the tile counts it gives.
+//   * r < 24 (weight streaming): G2Skinny; G2Narrow when the weights that can be touched are
+//     under 512 MiB, where a call is a few tiles per unit and their latency counts.
+//     Measured, up and down projection in us: 4 experts of 1024 x 4096 touched 18.7 + 39.0 ->
+//     14.8 + 29.5, 32 experts 57.9 + 61.1 -> 51.3 + 54.4, 55 experts 94.9 + 112.1 -> 84.4 +
+//     91.5, but 256 experts 241 -> 256 (down), 1024 experts of 16 rows 1680 -> 1770.
+//   * G2Mid, or G2Fat where its rounds over the units cost less: a round of G2Fat tiles (one
+//     block to a unit) takes about 1.65 rounds of G2Mid tiles (two to a unit).  Measured, up
+//     and down in us, G2Skinny / G2Mid / G2Fat: 16 experts of 100 rows 60 + 51 / 33 + 62 /
+//     38 + 87; 25 experts of 82 rows (D = 2048) 144 + 152 / 104 + 104 / 126 + 125; 25 of 324
+//     rows (D = 960, H = 3008) - / 110 + 101 / 124 + 84; 64 of 256 rows - / 283 + 229 /
+//     253 + 274; 16 of 2048 rows (D = 512) - / 182 + 106 / 142 + 86.
+//   * fewer G2Mid tiles than compute units (narrow outputs of few experts): smaller tiles.
+//     G2Skinny / G2Narrow / G2Mid64 / G2Mid / G2Fat, down projection of 16 experts in us:
+//     32 rows 45 / 31 / 40 / 54 / 73; 64 rows 46 / 45 / 43 / 56 / 77; 100 rows 51 / 49 / 46 /
+//     62 / 87; 150 rows 92 / 70 / 60 / 64 / 93.  So G2Narrow below 48 rows, else G2Mid64.
+enum RowTile { RT_SKINNY, RT_NARROW, RT_MID64, RT_MID, RT_FAT };
+static RowTile row_tile(const Shape& s, int64_t n, int64_t K) {
+  const double act = (double)std::min<int64_t>(s.N, s.P), r = (double)s.P / (double)s.N;
+  if (r < 24.0) return act * (double)n * (double)K * 2.0 < 536870912.0 ? RT_NARROW : RT_SKINNY;
+  const int cus = device_cus();
+  auto tiles = [&](int BM, int BN) { return act * std::max(1.0, r / BM + 0.5) * (double)((n + BN - 1) / BN); };
+  auto rounds = [&](double t, int per_cu) { return std::ceil(t / (double)(cus * per_cu)); };
+  const double mid = tiles(G2Mid::TMR, G2Mid::BN);
+  if (mid < cus) return r < 48.0 ? RT_NARROW : RT_MID64;
+  return 1.65 * rounds(tiles(G2Fat::TMR, G2Fat::BN), 1) <= rounds(mid, 2) ? RT_FAT : RT_MID;
+}
+// its tile height, which depends on n alone (every shape of r < 24 is 32 rows high)
+static int row_tile_rows(const Shape& s, int64_t n) {
+  switch (row_tile(s, n, 1)) {
+    case RT_MID64: return G2Mid64::TMR;
+    case RT_MID: return G2Mid::TMR;
+    case RT_FAT: return G2Fat::TMR;
+    default: return G2Skinny::TMR;
+  }
+}
+
+// One row-grouped GEMM in the tile shape row_tile picks: p.tscale and the grid are set here.
+template <bool BT, int EPI>
+static void run_gemm2_rows(const Shape& s, GemmArgs<bf16> p, hipStream_t st) {
+  auto go = [&](auto cfg) {
+    using C = decltype(cfg);
+    const int nt = (p.N + C::BN - 1) / C::BN;
+    const int64_t mt_ub = (s.P + C::TMR - 1) / C::TMR + std::min<int64_t>(s.N, s.P);
+    p.tscale = nt;
+    run_gemm2<GROUP_M, false, BT, EPI, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
+  };
+  switch (row_tile(s, p.N, p.K)) {
+    case RT_SKINNY: go(G2Skinny{}); break;
+    case RT_NARROW: go(G2Narrow{}); break;
+    case RT_MID64: go(G2Mid64{}); break;
+    case RT_MID: go(G2Mid{}); break;
+    case RT_FAT: go(G2Fat{}); break;
+  }
+}
+
 // fp32: 64-row tiles from an average of 48 rows per expert on
 static bool use_fat_f32(const Shape& s) { return s.P >= (int64_t)48 * s.N; }
 
