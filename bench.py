@@ -172,6 +172,8 @@ def _block_kernel_algorithmic(name, wl, rows, touched, e):
     lnp = 2 * touched * F * e + 8 * rows
     if name.startswith("(ln_act_fwd_kernel"):
         return "LayerNorm + act forward", 0, 2 * rows * F * e + lnp
+    if name.startswith("ln_bwd_kernel"):
+        return "LayerNorm + act backward (rows, scale, shift, bias)", 0, 3 * rows * F * e + lnp + 3 * touched * F * e
     if name.startswith("(ln_act_bwd_rows_kernel"):
         return "LayerNorm + act backward (rows)", 0, 3 * rows * F * e + lnp
     if name.startswith("(ln_act_bwd_params_kernel"):

@@ -176,9 +176,11 @@ struct Workspace {
   size_t tiles_off, tiles_bytes;   // grouped GEMM: two tile prefixes [N+1] + prefix of experts with rows
   size_t part_off, part_bytes;     // gate backward: dWg partial sums per token split
   size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute
+  size_t ln_off;                   // LayerNorm backward: partial column sums (over part and gq)
   size_t total;
   int64_t disp_blocks;             // dispatch blocks (pairs per block = DISP_CHUNK)
   int64_t gsplit, gsplit_tokens;   // gate backward token splits
+  int64_t ln_blocks;               // LayerNorm backward blocks (H up to 512 16-byte chunks)
 };
 
 constexpr int DISP_CHUNK = 1024;   // pairs per dispatch block

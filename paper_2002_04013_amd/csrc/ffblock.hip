@@ -259,6 +259,205 @@ ln_act_bwd_params_kernel(const E* h, const float* stats, const int32_t* offsets,
   *reinterpret_cast<uint4*>(dbeta + (int64_t)e * F + c) = Vec<E>::pack(acc[1]);
 }
 
+// ---- the whole backward of a normalisation step in one pass over h and da ----
+//
+// ln_bwd_kernel does what ln_act_bwd_rows_kernel, ln_act_bwd_params_kernel and the column sum
+// of dh (the bias gradient of the linear layer before it) do: dh per row, and per expert
+// dgamma, dbeta and db = sum of its dh rows (as stored).  A block holds whole rows, one
+// 16-byte chunk to a thread, two rows at a time with the next two loaded ahead; the row sums
+// meet in LDS, the column sums stay in the thread's registers while the expert's rows last.
+// A block takes a contiguous share of all rows: the sums of an expert that lies in one block
+// are stored at once, the pieces of an expert spread over several go to `part` and
+// ln_bwd_reduce_kernel adds them in row order.
+// Bound by memory: h and da read, dh written.  64 experts of 2048 rows, F = 4096 bf16: 711 to
+// 749 us (4.5 TB/s) and 9 for the reduction, in place of 390 (parameters) + 684 (rows) + 231
+// (column sums), which read h and da twice and dh once more.  Held to 128 registers, for two
+// blocks to a unit, it spills and takes 1590 us.
+constexpr int LB_R = 2;                  // rows in flight per block step
+
+static int lb_threads(int64_t chunks) { return chunks <= 64 ? 64 : chunks <= 128 ? 128 : chunks <= 256 ? 256 : 512; }
+// `part` rows of 3 F floats: piece of the expert that begins in an earlier block: the block's
+// index; piece of one that ends in a later block: after those, by expert or by block,
+// whichever are fewer
+__device__ __forceinline__ int lb_first_slot(int b) { return b; }
+__device__ __forceinline__ int lb_last_slot(int nb, int N, int b, int e) { return nb + (N < nb ? e : b); }
+
+// sum over the wave, left in lane 63
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float add_dpp(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum63(float v) {
+  v = add_dpp<0xB1, 0xf>(v);       // quad_perm [1,0,3,2]
+  v = add_dpp<0x4E, 0xf>(v);       // quad_perm [2,3,0,1]
+  v = add_dpp<0x141, 0xf>(v);      // row_half_mirror
+  v = add_dpp<0x140, 0xf>(v);      // row_mirror: every lane holds its row's sum
+  v = add_dpp<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v = add_dpp<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+template <typename E, int ACT, int NT>
+__global__ void __launch_bounds__(NT)
+ln_bwd_kernel(const E* h, const float* stats, const int32_t* offsets, int N, int F, const E* gamma, const E* beta,
+              const E* da, E* dh, E* dgamma, E* dbeta, E* db, float* part) {
+  constexpr int VEC = Vec<E>::N, NW = NT / 64;
+  __shared__ __align__(16) float red[2][NW][2 * LB_R];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = gridDim.x, blk = blockIdx.x;
+  const int P = offsets[N];
+  const int per = (P + nb - 1) / nb;
+  const int r0 = min(P, blk * per), r1 = min(P, r0 + per);
+  if (r0 >= r1) return;
+  const bool on = tid * VEC < F;
+  const int c = on ? tid * VEC : 0;
+  const float invF = 1.f / (float)F;
+  int e = row_expert(offsets, N, r0);
+  int buf = 0;
+  for (int r = r0; r < r1;) {
+    while (offsets[e + 1] <= r) ++e;
+    const int ebeg = offsets[e], eend = offsets[e + 1];
+    const int pend = min(r1, eend);
+    const uint4 gq = *reinterpret_cast<const uint4*>(gamma + (int64_t)e * F + c);
+    const uint4 bq = *reinterpret_cast<const uint4*>(beta + (int64_t)e * F + c);
+    float ag[VEC], ab[VEC], ad[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) ag[j] = ab[j] = ad[j] = 0.f;
+    struct Rows { uint4 h[LB_R], d[LB_R]; float2 st[LB_R]; };
+    Rows cur, nxt;
+    auto load = [&](Rows& v, int q) {
+#pragma unroll
+      for (int u = 0; u < LB_R; ++u) {
+        const int64_t row = min(q + u, pend - 1);
+        v.h[u] = *reinterpret_cast<const uint4*>(h + row * F + c);
+        v.d[u] = *reinterpret_cast<const uint4*>(da + row * F + c);
+        v.st[u] = *reinterpret_cast<const float2*>(stats + 2 * row);
+      }
+    };
+    load(cur, r);
+    for (int q = r; q < pend; q += LB_R) {
+      if (q + LB_R < pend) load(nxt, q + LB_R);
+      float dn[LB_R][VEC];
+      float s[2 * LB_R];
+      float g[VEC], b[VEC];
+      Vec<E>::unpack(gq, g);
+      Vec<E>::unpack(bq, b);
+#pragma unroll
+      for (int u = 0; u < LB_R; ++u) {
+        // a row past the piece contributes nothing (and is not stored below)
+        const float live = on && q + u < pend ? 1.f : 0.f;
+        float x[VEC], d[VEC];
+        Vec<E>::unpack(cur.h[u], x);
+        Vec<E>::unpack(cur.d[u], d);
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+          const float n = (x[j] - cur.st[u].x) * cur.st[u].y;
+          const float dz = d[j] * act_b<E, ACT>(fmaf(g[j], n, b[j]));
+          dn[u][j] = dz * g[j];
+          s1 += dn[u][j];
+          s2 += dn[u][j] * n;
+          if (live != 0.f) { ag[j] += dz * n; ab[j] += dz; }
+        }
+        s[2 * u] = live != 0.f ? s1 : 0.f;
+        s[2 * u + 1] = live != 0.f ? s2 : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 2 * LB_R; ++i) s[i] = wave_sum63(s[i]);
+      if (lane == 63) *reinterpret_cast<float4*>(red[buf][wave]) = make_float4(s[0], s[1], s[2], s[3]);
+      __syncthreads();
+      float m[2 * LB_R] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(red[buf][w]);
+        m[0] += v.x; m[1] += v.y; m[2] += v.z; m[3] += v.w;
+      }
+      buf ^= 1;
+#pragma unroll
+      for (int u = 0; u < LB_R; ++u) {
+        if (on && q + u < pend) {
+          const float m1 = m[2 * u] * invF, m2 = m[2 * u + 1] * invF;
+          float x[VEC], o[VEC];
+          Vec<E>::unpack(cur.h[u], x);
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) {
+            const float n = (x[j] - cur.st[u].x) * cur.st[u].y;
+            o[j] = cur.st[u].y * (dn[u][j] - m1 - n * m2);
+          }
+          const uint4 ov = Vec<E>::pack(o);
+          *reinterpret_cast<uint4*>(dh + (int64_t)(q + u) * F + c) = ov;
+          Vec<E>::unpack(ov, o);
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) ad[j] += o[j];
+        }
+      }
+      cur = nxt;
+    }
+    if (on) {
+      if (r == ebeg && pend == eend) {
+        *reinterpret_cast<uint4*>(dgamma + (int64_t)e * F + c) = Vec<E>::pack(ag);
+        *reinterpret_cast<uint4*>(dbeta + (int64_t)e * F + c) = Vec<E>::pack(ab);
+        *reinterpret_cast<uint4*>(db + (int64_t)e * F + c) = Vec<E>::pack(ad);
+      } else {
+        float* p = part + (int64_t)(r == r0 ? lb_first_slot(blk) : lb_last_slot(nb, N, blk, e)) * 3 * F + c;
+#pragma unroll
+        for (int j = 0; j < VEC; j += 4) {
+          *reinterpret_cast<float4*>(p + j) = make_float4(ag[j], ag[j + 1], ag[j + 2], ag[j + 3]);
+          *reinterpret_cast<float4*>(p + F + j) = make_float4(ab[j], ab[j + 1], ab[j + 2], ab[j + 3]);
+          *reinterpret_cast<float4*>(p + 2 * F + j) = make_float4(ad[j], ad[j + 1], ad[j + 2], ad[j + 3]);
+        }
+      }
+    }
+    r = pend;
+  }
+}
+
+// The experts whose rows ln_bwd_kernel's blocks split: their pieces added in row order.
+// Block (x, e): 256 threads take 1024 of the 3 F sums of expert e.
+template <typename E>
+__global__ void __launch_bounds__(256)
+ln_bwd_reduce_kernel(const int32_t* offsets, int N, int F, int nb, const float* part, E* dgamma, E* dbeta, E* db) {
+  const int e = blockIdx.y;
+  const int ebeg = offsets[e], eend = offsets[e + 1];
+  if (ebeg == eend) return;
+  const int P = offsets[N];
+  const int per = (P + nb - 1) / nb;
+  const int b0 = ebeg / per, b1 = (eend - 1) / per;
+  if (b0 == b1) return;
+  const int q = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;
+  if (q >= 3 * F) return;
+  float4 s = *reinterpret_cast<const float4*>(
+      part + (int64_t)(ebeg == b0 * per ? lb_first_slot(b0) : lb_last_slot(nb, N, b0, e)) * 3 * F + q);
+  for (int b = b0 + 1; b <= b1; ++b) {
+    const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)lb_first_slot(b) * 3 * F + q);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  E* out = (q < F ? dgamma : q < 2 * F ? dbeta : db) + (int64_t)e * F + q % F;   // F is a multiple of 64
+  out[0] = cvt<E>(s.x); out[1] = cvt<E>(s.y); out[2] = cvt<E>(s.z); out[3] = cvt<E>(s.w);
+}
+
+template <typename E>
+static void ln_bwd_fused(const Shape& s, const int32_t* offsets, const E* h, const float* stats, const E* g, const E* b,
+                         const E* da, E* dh, E* dg, E* dbe, E* db, float* part, hipStream_t st) {
+  const int N = (int)s.N, F = (int)s.H, nt = lb_threads(F / Vec<E>::N);
+  const int nb = (int)workspace_layout(s).ln_blocks;
+  auto go = [&](auto ACTc, auto NTc) {
+    constexpr int ACT = decltype(ACTc)::value, NT = decltype(NTc)::value;
+    DMOE_LAUNCH_NAMED("ln_bwd_kernel", (ln_bwd_kernel<E, ACT, NT>), dim3(nb), dim3(NT), 0, st, h, stats, offsets, N, F, g,
+                      b, da, dh, dg, dbe, db, part);
+  };
+  auto nts = [&](auto ACTc) {
+    if (nt == 64) go(ACTc, std::integral_constant<int, 64>{});
+    else if (nt == 128) go(ACTc, std::integral_constant<int, 128>{});
+    else if (nt == 256) go(ACTc, std::integral_constant<int, 256>{});
+    else go(ACTc, std::integral_constant<int, 512>{});
+  };
+  if (s.act == DMOE_RELU) nts(std::integral_constant<int, DMOE_RELU>{});
+  else nts(std::integral_constant<int, DMOE_GELU>{});
+  DMOE_LAUNCH_NAMED("ln_bwd_reduce_kernel", ln_bwd_reduce_kernel<E>, dim3((unsigned)((3 * F + 1023) / 1024), (unsigned)N),
+                    dim3(256), 0, st, offsets, N, F, nb, part, dg, dbe, db);
+}
+
 // chunks per lane for a row of F values: the smallest of 1, 2, 4, 8 that holds it
 template <typename E> static int ln_chunks(int64_t F) {
   const int64_t per = (F / Vec<E>::N + 63) / 64;
@@ -416,19 +615,18 @@ static void block_fwd(const Shape& s, const int32_t* offsets, const E* xp, const
 // g2 holds da2 then dh2, g1 holds da1 then dh1 (each normalisation backward in place).
 template <typename E, typename CW>
 static void block_bwd(const Shape& s, const int32_t* offsets, const E* xp, const BlockP<E>& q, const BlockA<E>& t,
-                      const E* dyp, E* g1, E* g2, E* dxp, const BlockG<E>& d, const Plan& pl, hipStream_t st) {
+                      const E* dyp, E* g1, E* g2, E* dxp, const BlockG<E>& d, const Plan& pl, float* part,
+                      hipStream_t st) {
   const int D = (int)s.D, F = (int)s.H;
   const int32_t* tact = pl.act;
   block_plan<E>(s, offsets, pl, st);
   lin_wgrad<E, CW>(s, offsets, tact, dyp, D, t.a2, F, d.W3, st);     // dW3 = dy^T a2
   colsum<E>(s, offsets, dyp, D, d.b3, st);                            // db3
   lin_dgrad<E>(s, offsets, pl.a, dyp, D, q.W3, F, g2, st);            // da2 = dy W3
-  ln_bwd<E>(s, offsets, t.h2, t.st2, q.g2, q.be2, g2, g2, d.g2, d.be2, st);
-  colsum<E>(s, offsets, g2, F, d.b2, st);                             // db2
+  ln_bwd_fused<E>(s, offsets, t.h2, t.st2, q.g2, q.be2, g2, g2, d.g2, d.be2, d.b2, part, st);   // dh2, dg2, dbe2, db2
   lin_wgrad<E, CW>(s, offsets, tact, g2, F, t.a1, F, d.W2, st);       // dW2 = dh2^T a1
   lin_dgrad<E>(s, offsets, pl.a, g2, F, q.W2, F, g1, st);             // da1 = dh2 W2
-  ln_bwd<E>(s, offsets, t.h1, t.st1, q.g1, q.be1, g1, g1, d.g1, d.be1, st);
-  colsum<E>(s, offsets, g1, F, d.b1, st);                             // db1
+  ln_bwd_fused<E>(s, offsets, t.h1, t.st1, q.g1, q.be1, g1, g1, d.g1, d.be1, d.b1, part, st);   // dh1, dg1, dbe1, db1
   lin_wgrad<E, CW>(s, offsets, tact, g1, F, xp, D, d.W1, st);         // dW1 = dh1^T x
   lin_dgrad<E>(s, offsets, pl.b, g1, F, q.W1, D, dxp, st);            // dx_perm = dh1 W1
 }
@@ -561,21 +759,22 @@ extern "C" int dmoe_expert_ffblock_bwd(const dmoe_dims* dims, const int32_t* off
   if (!params_aligned(params) || !params_aligned(grads) || !acts_aligned(acts)) return DMOE_EUNSUPPORTED;
   const Plan pl =
       plan_at(reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).tiles_off), s.N, true);
+  float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + workspace_layout(s).ln_off);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (s.dtype == DMOE_BF16) {
     auto c = [](const void* q) { return reinterpret_cast<const bf16*>(q); };
     auto m = [](void* q) { return reinterpret_cast<bf16*>(q); };
     if (deep_wgrad(s))
       block_bwd<bf16, G2DW>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts), c(dy_perm),
-                            m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, st);
+                            m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, part, st);
     else
       block_bwd<bf16, G2DWShort>(s, offsets, c(x_perm), params_of<bf16>(params), acts_of<bf16>(acts), c(dy_perm),
-                                 m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, st);
+                                 m(g1), m(g2), m(dx_perm), grads_of<bf16>(grads), pl, part, st);
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
     block_bwd<float, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts), c(dy_perm),
-                             m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, st);
+                             m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, part, st);
   }
   return launch_status();
 }

@@ -623,6 +623,7 @@ __device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples&
     if (lane + 64 * h < dM) {
       const float* dv = q.dec + ci[h] * M4;
       int r = 0;
+#pragma unroll 8
       for (int u = 0; u < M4; u += 4) {
         const float4 o = *reinterpret_cast<const float4*>(dv + u);
         r += (o.x > cv[h]) + (o.y > cv[h]) + (o.z > cv[h]) + (o.w > cv[h]);
@@ -683,10 +684,11 @@ __device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples&
   }
   wave_lds_sync();
   int rc[2] = {0, 0};
+#pragma unroll 8
   for (int o = 0; o < cnt; ++o) {
     const double v = q.tot[o];
     rc[0] += v > tv[0];
-    if (cnt > 64) rc[1] += v > tv[1];
+    rc[1] += v > tv[1];
   }
   auto put_cells = [&]() {
 #pragma unroll
@@ -940,14 +942,14 @@ static size_t gate_f64_lds_bytes(const Shape& s) {
 }
 // bf16 gates with at most 96 columns: exact scores for every token, or the certified route
 // (three launches: queue clearing, scoring, recomputation).  In microseconds the exact route
-// takes about its padded matrix flops at 70 TFLOP/s plus T / 1500 of selection, above the
-// launch; the certified one starts at about 36 and follows the read of x.  Measured, exact
-// against certified: T = 4096, D = 1024, 64 columns 24 / 58; T = 8192, D = 4096, 32 columns
-// 40 / 55; T = 32768, D = 1024, 32 columns 59 / 50; T = 32768, D = 4096, 32 columns
-// 193 / 97.  So exact up to 48 us by that estimate.
+// takes about 8, its padded matrix flops at 70 TFLOP/s, T / 1500 for the selection and the
+// read of x; the certified one 36 and the read of x.  Measured, exact against certified:
+// T = 3001, D = 960, 16 columns 15 / 38; T = 4096, D = 1024, 64 columns 24 / 58; T = 8192,
+// D = 4096, 16 columns 40 / 55; T = 32768, D = 1024, 16 columns 59 / 50; T = 32768,
+// D = 4096, 32 columns 193 / 97.
 static bool gate_f64_pays(const Shape& s) {
   const double flops = 2.0 * (double)s.T * (double)s.D * 16.0 * gate_f64_tiles(s);
-  return flops / 70e6 + (double)s.T / 1500.0 <= 48.0;
+  return flops / 70e6 + (double)s.T / 1500.0 <= 28.0;
 }
 static size_t gate_mfma_lds_bytes(int dM, int kw) {
   const size_t ring = (size_t)kw * GM_RING * 4096 * (1 + (dM + 31) / 32);

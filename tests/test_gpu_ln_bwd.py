@@ -1,0 +1,70 @@
+"""The one-pass LayerNorm backward of the block experts at the edges of its row shares (at
+least 8 rows a block, two at a time): experts of odd counts, within one block, spread over
+several, beginning and ending on block bounds, empty, more experts than blocks and fewer; row
+widths at each block size and at the widest.  Against fp64 on the GPU from the library's own
+stored inputs to each step (h, the incoming gradient rounded to the stored type), elementwise
+|err| <= rtol (|ref| + rms) with the tolerances of the stored type (bf16 2e-2, fp32 1e-5 times
+the square root of the rows added)."""
+import pytest
+import torch
+
+from paper_2002_04013_amd import abi
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    ("bf16", 64, 64, [8, 8, 16, 1, 0, 7, 9, 23]), ("bf16", 64, 576, [301, 0, 2, 5]),
+    ("bf16", 128, 1088, [3] * 40 + [0, 17, 1, 33]), ("bf16", 64, 4096, [129, 0, 64, 3]),
+    ("f32", 64, 64, [5, 0, 90, 1, 8, 8]), ("f32", 64, 320, [2] * 60 + [41]), ("f32", 64, 2048, [1, 70, 0, 9]),
+]
+
+
+@pytest.mark.parametrize("dtype,D,F,counts", CASES)
+def test_block_backward_normalisation(dtype, D, F, counts):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    N, rows = len(counts), sum(counts)
+    P, dev = rows + 3, torch.device("cuda:0")
+    g = torch.Generator(device="cuda").manual_seed(F + N)
+    rn = lambda *s, sc=1.0: (torch.randn(*s, generator=g, device=dev) * sc).to(dt)
+    dims = abi.make_dims(P, D, F, 1, N, 1, dtype, "gelu")
+    offs = torch.tensor([0] + counts, dtype=torch.int32).cumsum(0).to(torch.int32)
+    par = dict(W1=rn(N, F, D, sc=D ** -0.5), b1=rn(N, F), g1=1 + rn(N, F, sc=0.3), be1=rn(N, F), W2=rn(N, F, F, sc=F ** -0.5),
+               b2=rn(N, F), g2=1 + rn(N, F, sc=0.3), be2=rn(N, F), W3=rn(N, D, F, sc=F ** -0.5), b3=rn(N, D))
+    x, dy = rn(P, D), rn(P, D)
+    nan = lambda *s, t=dt: torch.full(s, float("nan"), dtype=t, device=dev)
+    acts = dict(h1=nan(P, F), a1=nan(P, F), st1=nan(P, 2, t=torch.float32), h2=nan(P, F), a2=nan(P, F),
+                st2=nan(P, 2, t=torch.float32))
+    grads = {n: torch.full_like(v, 7.0) for n, v in par.items()}
+    d1, d2, dx, y = nan(P, F), nan(P, F), nan(P, D), nan(P, D)
+    ws = torch.full((abi.workspace_bytes(dims),), 255, dtype=torch.uint8, device=dev)
+    off = offs.to(dev)
+    abi.dmoe_expert_ffblock_fwd(dims, off, x, par, acts, y, ws)
+    abi.dmoe_expert_ffblock_bwd(dims, off, x, par, acts, dy, d1, d2, dx, grads, ws)
+    torch.cuda.synchronize()
+    for t in (d1, d2, dx):
+        assert bool(t[rows:].isnan().all()) and not bool(t[:rows].isnan().any())
+    for e in range(N):
+        if counts[e] == 0:
+            assert all(bool((v[e] == 7.0).all()) for v in grads.values()), e
+            continue
+        s = slice(int(offs[e]), int(offs[e + 1]))
+
+        def step(da, h, gam, bet, dh, dgam, dbet, db, tag):
+            h, gam, bet, da = h[s].double(), gam[e].double(), bet[e].double(), da.to(dt).double()
+            rstd = 1.0 / torch.sqrt(h.var(1, unbiased=False, keepdim=True) + 1e-5)
+            n = (h - h.mean(1, keepdim=True)) * rstd
+            z = gam * n + bet
+            dz = da * (0.5 * (1 + torch.erf(z * 0.5 ** 0.5)) + z * torch.exp(-0.5 * z * z) * (2 * torch.pi) ** -0.5)
+            dn = dz * gam
+            want = rstd * (dn - dn.mean(1, keepdim=True) - n * (dn * n).mean(1, keepdim=True))
+            rt = 2e-2 if dtype == "bf16" else 1e-5 * max(1.0, counts[e] ** 0.5)
+            for got, ref, name in ((dh[s], want, "dh"), (dgam[e], (dz * n).sum(0), "scale"), (dbet[e], dz.sum(0), "shift"),
+                                   (db[e], dh[s].double().sum(0), "bias")):
+                # sums are compared against the size of what is added, not of a sum that may cancel
+                rms = (dz.square().sum(0).mean().sqrt() if name != "dh" else ref.square().mean().sqrt())
+                assert bool(((got.double() - ref).abs() <= rt * (ref.abs() + rms)).all()), (tag, name, e)
+
+        step(dy[s].double() @ par["W3"][e].double(), acts["h2"], par["g2"], par["be2"], d2, grads["g2"], grads["be2"],
+             grads["b2"], "second")
+        step(d2[s].double() @ par["W2"][e].double(), acts["h1"], par["g1"], par["be1"], d1, grads["g1"], grads["be1"],
+             grads["b1"], "first")
