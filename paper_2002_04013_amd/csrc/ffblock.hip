@@ -773,8 +773,12 @@ extern "C" int dmoe_expert_ffblock_bwd(const dmoe_dims* dims, const int32_t* off
   } else {
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
-    block_bwd<float, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts), c(dy_perm),
-                             m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, part, st);
+    if (use_fat_f32(s))
+      block_bwd<float, CfgF32DW>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts), c(dy_perm),
+                                 m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, part, st);
+    else
+      block_bwd<float, CfgF32>(s, offsets, c(x_perm), params_of<float>(params), acts_of<float>(acts), c(dy_perm),
+                               m(g1), m(g2), m(dx_perm), grads_of<float>(grads), pl, part, st);
   }
   return launch_status();
 }

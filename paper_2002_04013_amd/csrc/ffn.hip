@@ -304,7 +304,7 @@ static int ffn_bwd_checked(const dmoe_dims* dims, const int32_t* offsets, const 
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
     if (use_fat_f32(s))
-      ffn_bwd_f32<CfgF32, CfgF32>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh), m(dx_perm),
+      ffn_bwd_f32<CfgF32, CfgF32DW>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh), m(dx_perm),
                                   m(dW1), m(db1), m(dW2), m(db2), pl, planned, 0.f, st);
     else
       ffn_bwd_f32<CfgF32Skinny, CfgF32>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
@@ -385,7 +385,7 @@ extern "C" int dmoe_expert_ffn_bwd_sgd(const dmoe_dims* dims, const int32_t* off
     auto c = [](const void* q) { return reinterpret_cast<const float*>(q); };
     auto m = [](void* q) { return reinterpret_cast<float*>(q); };
     if (use_fat_f32(s))
-      ffn_bwd_f32<CfgF32, CfgF32, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
+      ffn_bwd_f32<CfgF32, CfgF32DW, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),
                                         m(dx_perm), m(W1), m(b1), m(W2), m(b2), pl, false, lr, st);
     else
       ffn_bwd_f32<CfgF32Skinny, CfgF32, true>(s, offsets, c(x_perm), c(h), c(a), c(dy_perm), c(W1), c(W2), m(dh),

@@ -420,8 +420,9 @@ dispatch_bwd_kernel(const E* dxp, const int32_t* pos, const int32_t* idx, const 
   float wsum = 0.f;
   bool first = lane < nterm;
   for (int q = 0; q < nterm; ++q) {
-    const int cq = __shfl(mycol, q, 64);
-    const float wq = __shfl(myw, q, 64);
+    // q is the same in every lane: a register read, not an exchange through LDS
+    const int cq = __builtin_amdgcn_readlane(mycol, q);
+    const float wq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(myw), q));
     if (lane < nterm && cq == mycol) {
       if (q < lane) first = false;
       wsum += wq;
@@ -446,8 +447,8 @@ dispatch_bwd_kernel(const E* dxp, const int32_t* pos, const int32_t* idx, const 
 #pragma unroll
   for (int g = 0; g < GCR; ++g) {
     const int src = fm ? __builtin_ctzll(fm) : 0;
-    gcol[g] = g < ncol ? __shfl(mycol, src, 64) : 0;
-    gw[g] = g < ncol ? __shfl(wsum, src, 64) : 0.f;
+    gcol[g] = g < ncol ? __builtin_amdgcn_readlane(mycol, src) : 0;
+    gw[g] = g < ncol ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wsum), src)) : 0.f;
     fm &= fm ? fm - 1 : 0ull;
   }
   const int CPR = D / VEC;
