@@ -114,7 +114,14 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# The current stream's handle without the Stream object around it (2.8 us a call on the
+# host, of about 10 us per entry point); a torch without this accessor takes the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
+    if stream is None and _raw_stream is not None:
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
     s = torch.cuda.current_stream() if stream is None else stream
     return ctypes.c_void_p(s.cuda_stream)
 
