@@ -134,8 +134,10 @@ int dmoe_trace_end(void);
  * tie is recomputed with exact fp64 accumulation, so the selection equals the one
  * of the exact scores; the returned scores, g and w carry the (bounded) MFMA error.
  * fp32, and bf16 with d*M > 96: exact fp64 accumulation for every token.
- * Inputs are expected to be finite: with NaN or infinite scores the choice is
- * unspecified (every returned index is still a valid expert id) and w may be NaN.
+ * Inputs are expected to be finite.  A NaN score ranks below every other score of its
+ * dimension, so an expert with one is chosen only when fewer than k are left; otherwise
+ * the choice with NaN or infinite scores is unspecified (every returned index is still a
+ * valid expert id), and w may be NaN when such an expert is chosen.
  * Uses workspace: bf16 with d*M <= 96, and DMOE_FLAG_ALIVE_TOPK with either dtype
  * (the queue of tokens to recompute; ws must not be NULL, else DMOE_EINVAL);
  * otherwise no. */

@@ -28,9 +28,9 @@ struct GateArgs {
 //  * K1 = k+1 cells (k if k = N) are ranked, and the selection is kept only if their
 //    totals are separated by more than 2E, E = d (delta_max + amax 2^-23) with
 //    delta = gam * ab[c] the bound on the score's accumulation error, and if the nonzero
-//    scores span less than 2^25 in magnitude (beyond it an fp64 total of d fp32 values may
-//    round and the dominance argument no longer holds exactly).  Returns false (nothing
-//    written) otherwise;
+//    scores are finite and span less than 2^25 in magnitude (beyond it an fp64 total of d
+//    fp32 values may round and the dominance argument no longer holds exactly).  Returns
+//    false (nothing written) otherwise.  A NaN score is below every other one;
 //  * Eq. 1 weights over the chosen experts that are alive, from fp64 totals.
 // CAP: list capacity, at least K1 (the callers pick 5 when K1 <= 5, else KMAX + 1;
 // for ALIVE 7 when k <= 4, else KMAX + 3).
@@ -89,7 +89,9 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
       v = sw ? ov : v; f = sw ? of : f; uu = sw ? ou : uu;
     }
   };
-  if (amax > 0.f && !(amax <= amin * 33554432.f)) return false;   // span 2^25
+  // span 2^25; infinite scores (their totals may be NaN, which the lists cannot hold) are
+  // left to the exact path whatever the others are
+  if (!(amax < INFINITY) || (amax > 0.f && !(amax <= amin * 33554432.f))) return false;
   {
     // odometer over the rank digits r_0 .. r_{d-1} (last digit fastest), visiting only
     // the tuples with prod(r_i + 1) <= K1: a digit whose prefix product would exceed
@@ -547,7 +549,7 @@ __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const double* s
       for (int i = 0; i < DMAX; ++i)
         if (i < d) { tot += (double)(float)sc[i * M + u[i]]; uu |= u[i] << (8 * i); }
       const uint32_t l = !ALIVE || a.alive == nullptr || a.alive[f] != 0 ? 1u : 0u;
-      const uint64_t tt = ord64(tot + 0.0);                          // -0 and +0 are one value
+      const uint64_t tt = ord64(tot == tot ? tot + 0.0 : -INFINITY);  // -0 and +0 are one value
       const uint32_t n = ~(uint32_t)f;
       if (cell_gt(pl, pt, pn, l, tt, n) && cell_gt(l, tt, n, bl, bt, bn)) { bl = l; bt = tt; bn = n; bu = uu; }
 #pragma unroll
@@ -589,8 +591,8 @@ __device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples&
   const int M4 = (M + 3) & ~3;
   const int K1 = rank_k1<ALIVE>(a);
   const int L = min(K1, M);
-  // decision scores, their span, and safe contents for the rank slots (NaN scores leave
-  // slots unwritten: the choice is then unspecified but valid)
+  // decision scores (a NaN ranks with -inf, last), their span, and safe contents for the
+  // rank slots
   int ci[2], cu[2];
   float cv[2];
   float amax = 0.f, amin = 3.4e38f;
@@ -601,9 +603,9 @@ __device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples&
     cu[h] = c - ci[h] * M;
     cv[h] = 0.f;
     if (c < dM) {
-      cv[h] = (float)sc[c];
+      const float v = (float)sc[c], av = fabsf(v);
+      cv[h] = v == v ? v : -INFINITY;
       q.dec[ci[h] * M4 + cu[h]] = cv[h];
-      const float av = fabsf(cv[h]);
       if (av > 0.f) { amax = fmaxf(amax, av); amin = fminf(amin, av); }
     }
   }
@@ -675,7 +677,8 @@ __device__ __forceinline__ void select_wave(const GateArgs& a, const RankTuples&
         }
       }
       if (tk[h]) {
-        tv[h] = tot; tf[h] = flat; tu[h] = uu;
+        tv[h] = tot == tot ? tot : -INFINITY;                        // inf - inf
+        tf[h] = flat; tu[h] = uu;
         lv[h] = a.alive == nullptr || a.alive[flat] != 0;
       }
       q.tot[p] = tv[h];

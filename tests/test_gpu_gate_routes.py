@@ -107,3 +107,34 @@ def test_certified_route_matches_the_exact_one(T, D, d, M, k, p_alive, alive_fir
     assert float((out[0][3] - out[1][3]).abs().max()) <= lim
     assert float((out[0][2] - out[1][2]).abs().max()) <= d * lim
     assert float((out[0][1] - out[1][1]).abs().max()) <= 2 * d * lim + 1e-6
+
+
+@pytest.mark.parametrize("dtype,T,D,d,M,k,p_alive,alive_first", [
+    ("f32", 65, 64, 2, 6, 4, 1.0, False), ("f32", 40, 64, 3, 5, 8, 0.6, True), ("f32", 50, 128, 1, 100, 8, 0.9, False),
+    ("bf16", 77, 64, 2, 9, 4, 0.9, False), ("bf16", 130, 128, 2, 60, 8, 0.6, True),
+    ("bf16", 40000, 1024, 2, 16, 4, 0.9, False), ("bf16", 40000, 1024, 2, 32, 4, 0.6, True),   # certified
+])
+def test_non_finite_scores(dtype, T, D, d, M, k, p_alive, alive_first):
+    """Two gate columns whose weights are NaN: every token is routed among the others, with
+    finite weights.  Tokens with infinities or a NaN of their own: valid expert ids."""
+    gen = torch.Generator().manual_seed(T + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dM, N, n = d * M, M ** d, min(T, 2000)
+    x, Wg, bg = (torch.randn(*s, generator=gen) for s in ((T, D), (dM, D), (dM,)))
+    Wg *= D ** -0.5
+    alive = (torch.rand(N, generator=gen) < p_alive).to(torch.uint8)
+    Wg[1], Wg[(d - 1) * M + 2, 3] = float("nan"), float("nan")
+    x[5, 1], x[7, 1], x[9, 2], x[11, :] = float("inf"), float("nan"), -float("inf"), float("inf")
+    x, Wg, bg = x.to(dt), Wg.to(dt), bg.to(dt)
+    dims = abi.make_dims(T, D, 64, d, M, k, dtype, "relu", abi.DMOE_FLAG_ALIVE_TOPK if alive_first else 0)
+    idx, w, g, _ = gate(dims, x.cuda(), Wg.cuda(), bg.cuda(), alive.cuda(), T, k, dM)
+    assert int(idx.min()) >= 0 and int(idx.max()) < N
+    keep = torch.ones(T, dtype=torch.bool)
+    keep[[5, 7, 9, 11]] = False
+    assert bool(w[keep].isfinite().all()) and bool(g[keep].isfinite().all())
+    keep = keep[:n]
+    S = x[:n].double() @ Wg.double().t() + bg.double()      # NaN columns below every other
+    S = torch.where(S.isnan(), torch.full_like(S, -1e30), S)
+    _, ridx, rg, rw = reference(S[keep], torch.eye(dM), torch.zeros(dM), alive, d, M, k, alive_first)
+    assert torch.equal(idx[:n][keep], ridx)
+    assert float((w[:n][keep] - rw).abs().max()) <= 1e-4    # bf16 score bound of the certified route
