@@ -207,7 +207,7 @@ int dmoe_combine_bwd(const dmoe_dims* dims, const void* dy, const void* y_perm,
  *   dWg = ds^T x   [d*M, D]  (dtype of Wg),   dbg = sum_t ds  [d*M] (dtype of Wg)
  * The gate's share of dx (ds Wg) is added by dmoe_dispatch_bwd.
  *   x [T, D], idx [T, k], w [T, k], dw [T, k], alive [N] or NULL
- * outputs: dg [T, k] fp32, dWg, dbg (dbg may be NULL).  Uses workspace. */
+ * outputs: dg [T, k] fp32 (may alias dw or w), dWg, dbg (dbg may be NULL).  Uses workspace. */
 int dmoe_gate_topk_bwd(const dmoe_dims* dims, const void* x, const int32_t* idx,
                        const float* w, const float* dw, const uint8_t* alive, float* dg,
                        void* dWg, void* dbg, void* ws, void* stream);

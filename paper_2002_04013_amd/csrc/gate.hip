@@ -966,11 +966,14 @@ static size_t gate_mfma_lds_bytes(int dM, int kw) {
 // i*M + u_i for every dimension i; dWg = ds^T x, dbg = sum_t ds.  Two launches: one kernel
 // whose blocks either write dg and the bias gradient's partial sums (GD_TOK tokens each) or
 // multiply a token split by GB_BN columns of x into a partial dWg, and a reduction of the
-// partials in split order.  ds is never stored: a block expands the k terms per token and
-// dimension of the tokens of its next stage in LDS, column-major like an MFMA operand.  A
-// thread owns one token's entries of one dimension: it clears those it wrote two stages ago
-// and writes the new ones, so the expansion needs no barrier of its own.  bf16: ds as hi and
-// lo bf16 parts, both multiplied into the same fp32 accumulator (about 16 mantissa bits).
+// partials in split order.  Every block of the first launch reads w and dw, so when dg lies
+// over one of them the second launch writes it instead (the call is then 2.8 us longer at
+// k = 8: the tokens' loads and arithmetic once more).
+// ds is never stored: a block expands the k terms per token and dimension of the tokens of its
+// next stage in LDS, column-major like an MFMA operand.  A thread owns one token's entries of
+// one dimension: it clears those it wrote two stages ago and writes the new ones, so the
+// expansion needs no barrier of its own.  bf16: ds as hi and lo bf16 parts, both multiplied
+// into the same fp32 accumulator (about 16 mantissa bits).
 // Bound by latency: a stage's expansion, barrier and loads follow one another, two blocks to
 // a compute unit (T = 32768, D = 4096, 32 columns: 92 us for 268 MB, 2.9 TB/s).  Five
 // launches before (dg and dense ds; split offsets; a register-staged GEMM over ds in memory;
@@ -989,6 +992,7 @@ struct GateBwdArgs {
   float* dg; float* dbg_part; float* part;
   int T, D, d, M, k, dM;
   int gblk, nb, split;             // dg blocks; column blocks; tokens per split
+  int dg_late;                     // dg is written by the second launch
 };
 
 // The k terms of token t: dg and the grid indices (8 bits per dimension); zeros past `end`.
@@ -1037,7 +1041,8 @@ struct GateTerms {
   }
 };
 
-// dg of GD_TOK tokens, and their sums per gate column (rows in order, in two halves)
+// dg of GD_TOK tokens (unless it is left to the second launch), and their sums per gate column
+// (rows in order, in two halves)
 __device__ __forceinline__ void gate_dg_block(const GateBwdArgs& p, int blk, float* rows) {
   const int SR = p.dM + 1;
   const int t0 = blk * GD_TOK, nt = min(GD_TOK, p.T - t0);
@@ -1050,7 +1055,7 @@ __device__ __forceinline__ void gate_dg_block(const GateBwdArgs& p, int blk, flo
     v.load_alive(p);
     float* row = rows + threadIdx.x * SR;
     v.each(p, [&](int j, float g, uint32_t dig) {
-      p.dg[(int64_t)t * p.k + j] = g;
+      if (!p.dg_late) p.dg[(int64_t)t * p.k + j] = g;
       for (int i = 0; i < p.d; ++i) row[i * p.M + ((dig >> (8 * i)) & 0xff)] += g;
     });
   }
@@ -1241,13 +1246,16 @@ static size_t gate_bwd_lds_bytes(const Shape& s) {
   return mm > rows ? mm : rows;
 }
 
-// dWg = sum of the splits' partials in split order (4 values a thread); the blocks past
-// nred: dbg[c] = sum over the dg blocks of their partial column sums, thread i adding a
-// contiguous run of blocks, then a tree over the threads.
+// dWg = sum of the splits' partials in split order (4 values a thread); the ndg blocks past
+// nred: dg, a token a thread; the blocks past those: dbg[c] = sum over the dg blocks of their
+// partial column sums, thread i adding a contiguous run of blocks, then a tree over the
+// threads.
 template <typename E>
 __global__ void __launch_bounds__(256)
-gate_reduce_kernel(const float* part, int nsplit, int64_t n, E* dWg, int nred, const float* dbg_part, int nblk, int dM,
-                   E* dbg) {
+gate_reduce_kernel(GateBwdArgs p, int nsplit, int64_t n, E* dWg, int nred, int ndg, E* dbg) {
+  const float* part = p.part;
+  const float* dbg_part = p.dbg_part;
+  const int nblk = p.gblk, dM = p.dM;
   if ((int)blockIdx.x < nred) {
     const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (q >= n) return;
@@ -1261,7 +1269,15 @@ gate_reduce_kernel(const float* part, int nsplit, int64_t n, E* dWg, int nred, c
     dWg[q] = cvt<E>(s.x); dWg[q + 1] = cvt<E>(s.y); dWg[q + 2] = cvt<E>(s.z); dWg[q + 3] = cvt<E>(s.w);
     return;
   }
-  const int c = blockIdx.x - nred;
+  if ((int)blockIdx.x < nred + ndg) {
+    const int t = ((int)blockIdx.x - nred) * 256 + (int)threadIdx.x;
+    GateTerms v;
+    v.load(p, t, p.T);
+    v.load_alive(p);
+    if (t < p.T) v.each(p, [&](int j, float g, uint32_t) { p.dg[(int64_t)t * p.k + j] = g; });
+    return;
+  }
+  const int c = blockIdx.x - nred - ndg;
   const int per = (nblk + 255) / 256;
   const int b0 = threadIdx.x * per, b1 = min(nblk, b0 + per);
   float s = 0.f;
@@ -1347,7 +1363,12 @@ static int gate_bwd_impl(const Shape& s, const void* x, const int32_t* idx, cons
   unsigned char* base = reinterpret_cast<unsigned char*>(ws);
   GateBwdArgs p{x, idx, w, dw, alive, dg, nullptr, reinterpret_cast<float*>(base + L.part_off),
                 (int)s.T, (int)s.D, s.d, s.M, s.k, (int)s.dM,
-                (int)((s.T + GD_TOK - 1) / GD_TOK), (int)((s.D + GB_BN - 1) / GB_BN), (int)L.gsplit_tokens};
+                (int)((s.T + GD_TOK - 1) / GD_TOK), (int)((s.D + GB_BN - 1) / GB_BN), (int)L.gsplit_tokens, 0};
+  auto over = [&](const float* q) {
+    const uintptr_t a = (uintptr_t)dg, b = (uintptr_t)q, n = (uintptr_t)s.P * sizeof(float);
+    return a < b + n && b < a + n;
+  };
+  p.dg_late = over(w) || over(dw);
   // the bias gradient's per-block column sums use the forward pass's queue region
   // (calls on one stream do not overlap): ceil(T / 128) x dM floats <= 4 T bytes
   if (dbg) p.dbg_part = reinterpret_cast<float*>(base + L.gq_off);
@@ -1368,9 +1389,9 @@ static int gate_bwd_impl(const Shape& s, const void* x, const int32_t* idx, cons
     default: go(std::integral_constant<int, 4>{}); break;
   }
   const int64_t n = s.dM * s.D;                          // a multiple of 64
-  const int nred = (int)((n / 4 + 255) / 256);
-  DMOE_LAUNCH_NAMED("gate_reduce_kernel", gate_reduce_kernel<E>, dim3((unsigned)(nred + (dbg ? s.dM : 0))), dim3(256), 0,
-                    st, p.part, (int)L.gsplit, n, reinterpret_cast<E*>(dWg), nred, p.dbg_part, p.gblk, (int)s.dM,
+  const int nred = (int)((n / 4 + 255) / 256), ndg = p.dg_late ? (int)((s.T + 255) / 256) : 0;
+  DMOE_LAUNCH_NAMED("gate_reduce_kernel", gate_reduce_kernel<E>, dim3((unsigned)(nred + ndg + (dbg ? s.dM : 0))),
+                    dim3(256), 0, st, p, (int)L.gsplit, n, reinterpret_cast<E*>(dWg), nred, ndg,
                     reinterpret_cast<E*>(dbg));
   return launch_status();
 }

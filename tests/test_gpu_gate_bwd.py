@@ -1,7 +1,7 @@
 """The gate's backward at the edges of its tiles: token counts around a stage (64 bf16 or 32
 fp32 tokens), the 256-token groups, the dg blocks of 128 and the token splits; d_model with a
 half column block; gate columns at the edges of the 32-column blocks; chosen experts that
-share grid indices; dead experts.  Against fp64: dg within fp32 rounding, dWg and dbg within
+share grid indices; dead experts; dg written over an input.  Against fp64: dg within fp32 rounding, dWg and dbg within
 the stored type's rounding plus the error of fp32 sums of T terms (bf16: of terms carrying 16
 mantissa bits)."""
 import pytest
@@ -41,6 +41,12 @@ def test_gate_backward(dtype, T, D, d, M, k, p_alive):
     abi.dmoe_gate_topk_bwd(dims, x.to(dev), idx.to(dev), w.to(dev), dw.to(dev), alive.to(dev), dg, dWg2, None, ws)
     torch.cuda.synchronize()
     assert torch.equal(dWg, dWg2)
+    for which in (0, 1):                                 # dg written over w or over dw
+        wd = [w.to(dev), dw.to(dev)]
+        dWg3, dbg3 = torch.empty_like(dWg), torch.empty_like(dbg)
+        abi.dmoe_gate_topk_bwd(dims, x.to(dev), idx.to(dev), wd[0], wd[1], alive.to(dev), wd[which], dWg3, dbg3, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(wd[which], dg) and torch.equal(dWg, dWg3) and torch.equal(dbg, dbg3)
     wl = torch.where(alive[idx.long()] != 0, w, torch.zeros_like(w)).double()
     rdg = wl * (dw.double() - (wl * dw.double()).sum(1, keepdim=True))
     ds = torch.zeros(T, dM, dtype=torch.float64)
