@@ -2,8 +2,9 @@
 
 Exact route (fp64 matrix products, a wave per token selecting): gate columns at the edges
 of the 16-column tiles and of the 64 lanes, ragged token counts, tied scores and totals
-(small integers: every score is exact), scores of very different magnitude (every cell is
-then ranked), sparse alive sets with TopK among the alive experts.  The reference ranks
+(small integers: every score is exact), scores of very different magnitude and sparse alive
+sets with TopK among the alive experts (every cell is then ranked), there also with scores
+that rise along the grid and that are all equal.  The reference ranks
 every cell in fp64 by (alive first, total desc, flat index asc).
 
 Certified route (bf16 matrix products plus recomputation of the rejected tokens): sizes
@@ -59,6 +60,8 @@ EXACT = [
     ("bf16", 130, 512, 2, 64, 8, "ties", 0.9, False), ("bf16", 63, 64, 2, 49, 8, "normal", 0.02, True),
     ("bf16", 200, 320, 3, 16, 4, "ties", 0.9, True), ("bf16", 77, 64, 2, 8, 3, "span", 0.9, False),
     ("bf16", 300, 128, 4, 8, 8, "ties", 0.9, False), ("bf16", 50, 2112, 3, 25, 8, "normal", 0.5, True),
+    ("f32", 20, 64, 2, 40, 8, "rising", 0.2, True), ("bf16", 20, 64, 3, 25, 8, "rising", 0.003, True),
+    ("f32", 20, 64, 2, 30, 8, "equal", 0.1, True), ("f32", 20, 64, 2, 64, 8, "ties", 0.05, True),
 ]
 
 
@@ -74,6 +77,10 @@ def test_exact_route_matches_the_definition(dtype, T, D, d, M, k, inputs, p_aliv
         x = torch.randint(-1, 2, (T, D), generator=gen).float()
         Wg = torch.randint(-1, 2, (dM, D), generator=gen).float() * (torch.rand(dM, D, generator=gen) < 8.0 / D)
         bg = torch.randint(-1, 2, (dM,), generator=gen).float()
+        if inputs in ("rising", "equal"):  # each cell beats those before it; all scores 0
+            Wg.zero_()
+            bg = torch.arange(M).float().repeat(d) if inputs == "rising" else torch.zeros(dM)
+            bg[:M * (d - 1)] *= 8.0
         if inputs == "span":              # one column of each dimension 2^30 times the others
             Wg[::M] *= 2.0 ** 30
     x, Wg, bg = x.to(dt).cuda(), Wg.to(dt).cuda(), bg.to(dt).cuda()
