@@ -528,7 +528,7 @@ __device__ __forceinline__ uint32_t shift_up(uint32_t v) {
 // totals adding the d decision scores in fp64 in dimension order, ranked (alive first when
 // ALIVE, total desc, flat asc).  The k best so far lie in lanes 0 .. k - 1, best first; the
 // few cells of a step that beat the k-th (a ballot) are inserted one by one, at their count of
-// better entries.  A step's alive flags are loaded RA_U steps at a time.
+// better entries; the first 64 cells, most of which would be, are ranked by counting.  A step's alive flags are loaded RA_U steps at a time.
 // Reached where a ranking of the likely cells does not decide: fewer than k alive among them,
 // or totals that may round.  Bound by the latency of a step's and of an insertion's chain.  The
 // gate call with a fifth of the experts alive, D = 512, fp32, as k rounds over every cell /
@@ -553,6 +553,12 @@ __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const float* de
   uint64_t et = 0ull;
   uint32_t kl = 0u, kn = 0u;                                         // the k-th entry
   uint64_t kt = 0ull;
+  auto kth = [&]() {
+    kl = (uint32_t)__builtin_amdgcn_readlane((int)el, k - 1);
+    kn = (uint32_t)__builtin_amdgcn_readlane((int)en, k - 1);
+    kt = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(et >> 32), k - 1) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)et, k - 1);
+  };
   for (int f0 = 0; f0 < N; f0 += 64 * RA_U) {
     uint32_t live[RA_U];
     uint64_t tt[RA_U];
@@ -579,14 +585,36 @@ __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const float* de
     for (int q = 0; q < RA_U; ++q) {
       const int f = f0 + 64 * q + lane;
       const uint32_t n = ~(uint32_t)f, l = live[q] != 0u ? 1u : 0u;
+      auto take = [&](int s, uint32_t& cl, uint64_t& ct, uint32_t& cn) {     // the cell of lane s
+        cl = (uint32_t)__builtin_amdgcn_readlane((int)l, s);
+        cn = (uint32_t)__builtin_amdgcn_readlane((int)n, s);
+        ct = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(tt[q] >> 32), s) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tt[q], s);
+      };
+      if (q == 0 && f0 == 0) {                                       // the first cells: by counting
+        int better = f < N ? 0 : 64;
+        for (int s = 0; s < min(N, 64); ++s) {
+          uint32_t cl, cn;
+          uint64_t ct;
+          take(s, cl, ct, cn);
+          better += cell_gt(cl, ct, cn, l, tt[q], n);
+        }
+        for (int j = 0; j < min(N, k); ++j) {
+          uint32_t cl, cn;
+          uint64_t ct;
+          take(__builtin_ctzll(__ballot(better == j)), cl, ct, cn);
+          if (lane == j) { el = cl; et = ct; en = cn; }
+        }
+        kth();
+        continue;
+      }
       uint64_t in = __ballot(f < N && cell_gt(l, tt[q], n, kl, kt, kn));
       while (in) {
         const int s = __builtin_ctzll(in);
         in &= in - 1;
-        const uint32_t cl = (uint32_t)__builtin_amdgcn_readlane((int)l, s);
-        const uint32_t cn = (uint32_t)__builtin_amdgcn_readlane((int)n, s);
-        const uint64_t ct = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(tt[q] >> 32), s) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tt[q], s);
+        uint32_t cl, cn;
+        uint64_t ct;
+        take(s, cl, ct, cn);
         if (!cell_gt(cl, ct, cn, kl, kt, kn)) continue;              // a cell of this step took its place
         const int pos = __popcll(__ballot(lane < k && cell_gt(el, et, en, cl, ct, cn)));
         const uint32_t pl = shift_up(el), pn = shift_up(en);
@@ -594,10 +622,7 @@ __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const float* de
         el = lane == pos ? cl : lane > pos ? pl : el;
         et = lane == pos ? ct : lane > pos ? pt : et;
         en = lane == pos ? cn : lane > pos ? pn : en;
-        kl = (uint32_t)__builtin_amdgcn_readlane((int)el, k - 1);
-        kn = (uint32_t)__builtin_amdgcn_readlane((int)en, k - 1);
-        kt = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(et >> 32), k - 1) << 32) |
-             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)et, k - 1);
+        kth();
       }
     }
   }
