@@ -34,6 +34,7 @@ struct GateArgs {
 //  * Eq. 1 weights over the chosen experts that are alive, from fp64 totals.
 // CAP: list capacity, at least K1 (the callers pick 5 when K1 <= 5, else KMAX + 1;
 // for ALIVE 7 when k <= 4, else KMAX + 3).
+// EXACT: the scores are exact (ab is not read), E covers their rounding alone.
 // ALIVE (TopK among the alive experts): the K1 = min(N, CAP) best cells are
 // ranked the same way; walking them in order, the first k alive ones are the k best
 // alive experts of the whole grid as soon as the k-th of them lies within those K1 (a
@@ -43,7 +44,7 @@ struct GateArgs {
 // nothing is written (the token goes to the exact alive-first path).
 // One lane per token is the form with the least work per token; the exact kernels below
 // select with a wave per token, which has the lower latency.
-template <int CAP, bool ALIVE>
+template <int CAP, bool ALIVE, bool EXACT>
 __device__ __forceinline__ bool select_token_cap(const double* s64, const float* ab, const uint8_t* alive, int d,
                                                  int M, int k, int N, float gam, int32_t* idx_out, float* w_out,
                                                  float* g_out) {
@@ -62,7 +63,7 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
         int id = u;
         const float av = fabsf(v);
         if (av > 0.f) { amax = fmaxf(amax, av); amin = fminf(amin, av); }
-        dmax = fmaxf(dmax, gam * ab[i * M + u]);
+        if constexpr (!EXACT) dmax = fmaxf(dmax, gam * ab[i * M + u]);
 #pragma unroll
         for (int p = 0; p < CAP; ++p) {
           const bool sw = v > lv[i][p];
@@ -216,15 +217,15 @@ __device__ __forceinline__ bool select_token_cap(const double* s64, const float*
   return true;
 }
 
-template <bool ALIVE>
+template <bool ALIVE, bool EXACT = false>
 __device__ __forceinline__ bool select_token(const double* s64, const float* ab, const uint8_t* alive, int d, int M,
                                              int k, int N, float gam, int32_t* idx_out, float* w_out, float* g_out) {
   if constexpr (ALIVE) {      // k + 3 cells ranked: up to two dead ones ahead of the k-th alive
-    if (k <= 4) return select_token_cap<7, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
-    return select_token_cap<KMAX + 3, true>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+    if (k <= 4) return select_token_cap<7, true, EXACT>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+    return select_token_cap<KMAX + 3, true, EXACT>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
   }
-  if (k + 1 <= 5) return select_token_cap<5, false>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
-  return select_token_cap<KMAX + 1, false>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+  if (k + 1 <= 5) return select_token_cap<5, false, EXACT>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
+  return select_token_cap<KMAX + 1, false, EXACT>(s64, ab, alive, d, M, k, N, gam, idx_out, w_out, g_out);
 }
 
 // ---------------------------------------------------------------- bf16: MFMA scores + certificate
@@ -932,23 +933,29 @@ constexpr int GF_P = 4;           // chunks per step
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-template <typename E, bool ALIVE>
-__global__ void __launch_bounds__(1024) gate_topk_f64(GateArgs a, int CTN) {
+//
+// LANE: one lane per token selects (select_token; its few undecided tokens go to select_wave),
+// in blocks of two token tiles and a wave per tile of columns and tokens.  The least work per
+// token, for calls of many tokens with few candidates (gate_f64_lane).
+template <typename E, bool ALIVE, bool LANE>
+__global__ void __launch_bounds__(LANE ? 512 : 1024) gate_topk_f64(GateArgs a, int CTN) {
   extern __shared__ __align__(16) unsigned char sm[];
   constexpr int VEC = 16 / sizeof(E), CHUNK = 4 * VEC;
   const int dM = a.dM, SLD = dM + 1;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int NWV = blockDim.x >> 6, S = NWV / CTN;
-  double* s64 = reinterpret_cast<double*>(sm);                                   // [GF_TOK][SLD]
+  constexpr int TOK = LANE ? 2 * GF_TOK : GF_TOK;
+  const int NWV = blockDim.x >> 6, S = LANE ? 1 : NWV / CTN;
+  double* s64 = reinterpret_cast<double*>(sm);                                   // [TOK][SLD]
   // the waves' partial sums, and in their place afterwards the waves' selection scratch
-  double (*part)[GF_TOK][17] = reinterpret_cast<double (*)[GF_TOK][17]>(s64 + GF_TOK * SLD);
-  SelectScratch& scratch = reinterpret_cast<SelectScratch*>(s64 + GF_TOK * SLD)[wv];
-  const int t0 = blockIdx.x * GF_TOK;
+  double (*part)[GF_TOK][17] = reinterpret_cast<double (*)[GF_TOK][17]>(s64 + TOK * SLD);
+  SelectScratch& scratch = reinterpret_cast<SelectScratch*>(s64 + TOK * SLD)[wv];
+  const int t0 = blockIdx.x * TOK;
   const int r16 = lane & 15, g = lane >> 4;
-  const int ct = wv % CTN, sl = wv / CTN;
+  const int ct = wv % CTN, sl = LANE ? 0 : wv / CTN;
+  const int row = LANE ? wv / CTN * GF_TOK + r16 : r16;
   const RankTuples tup = rank_tuples<ALIVE>(a);
-  const E* xr = reinterpret_cast<const E*>(a.x) + (int64_t)min(t0 + r16, a.T - 1) * a.D + g * VEC;
+  const E* xr = reinterpret_cast<const E*>(a.x) + (int64_t)min(t0 + row, a.T - 1) * a.D + g * VEC;
   const E* wr = reinterpret_cast<const E*>(a.Wg) + (int64_t)min(16 * ct + r16, dM - 1) * a.D + g * VEC;
   const int nc = a.D / CHUNK;                          // D is a multiple of 64
   const int c0 = nc * sl / S, c1 = nc * (sl + 1) / S;  // this wave's chunks
@@ -981,19 +988,32 @@ __global__ void __launch_bounds__(1024) gate_topk_f64(GateArgs a, int CTN) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) part[wv][r16][4 * v + g] = acc[v];
   __syncthreads();
-  const int nt = min(GF_TOK, a.T - t0);
+  const int nt = min(TOK, a.T - t0);
   {
     const E* bg = reinterpret_cast<const E*>(a.bg);
-    const int tok = threadIdx.x & 15;
-    for (int c = threadIdx.x >> 4; c < dM; c += NWV * 4) {
+    const int tok = threadIdx.x & (TOK - 1), half = LANE ? tok / GF_TOK : 0;
+    for (int c = threadIdx.x / TOK; c < dM; c += NWV * 64 / TOK) {
       double v = bg ? (double)ldf(bg + c) : 0.0;
-      for (int q = 0; q < S; ++q) v += part[(c >> 4) + CTN * q][tok][c & 15];
+      for (int q = 0; q < S; ++q) v += part[(c >> 4) + CTN * (q + half)][tok & (GF_TOK - 1)][c & 15];
       s64[tok * SLD + c] = v;
       if (a.scores && tok < nt) a.scores[(int64_t)(t0 + tok) * dM + c] = (float)v;
     }
   }
   __syncthreads();
-  for (int tt = wv; tt < nt; tt += NWV) select_wave<ALIVE>(a, tup, s64 + tt * SLD, scratch, t0 + tt);
+  if constexpr (LANE) {
+    if (wv > 0) return;
+    bool ok = true;
+    if (lane < nt)
+      ok = select_token<false, true>(s64 + lane * SLD, nullptr, a.alive, a.d, a.M, a.k, a.N, 0.f,
+                               a.idx + (int64_t)(t0 + lane) * a.k, a.w + (int64_t)(t0 + lane) * a.k,
+                               a.g ? a.g + (int64_t)(t0 + lane) * a.k : nullptr);
+    for (uint64_t bad = __ballot(!ok); bad; bad &= bad - 1) {
+      const int tt = __builtin_ctzll(bad);
+      select_wave<false>(a, tup, s64 + tt * SLD, scratch, t0 + tt);
+    }
+  } else {
+    for (int tt = wv; tt < nt; tt += NWV) select_wave<ALIVE>(a, tup, s64 + tt * SLD, scratch, t0 + tt);
+  }
 }
 
 // 16-column tiles of the gate columns (at most 8), and waves per block: every tile over as
@@ -1003,14 +1023,27 @@ __global__ void __launch_bounds__(1024) gate_topk_f64(GateArgs a, int CTN) {
 // columns 94 / 69 us; T = 200, D = 8192, 96 columns 194 / 140 us; T = 1024, 15625 experts, a
 // fifth of them alive, k = 8 340 / 192 us; T = 4096, D = 1024, 64 columns 23 / 21 us.
 static int gate_f64_tiles(const Shape& s) { return (int)((s.dM + 15) / 16); }
+// A lane per token selects where the tokens are many, so that the work per token counts and
+// not its latency, and the selection is the larger part of the call (narrow d_model, few
+// columns, small k).  Measured in us, a wave per token / a lane per token: T = 65536, D = 64,
+// 32 columns, k = 4 64 / 33; k = 8 71 / 57; 64 columns, k = 4 73 / 57; 4 dimensions of 8
+// 71 / 47; D = 1024, 32 columns 174 / 144, 64 columns 271 / 277; T = 16384, D = 64, 32 columns,
+// k = 4 19 / 16, 4 dimensions of 8 21 / 25, k = 8 21 / 33; T = 8192 11 / 15.
+static bool gate_f64_lane(const Shape& s) {
+  if (s.dtype != DMOE_F32 || (s.flags & DMOE_FLAG_ALIVE_TOPK) || s.D > 1024) return false;
+  if (s.dM <= 32 && s.k <= 4) return s.T >= (s.d <= 2 ? 16384 : 32768);
+  return (s.dM <= 32 || (s.dM <= 64 && s.k <= 4)) && s.D <= 512 && s.T >= 65536;
+}
+static int gate_f64_tokens(const Shape& s) { return gate_f64_lane(s) ? 2 * GF_TOK : GF_TOK; }
 static int gate_f64_waves(const Shape& s) {
   const int n = gate_f64_tiles(s);
+  if (gate_f64_lane(s)) return n * 2;
   return n * (((s.T + GF_TOK - 1) / GF_TOK <= 256 ? 16 : 8) / n);
 }
 static size_t gate_f64_lds_bytes(const Shape& s) {
   static_assert(GF_TOK % 2 == 0 && alignof(SelectScratch) <= 16, "s64 rows end on 16 bytes");
   const size_t part = GF_TOK * 17 * sizeof(double);
-  return GF_TOK * (s.dM + 1) * sizeof(double) + gate_f64_waves(s) * std::max(part, sizeof(SelectScratch));
+  return gate_f64_tokens(s) * (s.dM + 1) * sizeof(double) + gate_f64_waves(s) * std::max(part, sizeof(SelectScratch));
 }
 // bf16 gates with at most 96 columns: exact scores for every token, or the certified route
 // (three launches: queue clearing, scoring, recomputation).  In microseconds the exact route
@@ -1384,10 +1417,13 @@ extern "C" int dmoe_gate_topk(const dmoe_dims* dims, const void* x, const void* 
   }
   if (!mfma || (s.flags & DMOE_FLAG_GATE_EXACT) || gate_f64_pays(s)) {
     // exact fp64 scores for every token
-    const dim3 grid((unsigned)((s.T + GF_TOK - 1) / GF_TOK));
+    const int tok = gate_f64_tokens(s);
+    const dim3 grid((unsigned)((s.T + tok - 1) / tok));
     auto go = [&](auto EK) {
       using E = typename decltype(EK)::type;
-      auto kern = alive_first ? gate_topk_f64<E, true> : gate_topk_f64<E, false>;
+      auto kern = alive_first ? gate_topk_f64<E, true, false> : gate_topk_f64<E, false, false>;
+      if constexpr (sizeof(E) == 4)
+        if (gate_f64_lane(s)) kern = gate_topk_f64<E, false, true>;
       DMOE_LAUNCH_NAMED("gate_topk_f64", kern, grid, dim3(64 * gate_f64_waves(s)), gate_f64_lds_bytes(s), st, a,
                         gate_f64_tiles(s));
     };
