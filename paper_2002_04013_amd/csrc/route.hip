@@ -164,6 +164,7 @@ __device__ __forceinline__ int scan_lds(int* cnt, int N, int* part) {
   return total;
 }
 
+constexpr int FOLD_U = 8;                 // histograms loaded at once
 // FOLD: the block's starting rows come from the histograms of all nb blocks (step 2 here;
 // block 0 writes counts and offsets); else from block_hist, already scanned, and offsets.
 template <bool FOLD>
@@ -176,11 +177,25 @@ dispatch_scatter(const int32_t* idx, const uint8_t* alive, int P, int N, int k, 
     int* before = base + N;
     for (int e = threadIdx.x; e < N; e += RT_NT) {
       int tot = 0, mine = 0;
-#pragma unroll 8
-      for (int b = 0; b < nb; ++b) {
-        const int v = block_hist[(int64_t)b * N + e];
+      const int32_t* h = block_hist + e;
+      auto add = [&](int v, int b) {
         tot += v;
         mine += b < (int)blockIdx.x ? v : 0;
+      };
+      int b = 0;
+      for (; b + FOLD_U <= nb; b += FOLD_U) {
+        int v[FOLD_U];
+#pragma unroll
+        for (int u = 0; u < FOLD_U; ++u) v[u] = h[(int64_t)(b + u) * N];
+#pragma unroll
+        for (int u = 0; u < FOLD_U; ++u) add(v[u], b + u);
+      }
+      if (b < nb) {                                      // the remainder at once as well
+        int v[FOLD_U];
+#pragma unroll
+        for (int u = 0; u < FOLD_U; ++u) v[u] = h[(int64_t)min(b + u, nb - 1) * N];
+#pragma unroll
+        for (int u = 0; u < FOLD_U; ++u) add(b + u < nb ? v[u] : 0, b + u);
       }
       base[e] = tot;
       before[e] = mine;
@@ -295,8 +310,12 @@ dispatch_small(const int32_t* idx, const uint8_t* alive, int P, int N, int k, in
 constexpr int64_t SMALL_EXPERTS = 8192;
 // the rows step 4 writes when one block may do it too
 constexpr int64_t SMALL_ROW_BYTES = 128 * 1024;
-// steps 2 and 3 in one launch up to this many histogram entries (read by every block)
-constexpr int64_t FOLD_ENTRIES = 32768, FOLD_EXPERTS = 4096;
+// steps 2 and 3 in one launch up to this many histogram entries (read by every block), and
+// histograms (a thread adds an expert's one after another; with few experts few threads do).
+// Call in us, four launches / two: 131072 pairs over 4 experts 20 / 17, over 64 21 / 17; 262144
+// over 4 24 / 26, over 16 25 / 25; 1048576 over 4 65 / 81, over 16 70 / 79; 5000 over 2916
+// experts 23 / 21, over 4096 25 / 24 (35 with the remainder of the eight loaded one by one).
+constexpr int64_t FOLD_ENTRIES = 32768, FOLD_EXPERTS = 4096, FOLD_BLOCKS = 192;
 
 // y[t] = sum_j w[t,j] y_perm[pos[t,j]]; one wave per token (KM >= k slots held in
 // registers, each chunk's row loads issued before they are added in slot order).
@@ -524,7 +543,7 @@ extern "C" int dmoe_dispatch(const dmoe_dims* dims, const void* x, const int32_t
   } else {
     if (nb > 0)
       DMOE_LAUNCH(dispatch_hist, dim3(nb), dim3(RT_NT), N * sizeof(int), st, idx, alive, P, N, bh);
-    if (nb > 0 && (int64_t)nb * N <= FOLD_ENTRIES && N <= FOLD_EXPERTS) {
+    if (nb > 0 && nb <= FOLD_BLOCKS && (int64_t)nb * N <= FOLD_ENTRIES && N <= FOLD_EXPERTS) {
       DMOE_LAUNCH_NAMED("dispatch_scatter", dispatch_scatter<true>, dim3(nb), dim3(RT_NT), 2 * N * sizeof(int), st, idx,
                         alive, P, N, s.k, nb, bh, counts, offsets, pos, row_token);
     } else {

@@ -15,6 +15,7 @@ CASES = [
     (63, 1, 2, 4, 64, 0.9, False), (13, 5, 3, 5, 128, 0.9, True), (341, 3, 1, 128, 192, 0.8, False),
     (1023, 1, 2, 64, 64, 0.9, False), (205, 5, 2, 64, 64, 1.0, True), (512, 4, 3, 20, 256, 0.9, False),
     (2049, 1, 2, 4, 64, 0.9, False), (1025, 2, 1, 90, 64, 0.0, False), (4096, 4, 2, 32, 64, 0.9, False),
+    (98305, 2, 1, 4, 64, 0.9, False), (98304, 2, 2, 3, 64, 0.9, False), (1250, 4, 2, 64, 64, 0.9, False),
     (700, 3, 2, 64, 64, 0.9, True), (4099, 8, 2, 31, 64, 0.95, False), (5000, 8, 2, 64, 64, 0.9, False),
     (200, 8, 3, 25, 64, 0.9, False), (33, 2, 3, 25, 64, 0.9, False), (100, 4, 2, 64, 64, 0.9, False),
 ]
