@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdio>
+#include <utility>
 
 #include "common.hpp"
 #include "gemm.hpp"
@@ -307,43 +308,85 @@ struct G2DWShort { static constexpr int BM = 256, BN = 256, WM = 4, WN = 2, ST =
 // weight gradients: 64-deep k-steps from an average of 96 rows per expert on
 static bool deep_wgrad(const Shape& s) { return s.P >= (int64_t)96 * s.N; }
 
-// The row-grouped tile shape for an output of n columns and a contraction over K, from the
-// average number of rows per expert r = P / N and the tile counts it gives.
-//   * r < 24 (weight streaming): G2Skinny; G2Narrow when the weights that can be touched are
-//     under 512 MiB, where a call is a few tiles per unit and their latency counts.
-//     Measured, up and down projection in us: 4 experts of 1024 x 4096 touched 18.7 + 39.0 ->
-//     14.8 + 29.5, 32 experts 57.9 + 61.1 -> 51.3 + 54.4, 55 experts 94.9 + 112.1 -> 84.4 +
-//     91.5, but 256 experts 241 -> 256 (down), 1024 experts of 16 rows 1680 -> 1770.
-//   * G2Mid, or G2Fat where its rounds over the units cost less: a round of G2Fat tiles (one
-//     block to a unit) takes about 1.65 rounds of G2Mid tiles (two to a unit).  Measured, up
-//     and down in us, G2Skinny / G2Mid / G2Fat: 16 experts of 100 rows 60 + 51 / 33 + 62 /
-//     38 + 87; 25 experts of 82 rows (D = 2048) 144 + 152 / 104 + 104 / 126 + 125; 25 of 324
-//     rows (D = 960, H = 3008) - / 110 + 101 / 124 + 84; 64 of 256 rows - / 283 + 229 /
-//     253 + 274; 16 of 2048 rows (D = 512) - / 182 + 106 / 142 + 86.
-//   * fewer G2Mid tiles than compute units (narrow outputs of few experts): smaller tiles.
-//     G2Skinny / G2Narrow / G2Mid64 / G2Mid / G2Fat, down projection of 16 experts in us:
-//     32 rows 45 / 31 / 40 / 54 / 73; 64 rows 46 / 45 / 43 / 56 / 77; 100 rows 51 / 49 / 46 /
-//     62 / 87; 150 rows 92 / 70 / 60 / 64 / 93.  So G2Narrow below 48 rows, else G2Mid64.
+// The row-grouped tile shape for an output of n columns: row_tile_line's; from 24 rows per
+// expert on the lowest estimate's, below, where the line's is 10% above it, and the outer shape
+// for the rows (G2Skinny below 96 per expert, else G2Fat) where its estimate is no higher.
+//
+// A shape's time is its rounds over the units, R (a + K/64 (b + c rho)) with rho the 32-row
+// blocks a tile holds, and what it streams, w / u + (v - w) / v0 with w the weights of the
+// experts with rows and v the weights every m-tile streams (MB), the larger of the two with a
+// soft corner, plus a start.  m-tiles of an expert: rows spread by sqrt(r) and 5%, as routing
+// by a fresh gate spreads them.  The coefficients (us) are a least-squares fit to the
+// launches of 1196 layers: 2 to 1024 experts, 4 to 4096 rows each, five (d_model, hidden) from
+// 256 x 4096 to 2048 x 2048; up, down and their data gradients, each in every shape.  Over those
+// 4784 launches the choice is 2% above the best shape and 20% below the outer shapes alone
+// (geometric means), and more than 3% above the latter in 119; the line rule alone was 6.6%
+// above the best and slower than the outer shapes in 459, most where experts fill one or two
+// G2Fat tiles.  Measured in us, G2Skinny / G2Narrow / G2Mid64 / G2Mid / G2Fat:
+//   256 experts, n = 1024, K = 4096, r = 160: 916 / 969 / 679 / 804 / 489
+//   1024 experts, n = 2048, K = 2048, r = 80: 2230 / 2571 / 3154 / 2010 / 1982
+//   16 experts, n = 1024, K = 4096, r = 80: 47 / 49 / 42 / 61 / 81; r = 1024: 368 / 356 / 243 /
+//   206 / 143
+//   2 experts, n = 1024, K = 512, r = 512: 15 / 12 / 14 / 14 / 33
 enum RowTile { RT_SKINNY, RT_NARROW, RT_MID64, RT_MID, RT_FAT };
-static RowTile row_tile(const Shape& s, int64_t n, int64_t K) {
-  const double act = (double)std::min<int64_t>(s.N, s.P), r = (double)s.P / (double)s.N;
-  if (r < 24.0) return act * (double)n * (double)K * 2.0 < 536870912.0 ? RT_NARROW : RT_SKINNY;
-  const int cus = device_cus();
-  auto tiles = [&](int BM, int BN) { return act * std::max(1.0, r / BM + 0.5) * (double)((n + BN - 1) / BN); };
-  auto rounds = [&](double t, int per_cu) { return std::ceil(t / (double)(cus * per_cu)); };
-  const double mid = tiles(G2Mid::TMR, G2Mid::BN);
-  if (mid < cus) return r < 48.0 ? RT_NARROW : RT_MID64;
-  return 1.65 * rounds(tiles(G2Fat::TMR, G2Fat::BN), 1) <= rounds(mid, 2) ? RT_FAT : RT_MID;
-}
-// its tile height, which depends on n alone (every shape of r < 24 is 32 rows high)
-static int row_tile_rows(const Shape& s, int64_t n) {
-  switch (row_tile(s, n, 1)) {
-    case RT_MID64: return G2Mid64::TMR;
-    case RT_MID: return G2Mid::TMR;
-    case RT_FAT: return G2Fat::TMR;
-    default: return G2Skinny::TMR;
+struct RowCost { int rows, cols, per_cu; double a, b, c, u, v0, start; };
+constexpr RowCost ROW_COST[5] = {
+    {G2Skinny::TMR, G2Skinny::BN, 1, 5.14, 0.372, 0.130, 5.47, 20.1, 4.57},
+    {G2Narrow::TMR, G2Narrow::BN, 2, 3.99, 0.279, 0.068, 5.37, 15.3, 3.55},
+    {G2Mid64::TMR, G2Mid64::BN, 2, 6.65, 0.383, 0.074, 5.11, 11.0, 2.84},
+    {G2Mid::TMR, G2Mid::BN, 2, 9.85, 0.380, 0.063, 4.64, 5.98, 0.16},
+    {G2Fat::TMR, G2Fat::BN, 1, 13.7, 0.495, 0.138, 4.45, 3.25, 1.76},
+};
+static double row_cost(const RowCost& q, double act, double r, double n, double K, double cus) {
+  double mt = r / q.rows + 0.5;                              // m-tiles of an expert with rows
+  if (r < 8.0 * q.rows) {
+    const double sd = std::sqrt(r + 0.0025 * r * r);
+    mt = 1.0;
+    for (double at = q.rows; at < r + 2.0 * sd; at += q.rows)
+      mt += std::min(1.0, std::max(0.0, 0.5 + (r - at) / (4.0 * sd)));
   }
+  const double tiles = act * mt * std::ceil(n / q.cols);
+  const double rounds = std::max(1.0, std::ceil(tiles / (cus * q.per_cu) - 0.06));
+  const double w = act * n * K * 2e-6;
+  const double x = rounds * (q.a + K / 64.0 * (q.b + q.c * r / mt / 32.0));
+  const double y = w / q.u + w * (mt - 1.0) / q.v0;
+  return std::sqrt(std::sqrt(x * x * x * x + y * y * y * y)) + q.start;
 }
+// By lines on the rows per expert, the weights touched and the tile counts:
+//   * r < 24 (weight streaming): G2Skinny; G2Narrow when the weights that can be touched are
+//     under 512 MiB, where a call is a few tiles per unit and their latency counts (up and down
+//     projection in us: 4 experts of 1024 x 4096 touched 18.7 + 39.0 -> 14.8 + 29.5, 55 experts
+//     94.9 + 112.1 -> 84.4 + 91.5, but 256 experts 241 -> 256, down).
+//   * G2Mid, or G2Fat where its rounds over the units cost less: a round of G2Fat tiles (one
+//     block to a unit) takes about 1.65 rounds of G2Mid tiles (two to a unit).
+//   * fewer G2Mid tiles than compute units (narrow outputs of few experts): G2Narrow below 48
+//     rows, else G2Mid64 (down projection of 16 experts in us, in the order above: 32 rows
+//     45 / 31 / 40 / 54 / 73; 64 rows 46 / 45 / 43 / 56 / 77; 150 rows 92 / 70 / 60 / 64 / 93).
+static RowTile row_tile_line(double act, double r, double n, double K, double cus) {
+  if (r < 24.0) return act * n * K * 2.0 < 536870912.0 ? RT_NARROW : RT_SKINNY;
+  auto rounds = [&](const RowCost& q) {
+    const double t = act * std::max(1.0, r / q.rows + 0.5) * std::ceil(n / q.cols);
+    return std::pair<double, double>(t, std::ceil(t / (cus * q.per_cu)));
+  };
+  const auto mid = rounds(ROW_COST[RT_MID]);
+  if (mid.first < cus) return r < 48.0 ? RT_NARROW : RT_MID64;
+  return 1.65 * rounds(ROW_COST[RT_FAT]).second <= mid.second ? RT_FAT : RT_MID;
+}
+// The choice depends on n alone within a layer (a plan's tile height is shared by every GEMM
+// of an output width): K is taken as the other of D and H.
+static RowTile row_tile(const Shape& s, int64_t n) {
+  const double act = (double)std::min<int64_t>(s.N, s.P), r = (double)s.P / act;
+  const double K = (double)(n == s.H ? s.D : s.H), cus = (double)device_cus();
+  int pick = row_tile_line(act, (double)s.P / (double)s.N, (double)n, K, cus);
+  if (s.P < 24 * s.N) return (RowTile)pick;
+  double t[5];
+  for (int i = 0; i < 5; ++i) t[i] = row_cost(ROW_COST[i], act, r, (double)n, K, cus);
+  const int best = (int)(std::min_element(t, t + 5) - t);
+  const int outer = s.P >= 96 * s.N ? RT_FAT : RT_SKINNY;
+  if (t[pick] > 1.1 * t[best]) pick = best;
+  return (RowTile)(t[outer] <= t[pick] ? outer : pick);
+}
+static int row_tile_rows(const Shape& s, int64_t n) { return ROW_COST[row_tile(s, n)].rows; }
 
 // One row-grouped GEMM in the tile shape row_tile picks: p.tscale and the grid are set here.
 template <bool BT, int EPI>
@@ -355,7 +398,7 @@ static void run_gemm2_rows(const Shape& s, GemmArgs<bf16> p, hipStream_t st) {
     p.tscale = nt;
     run_gemm2<GROUP_M, false, BT, EPI, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
   };
-  switch (row_tile(s, p.N, p.K)) {
+  switch (row_tile(s, p.N)) {
     case RT_SKINNY: go(G2Skinny{}); break;
     case RT_NARROW: go(G2Narrow{}); break;
     case RT_MID64: go(G2Mid64{}); break;

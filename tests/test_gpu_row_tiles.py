@@ -4,6 +4,8 @@ counts either side of the 32-, 64-, 128- and 288-row tiles, widths that are no m
 tile, and a heavy expert among light ones.  Forward, data gradients and weight gradients
 against fp64 products on the GPU, elementwise |err| <= 2e-2 (|ref| + rms), the bf16 tolerance;
 each stage from the library's own stored inputs to it."""
+import ctypes
+
 import pytest
 import torch
 
@@ -17,17 +19,36 @@ CASES = {
     "narrow": (9, 320, 576, E(0, 1, 31, 32, 33, 3, 65, 2, 7)),
     # few rows, over 512 MiB of weights: 32 x 256 tiles
     "streaming": (70, 1984, 2112, E(0, 40, 32, 1) + [11 + (5 * e) % 17 for e in range(66)]),
-    # up projection on 128-row tiles (wide output), down projection on 32-row ones
+    # up projection on 128-row tiles (wide output), down projection on 32 x 128 ones
     "mid_narrow": (20, 192, 3136, E(0, 1, 127, 128, 129, 33, 2) + [30] * 13),
-    # down projection on 64-row tiles
-    "mid_mid64": (20, 192, 3136, E(0, 1, 63, 64, 65, 127, 128, 129, 257, 400) + [60] * 10),
+    # the same with more rows
+    "mid_narrow_rows": (20, 192, 3136, E(0, 1, 63, 64, 65, 127, 128, 129, 257, 400) + [60] * 10),
+    # up projection on 64-row tiles
+    "mid64": (12, 320, 2112, E(0, 1, 63, 64, 65, 127, 128, 129, 200, 33, 31, 150)),
     # 128-row tiles both ways
     "mid": (16, 2112, 2240, E(0, 1, 127, 128, 129, 255, 256, 257, 300) + [64] * 7),
     # 288-row tiles both ways, with and without their extra block
     "fat": (16, 2496, 2560, E(288, 257, 256, 289, 0, 1, 31, 32, 33, 575, 576, 577, 512, 534, 490, 255)),
-    # 288-row tiles up, smaller ones down
-    "fat_mid64": (4, 256, 10240, E(288, 1, 577, 300)),
+    # 288-row tiles up, 32 x 128 ones down
+    "fat_narrow": (4, 256, 10240, E(288, 1, 577, 300)),
 }
+
+# the tiles of the up and down projection that each case is there for
+TILES = {"narrow": ("32x128", "32x128"), "streaming": ("32x256", "32x256"), "mid_narrow": ("128x128", "32x128"),
+         "mid_narrow_rows": ("128x128", "32x128"), "mid64": ("64x128", "32x128"), "mid": ("128x128", "128x128"),
+         "fat": ("288x256", "288x256"), "fat_narrow": ("288x256", "32x128")}
+
+
+def kernels(f):
+    """The names of the kernels f enqueues."""
+    lib, cap = abi.load(), 8
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(cap)]
+    for e in ev:
+        e.record()                                 # creates the event's handle
+    handles, names = (ctypes.c_void_p * cap)(*[e.cuda_event for e in ev]), (ctypes.c_char_p * cap)()
+    assert lib.dmoe_trace_begin(handles, names, cap) == 0
+    f()
+    return [names[i].decode() for i in range(lib.dmoe_trace_end())]
 
 
 def close(got, ref, name):
@@ -51,7 +72,9 @@ def test_row_tile_shapes(name):
     h, a, y, dh, dx = nan(P, H), nan(P, H), nan(P, D), nan(P, H), nan(P, D)
     dW1, db1, dW2, db2 = (torch.full_like(v, 7.0) for v in (W1, b1, W2, b2))
     off, cnt = offs.to(dev), torch.tensor(counts, dtype=torch.int32, device=dev)
-    abi.dmoe_expert_ffn_fwd(dims, off, x, W1, b1, W2, b2, h, a, y, ws)
+    ran = kernels(lambda: abi.dmoe_expert_ffn_fwd(dims, off, x, W1, b1, W2, b2, h, a, y, ws))
+    gemms = [n for n in ran if n.startswith("grouped_gemm2")]
+    assert [any(f",{t}," in n for n in gemms[i:i + 1]) for i, t in enumerate(TILES[name])] == [True, True], gemms
     h2, a2, y2 = nan(P, H), nan(P, H), nan(P, D)
     abi.dmoe_expert_ffn_fwd_noalloc(dims, off, x, W1, b1, W2, b2, h2, a2, y2)
     abi.dmoe_expert_ffn_bwd(dims, off, cnt, x, h, a, dy, W1, W2, dh, dx, dW1, db1, dW2, db2, ws)
