@@ -204,18 +204,18 @@ ln_act_bwd_rows_kernel(const E* h, const float* stats, const int32_t* offsets, i
 
 // Scale and shift gradients of the normalisation step, per expert e and feature f:
 //   dgamma[e][f] = sum over e's rows of da act'(z) n,  dbeta[e][f] = sum of da act'(z).
-// Block (x, e) takes CS_CL * VEC features of expert e, its rows split over slices as in
+// Block (x, e) takes CL * VEC features of expert e, its rows split over slices as in
 // segment_colsum (64 experts of 2048 rows, F = 4096 bf16: 722-784 -> 390-410 us).
 // Experts without rows are left untouched.
-template <typename E, int ACT>
+template <typename E, int ACT, int CL>
 __global__ void __launch_bounds__(CS_NT)
 ln_act_bwd_params_kernel(const E* h, const float* stats, const int32_t* offsets, int F, const E* gamma,
                          const E* beta, const E* da, E* dgamma, E* dbeta) {
-  constexpr int VEC = Vec<E>::N, S = CS_SL;
+  constexpr int VEC = Vec<E>::N, S = CS_NT / CL;
   const int e = blockIdx.y;
   const int r0 = offsets[e], r1 = offsets[e + 1];
   if (r1 == r0) return;
-  const int c = ((int)blockIdx.x * CS_CL + (int)threadIdx.x % CS_CL) * VEC;
+  const int c = ((int)blockIdx.x * CL + (int)threadIdx.x % CL) * VEC;
   const bool cok = c < F;
   const int cc = cok ? c : 0;
   float g[VEC], b[VEC], acc[2][VEC];                  // acc: scale, shift
@@ -236,7 +236,7 @@ ln_act_bwd_params_kernel(const E* h, const float* stats, const int32_t* offsets,
     }
   };
   constexpr int U = 4;
-  int r = r0 + (int)threadIdx.x / CS_CL;
+  int r = r0 + (int)threadIdx.x / CL;
   for (; r + (U - 1) * S < r1; r += U * S) {
     uint4 hv[U], dv[U];
     float2 st[U];
@@ -253,8 +253,8 @@ ln_act_bwd_params_kernel(const E* h, const float* stats, const int32_t* offsets,
   for (; r < r1; r += S)
     add(*reinterpret_cast<const uint4*>(h + (int64_t)r * F + cc), *reinterpret_cast<const uint4*>(da + (int64_t)r * F + cc),
         *reinterpret_cast<const float2*>(stats + 2 * (int64_t)r));
-  colsum_slices(acc);
-  if ((int)threadIdx.x >= CS_CL || !cok) return;
+  colsum_slices<CL>(acc);
+  if ((int)threadIdx.x >= CL || !cok) return;
   *reinterpret_cast<uint4*>(dgamma + (int64_t)e * F + c) = Vec<E>::pack(acc[0]);
   *reinterpret_cast<uint4*>(dbeta + (int64_t)e * F + c) = Vec<E>::pack(acc[1]);
 }
@@ -495,8 +495,11 @@ template <typename E, int ACT>
 static void ln_bwd_act(const Shape& s, const int32_t* offsets, const E* h, const float* stats, const E* g,
                        const E* b, const E* da, E* dh, E* dg, E* db, hipStream_t st) {
   const int N = (int)s.N, F = (int)s.H, grid = ln_grid(s);
-  DMOE_LAUNCH((ln_act_bwd_params_kernel<E, ACT>), dim3((unsigned)colsum_blocks<E>(F), (unsigned)N), dim3(CS_NT), 0,
-              st, h, stats, offsets, F, g, b, da, dg, db);
+  with_lanes(colsum_lanes<E>(s, F), [&](auto CLc) {
+    constexpr int CL = decltype(CLc)::value;
+    DMOE_LAUNCH((ln_act_bwd_params_kernel<E, ACT, CL>), dim3((unsigned)colsum_blocks<E>(F, CL), (unsigned)N), dim3(CS_NT), 0,
+                st, h, stats, offsets, F, g, b, da, dg, db);
+  });
   switch (ln_chunks<E>(F)) {
     case 1: DMOE_LAUNCH((ln_act_bwd_rows_kernel<E, 1, ACT>), dim3(grid), dim3(LN_NT), 0, st, h, stats, offsets, N, F, g, b, da, dh); break;
     case 2: DMOE_LAUNCH((ln_act_bwd_rows_kernel<E, 2, ACT>), dim3(grid), dim3(LN_NT), 0, st, h, stats, offsets, N, F, g, b, da, dh); break;

@@ -73,60 +73,76 @@ static void run_tile_plan(const Shape& s, const int32_t* offsets, int BMa, int B
 }
 
 // Column sums over each expert's rows, for the bias gradients (and the LayerNorm scale and
-// shift gradients of ffblock.hip).  Bound by the one read of X.  A block takes CS_CL * VEC
-// columns (256-byte row pieces) of one expert and splits its rows over CS_SL slices: slice
-// s adds the rows s, s + CS_SL, ... in order (so a wave reads four row pieces at a time),
-// the slices meet in LDS in slice order.  A thread walking all rows of its columns instead
-// (256 threads and 2048 columns to a block) left a layer of few experts with a few dozen
-// blocks: 64 experts of 2048 rows, 1024 bf16 columns (268 MB) 537 -> 44 us (6.1 TB/s), 4096
-// columns 687 -> 231 us; 25 experts of 324 rows, 3008 and 960 columns in one launch
-// 154 -> 13 us.  64-lane pieces and 4 slices, the better split of few rows a priori,
-// measured 39 against 43 us at 1000 experts of 16 rows and 37 against 33 us at a skewed
-// 1024-expert routing: not worth a second form.
-constexpr int CS_NT = 256, CS_CL = 16, CS_SL = CS_NT / CS_CL;
+// shift gradients of ffblock.hip).  Bound by the one read of X.  A block takes CL * VEC columns
+// of one expert and splits its rows over CS_NT / CL slices: slice s adds the rows s, s + slices,
+// ... in order, the slices meet in LDS in slice order.
+//   * 16 lanes, 16 slices for many rows: whole rows to a thread left a layer of few experts with
+//     a few dozen blocks (64 experts of 2048 rows, 1024 bf16 columns, 268 MB 537 -> 44 us, 6.1
+//     TB/s; 25 experts of 324 rows, 3008 and 960 columns in one launch 154 -> 13 us).
+//   * With few rows most slices have none and the blocks are too many.  Column sums / LayerNorm
+//     parameter sums in us, 256 / 64 / 16 lanes: 1024 experts, 512 and 2048 columns, 48 rows
+//     50 + 86 / 41 + 81 / 39 + 86; 16 rows 19 + 37 / 18 + 36 / 23 + 50; 8 rows 12 + 24 /
+//     12 + 25 / 20 + 43; 15625 experts, 8 rows 133 + 228 / 120 + 219 / 237 + 486; 2 rows 40 + 76 /
+//     49 + 116 / 186 + 406; a row to 50 experts 17 + 17 / 37 + 36 / 73 + 71; 128 and 512 columns,
+//     2 rows 29 + 45 / 23 + 37 / 53 + 114.
+constexpr int CS_NT = 256;
+template <typename E>
+static int colsum_lanes(const Shape& s, int ncols) {
+  if (s.P < s.N || (s.P < 4 * s.N && ncols >= CS_NT / 2 * (16 / (int)sizeof(E)))) return 256;
+  return s.P < 48 * s.N ? 64 : 16;
+}
+// f(lanes as a compile-time constant)
+template <typename F> static void with_lanes(int CL, F&& f) {
+  if (CL == 256) f(std::integral_constant<int, 256>{});
+  else if (CL == 64) f(std::integral_constant<int, 64>{});
+  else f(std::integral_constant<int, 16>{});
+}
 
 struct ColsumJob { const void* X; void* out; int ncols, blocks; };   // X rows are ncols apart
 
 template <typename E>
-static int colsum_blocks(int ncols) {
-  constexpr int W = CS_CL * (16 / (int)sizeof(E));
+static int colsum_blocks(int ncols, int CL) {
+  const int W = CL * (16 / (int)sizeof(E));
   return (ncols + W - 1) / W;
 }
 
 // acc[NS][VEC] of this thread summed over the block's slices, left in the threads of slice 0
-template <int NS, int VEC>
+template <int CL, int NS, int VEC>
 __device__ __forceinline__ void colsum_slices(float (&acc)[NS][VEC]) {
-  __shared__ float red[CS_SL - 1][NS][VEC][CS_CL];
-  const int l = threadIdx.x % CS_CL, sl = threadIdx.x / CS_CL;
-  if (sl > 0) {
-#pragma unroll
-    for (int n = 0; n < NS; ++n)
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) red[sl - 1][n][i][l] = acc[n][i];
-  }
-  __syncthreads();
-  if (sl == 0) {
-    for (int q = 0; q < CS_SL - 1; ++q)
+  constexpr int SL = CS_NT / CL;
+  if constexpr (SL > 1) {
+    __shared__ float red[SL - 1][NS][VEC][CL];
+    const int l = threadIdx.x % CL, sl = threadIdx.x / CL;
+    if (sl > 0) {
 #pragma unroll
       for (int n = 0; n < NS; ++n)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[n][i] += red[q][n][i][l];
+        for (int i = 0; i < VEC; ++i) red[sl - 1][n][i][l] = acc[n][i];
+    }
+    __syncthreads();
+    if (sl == 0) {
+      for (int q = 0; q < SL - 1; ++q)
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) acc[n][i] += red[q][n][i][l];
+    }
   }
 }
 
 // out[e][c] = sum of rows [offsets[e], offsets[e+1]) of column c (experts without rows
 // are left untouched); SGD: out[e][c] -= lr * that sum (out holds the parameters).
 // Two matrices in one launch: blocks [0, j0.blocks) of x sum j0, the rest j1.
-template <typename E, bool SGD>
+template <typename E, bool SGD, int CL>
 __global__ void __launch_bounds__(CS_NT)
 segment_colsum(ColsumJob j0, ColsumJob j1, const int32_t* offsets, float lr) {
-  constexpr int VEC = 16 / sizeof(E), S = CS_SL;
+  constexpr int VEC = 16 / sizeof(E), S = CS_NT / CL;
   const int e = blockIdx.y;
   const int r0 = offsets[e], r1 = offsets[e + 1];
   if (r1 == r0) return;
   const bool second = (int)blockIdx.x >= j0.blocks;
   const ColsumJob& j = second ? j1 : j0;
-  const int c = (((int)blockIdx.x - (second ? j0.blocks : 0)) * CS_CL + (int)threadIdx.x % CS_CL) * VEC;
+  const int c = (((int)blockIdx.x - (second ? j0.blocks : 0)) * CL + (int)threadIdx.x % CL) * VEC;
   const bool cok = c < j.ncols;
   const E* X = reinterpret_cast<const E*>(j.X) + (cok ? c : 0);
   const int64_t ld = j.ncols;
@@ -135,7 +151,7 @@ segment_colsum(ColsumJob j0, ColsumJob j1, const int32_t* offsets, float lr) {
   for (int i = 0; i < VEC; ++i) acc[0][i] = 0.f;
   // four loads in flight at a time
   constexpr int U = 4;
-  int r = r0 + (int)threadIdx.x / CS_CL;
+  int r = r0 + (int)threadIdx.x / CL;
   for (; r + (U - 1) * S < r1; r += U * S) {
     uint4 q[U];
 #pragma unroll
@@ -154,8 +170,8 @@ segment_colsum(ColsumJob j0, ColsumJob j1, const int32_t* offsets, float lr) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[0][i] += v[i];
   }
-  colsum_slices(acc);
-  if ((int)threadIdx.x >= CS_CL || !cok) return;
+  colsum_slices<CL>(acc);
+  if ((int)threadIdx.x >= CL || !cok) return;
   uint4* op = reinterpret_cast<uint4*>(reinterpret_cast<E*>(j.out) + (int64_t)e * j.ncols + c);
   if constexpr (SGD) {
     float w[VEC];
@@ -170,10 +186,13 @@ segment_colsum(ColsumJob j0, ColsumJob j1, const int32_t* offsets, float lr) {
 template <typename E, bool SGD = false>
 static void run_colsum(const Shape& s, const int32_t* offsets, const E* X0, int n0, E* out0, const E* X1, int n1,
                        E* out1, float lr, hipStream_t st) {
-  const ColsumJob j0{X0, out0, n0, colsum_blocks<E>(n0)};
-  const ColsumJob j1{X1, out1, n1, X1 ? colsum_blocks<E>(n1) : 0};
-  DMOE_LAUNCH_NAMED("segment_colsum", (segment_colsum<E, SGD>),
-                    dim3((unsigned)(j0.blocks + j1.blocks), (unsigned)s.N), dim3(CS_NT), 0, st, j0, j1, offsets, lr);
+  with_lanes(colsum_lanes<E>(s, std::max(n0, n1)), [&](auto CLc) {
+    constexpr int CL = decltype(CLc)::value;
+    const ColsumJob j0{X0, out0, n0, colsum_blocks<E>(n0, CL)};
+    const ColsumJob j1{X1, out1, n1, X1 ? colsum_blocks<E>(n1, CL) : 0};
+    DMOE_LAUNCH_NAMED("segment_colsum", (segment_colsum<E, SGD, CL>), dim3((unsigned)(j0.blocks + j1.blocks), (unsigned)s.N),
+                      dim3(CS_NT), 0, st, j0, j1, offsets, lr);
+  });
 }
 
 constexpr int MAX_DEVICES = 64;
