@@ -391,13 +391,13 @@ static RowTile row_tile_line(double act, double r, double n, double K, double cu
   if (mid.first < cus) return r < 48.0 ? RT_NARROW : RT_MID64;
   return 1.65 * rounds(ROW_COST[RT_FAT]).second <= mid.second ? RT_FAT : RT_MID;
 }
-// The choice depends on n alone within a layer (a plan's tile height is shared by every GEMM
-// of an output width): K is taken as the other of D and H.
-static RowTile row_tile(const Shape& s, int64_t n) {
-  const double act = (double)std::min<int64_t>(s.N, s.P), r = (double)s.P / act;
-  const double K = (double)(n == s.H ? s.D : s.H), cus = (double)device_cus();
+// A plan's tile height is shared by every GEMM of an output width, so from 24 rows on the
+// choice takes the other of D and H for K; below, both shapes are 32 rows high.
+static RowTile row_tile(const Shape& s, int64_t n, int64_t K_gemm) {
+  const double act = (double)std::min<int64_t>(s.N, s.P), r = (double)s.P / act, cus = (double)device_cus();
+  if (s.P < 24 * s.N) return row_tile_line(act, (double)s.P / (double)s.N, (double)n, (double)K_gemm, cus);
+  const double K = (double)(n == s.H ? s.D : s.H);
   int pick = row_tile_line(act, (double)s.P / (double)s.N, (double)n, K, cus);
-  if (s.P < 24 * s.N) return (RowTile)pick;
   double t[5];
   for (int i = 0; i < 5; ++i) t[i] = row_cost(ROW_COST[i], act, r, (double)n, K, cus);
   const int best = (int)(std::min_element(t, t + 5) - t);
@@ -405,7 +405,7 @@ static RowTile row_tile(const Shape& s, int64_t n) {
   if (t[pick] > 1.1 * t[best]) pick = best;
   return (RowTile)(t[outer] <= t[pick] ? outer : pick);
 }
-static int row_tile_rows(const Shape& s, int64_t n) { return ROW_COST[row_tile(s, n)].rows; }
+static int row_tile_rows(const Shape& s, int64_t n) { return ROW_COST[row_tile(s, n, 1)].rows; }
 
 // One row-grouped GEMM in the tile shape row_tile picks: p.tscale and the grid are set here.
 template <bool BT, int EPI>
@@ -417,7 +417,7 @@ static void run_gemm2_rows(const Shape& s, GemmArgs<bf16> p, hipStream_t st) {
     p.tscale = nt;
     run_gemm2<GROUP_M, false, BT, EPI, C::BM, C::BN, C::WM, C::WN, C::ST, C::BK, STORE_DIRECT, C::XB>(p, mt_ub * nt, st);
   };
-  switch (row_tile(s, p.N)) {
+  switch (row_tile(s, p.N, p.K)) {
     case RT_SKINNY: go(G2Skinny{}); break;
     case RT_NARROW: go(G2Narrow{}); break;
     case RT_MID64: go(G2Mid64{}); break;
