@@ -84,12 +84,14 @@ static void run_tile_plan(const Shape& s, const int32_t* offsets, int BMa, int B
 //     50 + 86 / 41 + 81 / 39 + 86; 16 rows 19 + 37 / 18 + 36 / 23 + 50; 8 rows 12 + 24 /
 //     12 + 25 / 20 + 43; 15625 experts, 8 rows 133 + 228 / 120 + 219 / 237 + 486; 2 rows 40 + 76 /
 //     49 + 116 / 186 + 406; a row to 50 experts 17 + 17 / 37 + 36 / 73 + 71; 128 and 512 columns,
-//     2 rows 29 + 45 / 23 + 37 / 53 + 114.
+//     2 rows 29 + 45 / 23 + 37 / 53 + 114.  Few blocks of 64 lanes leave units idle: LayerNorm
+//     backward of 16 experts of 32 rows, 2048 columns, 16 us with 64 lanes, 12 with 16.
 constexpr int CS_NT = 256;
 template <typename E>
 static int colsum_lanes(const Shape& s, int ncols) {
   if (s.P < s.N || (s.P < 4 * s.N && ncols >= CS_NT / 2 * (16 / (int)sizeof(E)))) return 256;
-  return s.P < 48 * s.N ? 64 : 16;
+  const int64_t blocks = s.N * ((ncols + 64 * (16 / (int)sizeof(E)) - 1) / (64 * (16 / (int)sizeof(E))));
+  return s.P < 16 * s.N || (s.P < 48 * s.N && blocks >= 1536) ? 64 : 16;
 }
 // f(lanes as a compile-time constant)
 template <typename F> static void with_lanes(int CL, F&& f) {
