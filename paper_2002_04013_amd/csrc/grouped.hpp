@@ -20,46 +20,52 @@ namespace dmoe {
 //                          (GROUP_M m-tiles; the GEMMs of a call use at most two)
 //   act[e]               = number of experts before e that have rows (GROUP_K experts)
 // with the totals at [N]; act may be null.  A GEMM with NT n-tiles (GROUP_M) or MT*NT tiles
-// per expert (GROUP_K) scales these.
+// per expert (GROUP_K) scales these.  One block: thread q owns the experts [q EPT, (q+1) EPT),
+// the waves' sums are scanned by shuffles and meet in LDS once (a forward of 4096 experts, almost
+// all without rows, 20.4 us with 21 barriers for the three sums, 19.6 with one).
 static __global__ void __launch_bounds__(1024)
 tile_plan(const int32_t* offsets, int N, int BMa, int BMb, int32_t* plan_a, int32_t* plan_b, int32_t* act) {
-  __shared__ int s_a[1024], s_b[1024], s_ac[1024];
-  const int q = threadIdx.x;
+  __shared__ int part[3][16];
+  const int q = threadIdx.x, lane = q & 63, wave = q >> 6;
   const int EPT = (N + 1023) / 1024;
   const int e0 = min(N, q * EPT), e1 = min(N, e0 + EPT);
-  int ma = 0, mb = 0, ac = 0;
-  for (int e = e0; e < e1; ++e) {
-    const int c = offsets[e + 1] - offsets[e];
-    ma += (c + BMa - 1) / BMa;
-    mb += (c + BMb - 1) / BMb;
-    ac += c > 0;
+  int mine[3] = {0, 0, 0}, run[3], total[3] = {0, 0, 0};
+  auto add = [&](int (&v)[3], int c) {
+    v[0] += (c + BMa - 1) / BMa;
+    v[1] += (c + BMb - 1) / BMb;
+    v[2] += c > 0;
+  };
+  for (int e = e0; e < e1; ++e) add(mine, offsets[e + 1] - offsets[e]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    int incl = mine[i];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) part[i][wave] = incl;
+    run[i] = incl - mine[i];
   }
-  s_a[q] = ma;
-  s_b[q] = mb;
-  s_ac[q] = ac;
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int va = q >= o ? s_a[q - o] : 0, vb = q >= o ? s_b[q - o] : 0, vc = q >= o ? s_ac[q - o] : 0;
-    __syncthreads();
-    s_a[q] += va;
-    s_b[q] += vb;
-    s_ac[q] += vc;
-    __syncthreads();
-  }
-  int ba = s_a[q] - ma, bb = s_b[q] - mb, bc = s_ac[q] - ac;
+  const int waves = (int)blockDim.x >> 6;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    for (int w = 0; w < waves; ++w) {
+      const int v = part[i][w];
+      if (w < wave) run[i] += v;
+      total[i] += v;
+    }
   for (int e = e0; e < e1; ++e) {
-    const int c = offsets[e + 1] - offsets[e];
-    plan_a[e] = ba;
-    plan_b[e] = bb;
-    if (act) act[e] = bc;
-    ba += (c + BMa - 1) / BMa;
-    bb += (c + BMb - 1) / BMb;
-    bc += c > 0;
+    plan_a[e] = run[0];
+    plan_b[e] = run[1];
+    if (act) act[e] = run[2];
+    add(run, offsets[e + 1] - offsets[e]);
   }
-  if (q == 1023) {
-    plan_a[N] = s_a[1023];
-    plan_b[N] = s_b[1023];
-    if (act) act[N] = s_ac[1023];
+  if (q == 0) {
+    plan_a[N] = total[0];
+    plan_b[N] = total[1];
+    if (act) act[N] = total[2];
   }
 }
 
