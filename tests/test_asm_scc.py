@@ -3,8 +3,8 @@ with a scalar add, which also writes SCC.  If the compiler held a compare result
 carry of a 64-bit address add split in two, in SCC across that statement, the branch or
 the high half of the address would read the statement's SCC instead (a wrong branch, or
 an address 4 GiB off whenever the low half carries).  The statement declares SCC
-clobbered; this test compiles the sources that instantiate the GEMMs to gfx950 assembly
-and checks that no instruction reads SCC after the statement before something writes
+clobbered; this test compiles the sources that contain it (the GEMMs, and the gate's weight
+gradient with their tiles; a further test that there are no others) to gfx950 assembly and checks that no instruction reads SCC after the statement before something writes
 it again.  CPU only (the compiler cross-compiles)."""
 import os
 import re
@@ -16,7 +16,7 @@ import pytest
 from paper_2002_04013_amd import build as B
 
 HIPCC = B.HIPCC
-SOURCES = ["ffn.hip", "ffblock.hip"]
+SOURCES = ["ffn.hip", "ffblock.hip", "gate.hip"]
 
 # scalar instructions that read SCC
 READERS = re.compile(r"^(s_cbranch_scc[01]|s_cselect_b(32|64)|s_addc_u32|s_subb_u32|s_cmov_b(32|64)|s_cmovk_i32)\b")
@@ -73,3 +73,21 @@ def test_no_scc_reader_after_direct_lds_load(src, tmp_path):
     assert any("global_load_lds_dwordx4" in l for l in lines), "no direct-to-LDS load compiled"
     bad = scc_hazards(lines)
     assert not bad, f"SCC read after the direct-to-LDS statement at assembly lines {bad[:5]}"
+
+
+def test_every_source_with_the_load_is_scanned():
+    """The sources whose includes reach the statement (gemm2.hpp) are the scanned ones."""
+    def text(name):
+        with open(os.path.join(B.CSRC, name)) as f:
+            return f.read()
+
+    def reaches(name, seen):
+        for inc in re.findall(r'#include "(\w+\.hpp)"', text(name)):
+            if inc not in seen:
+                seen.add(inc)
+                reaches(inc, seen)
+        return seen
+
+    found = [n for n in sorted(os.listdir(B.CSRC)) if n.endswith(".hip") and "gemm2.hpp" in reaches(n, set())]
+    assert found == sorted(SOURCES)
+    assert [n for n in os.listdir(B.CSRC) if "S_ADD_U32 m0" in text(n) or "s_add_u32 m0" in text(n)] == ["gemm2.hpp"]

@@ -1,4 +1,5 @@
-"""Host address check of the grouped bf16 GEMM kernel (csrc/gemm2.hpp).
+"""Host address check of the grouped GEMM kernels (csrc/gemm2.hpp: bf16; csrc/gemm_f32.hpp:
+fp32) and of the loads of the gate's weight gradient, which uses their tiles.
 
 The kernel's source is compiled for the CPU under AddressSanitizer, with a stand-in for
 the HIP runtime header (tests/hostcheck/hip/hip_runtime.h), and every thread of every
@@ -26,7 +27,8 @@ from paper_2002_04013_amd import build as B
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CLANG = "/opt/rocm/llvm/bin/clang++"
-CONFIGS = ("G2Fat", "G2Skinny", "G2DW", "G2DWShort")
+CONFIGS = ("G2Fat", "G2Skinny", "G2Narrow", "G2Mid64", "G2Mid", "G2DW", "G2DWShort",
+           "CfgF32", "CfgF32DW", "CfgF32Skinny")
 
 # (pattern, replacement, regex): each must match the source at least once
 SUBST = {
@@ -44,6 +46,7 @@ SUBST = {
         ("__attribute__((address_space(4)))", "", False),
         ("namespace dmoe {", "extern thread_local char* hostcheck_smem;\nnamespace dmoe {", False),
     ],
+    "gemm_f32.hpp": [("extern __shared__ __align__(1024) char smem[];", "char* smem = hostcheck_smem;", False)],
 }
 
 
@@ -59,9 +62,11 @@ def _patch(name, text):
 
 
 def _configs():
-    """The bf16 tile-shape structs of the launch helpers, as C++ text."""
+    """The tile-shape structs of the launch helpers, as C++ text; none may be missing here."""
     with open(os.path.join(B.CSRC, "grouped.hpp")) as f:
         src = f.read()
+    shapes = re.findall(r"struct ((?:G2|CfgF32)\w*)\s*\{", src)
+    assert sorted(shapes) == sorted(CONFIGS), shapes
     out = []
     for name in CONFIGS:
         m = re.search(r"struct %s\s*\{.*?\};" % name, src, flags=re.S)
@@ -74,7 +79,7 @@ def _configs():
 def test_grouped_gemm_addresses_stay_in_bounds(tmp_path):
     src = tmp_path / "src"
     src.mkdir()
-    for name in ("common.hpp", "gemm.hpp", "gemm2.hpp"):
+    for name in ("common.hpp", "gemm.hpp", "gemm2.hpp", "gemm_f32.hpp"):
         with open(os.path.join(B.CSRC, name)) as f:
             text = f.read()
         (src / name).write_text(_patch(name, text))
@@ -94,3 +99,7 @@ def test_grouped_gemm_addresses_stay_in_bounds(tmp_path):
     r = subprocess.run([str(exe), "short"], capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode != 0 and "heap-buffer-overflow" in r.stderr, r.stderr[-2000:]
     assert "grouped_gemm2<1, true, true" in r.stderr, r.stderr[-2000:]
+    # and one 4 elements short in the fp32 GEMM
+    r = subprocess.run([str(exe), "short_f32"], capture_output=True, text=True, env=env, timeout=600)
+    assert r.returncode != 0 and "heap-buffer-overflow" in r.stderr, r.stderr[-2000:]
+    assert "grouped_gemm_f32<1, true, true" in r.stderr, r.stderr[-2000:]
