@@ -57,8 +57,10 @@ Workspace workspace_layout(const Shape& s) {
   w.part_off = off;
   w.part_bytes = align256((size_t)w.gsplit * s.dM * s.D * sizeof(float));
   off += w.part_bytes;
+  // the forward's queue, or the backward's bias sums of each block of GD_TOK tokens
   w.gq_off = off;
-  w.gq_bytes = align256((size_t)(GQ_HEAD + s.T) * sizeof(int32_t));
+  const size_t dbg_bytes = (size_t)((s.T + GD_TOK - 1) / GD_TOK) * s.dM * sizeof(float);
+  w.gq_bytes = align256(std::max((size_t)(GQ_HEAD + s.T) * sizeof(int32_t), dbg_bytes));
   off += w.gq_bytes;
   // LayerNorm backward: partial column sums of the experts its blocks split.  The regions from
   // part_off on belong to other calls, so they share their memory.  Blocks of 64 to 512 threads

@@ -175,7 +175,8 @@ struct Workspace {
   size_t hist_off, hist_bytes;     // dispatch: per-block expert histograms
   size_t tiles_off, tiles_bytes;   // grouped GEMM: two tile prefixes [N+1] + prefix of experts with rows
   size_t part_off, part_bytes;     // gate backward: dWg partial sums per token split
-  size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute
+  size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute;
+                                   // gate backward: the dg blocks' column sums [blocks][d M]
   size_t ln_off;                   // LayerNorm backward: partial column sums (over part and gq)
   size_t total;
   int64_t disp_blocks;             // dispatch blocks (pairs per block = DISP_CHUNK)
@@ -185,6 +186,7 @@ struct Workspace {
 
 constexpr int DISP_CHUNK = 1024;   // pairs per dispatch block
 constexpr int GQ_HEAD = 64;        // gate queue: the count sits on its own 256-byte line
+constexpr int GD_TOK = 128;        // gate backward: tokens per dg block
 
 Workspace workspace_layout(const Shape& s);
 

@@ -1083,7 +1083,6 @@ static size_t gate_mfma_lds_bytes(int dM, int kw) {
 // D = 1024, 128 columns, k = 8 130 -> 48 us; T = 4096, D = 1024, 64 columns 67 -> 18 us;
 // fp32 T = 2048, D = 512, 8 columns 79 -> 19 us.
 
-constexpr int GD_TOK = 128;        // tokens per dg block
 constexpr int GB_NT = 256;
 constexpr int GB_BN = 128;         // x columns per block, 32 per wave
 constexpr int GB_ST = 3;           // x stages in LDS
@@ -1474,8 +1473,8 @@ static int gate_bwd_impl(const Shape& s, const void* x, const int32_t* idx, cons
     return a < b + n && b < a + n;
   };
   p.dg_late = over(w) || over(dw);
-  // the bias gradient's per-block column sums use the forward pass's queue region
-  // (calls on one stream do not overlap): ceil(T / 128) x dM floats <= 4 T bytes
+  // the bias gradient's per-block column sums use the forward pass's queue region, which is
+  // sized for both (calls on one stream do not overlap)
   if (dbg) p.dbg_part = reinterpret_cast<float*>(base + L.gq_off);
   const size_t lds = gate_bwd_lds_bytes(s);
   auto go = [&](auto CBc) {
