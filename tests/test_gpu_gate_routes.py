@@ -8,9 +8,13 @@ that rise along the grid and that are all equal.  The reference ranks
 every cell in fp64 by (alive first, total desc, flat index asc).
 
 Certified route (bf16 matrix products plus recomputation of the rejected tokens): sizes
-above the line where it is taken, for each column-block count, wave count and alive mode,
-against the exact route on the same inputs (DMOE_FLAG_GATE_EXACT): the same experts in the
-same order, and weights within the error the score bound allows (a few fp32 ulp)."""
+above the line where it is taken, which the launch trace confirms, for each column-block count
+(1 to 3), wave count (one, and two from d_model 2048 on) and alive mode, against the exact route
+on the same inputs (DMOE_FLAG_GATE_EXACT): the same experts in the same order, and weights
+within the error the score bound allows (a few fp32 ulp).  The same with tokens that the
+certificate has to reject, more of them than blocks that take the queue."""
+import ctypes
+
 import pytest
 import torch
 
@@ -28,6 +32,18 @@ def gate(dims, x, Wg, bg, alive, T, k, dM):
     abi.dmoe_gate_topk(dims, x, Wg, bg, alive, idx, w, g, sc, ws)
     torch.cuda.synchronize()
     return idx.cpu().long(), w.cpu(), g.cpu(), sc.cpu()
+
+
+def kernels(f):
+    """The names of the kernels f enqueues."""
+    lib, cap = abi.load(), 8
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(cap)]
+    for e in ev:
+        e.record()                                 # creates the event's handle
+    handles, names = (ctypes.c_void_p * cap)(*[e.cuda_event for e in ev]), (ctypes.c_char_p * cap)()
+    assert lib.dmoe_trace_begin(handles, names, cap) == 0
+    f()
+    return [names[i].decode() for i in range(lib.dmoe_trace_end())]
 
 
 def reference(x, Wg, bg, alive, d, M, k, alive_first):
@@ -100,8 +116,15 @@ def test_exact_route_matches_the_definition(dtype, T, D, d, M, k, inputs, p_aliv
 
 
 @pytest.mark.parametrize("T,D,d,M,k,p_alive,alive_first", [
-    (33000, 2048, 2, 16, 4, 1.0, False), (40001, 2112, 2, 16, 8, 0.9, False), (40000, 1024, 2, 32, 4, 0.9, True),
-    (16400, 2048, 2, 48, 8, 0.8, True), (30000, 1088, 3, 25, 4, 0.95, False), (50003, 1024, 3, 16, 4, 0.9, True),
+    # columns up to 32, one wave a block and two
+    (44000, 64, 2, 4, 4, 0.9, False), (43001, 64, 1, 32, 8, 0.9, True), (33000, 2048, 2, 16, 4, 1.0, False),
+    (40001, 2112, 2, 16, 8, 0.9, True),
+    # up to 64
+    (40000, 1024, 2, 32, 4, 0.95, False), (40000, 1024, 2, 32, 4, 0.9, True), (20000, 2112, 2, 17, 8, 0.9, False),
+    (20000, 2048, 4, 11, 4, 0.9, True),
+    # up to 96
+    (30000, 1088, 3, 25, 4, 0.95, False), (50003, 1024, 2, 40, 8, 0.9, True), (16400, 2048, 2, 48, 8, 0.8, False),
+    (16400, 2048, 2, 48, 4, 0.8, True),
 ])
 def test_certified_route_matches_the_exact_one(T, D, d, M, k, p_alive, alive_first):
     g = torch.Generator(device="cuda").manual_seed(T)
@@ -111,14 +134,66 @@ def test_certified_route_matches_the_exact_one(T, D, d, M, k, p_alive, alive_fir
     bg = torch.randn(dM, generator=g, device="cuda").to(torch.bfloat16)
     alive = (torch.rand(N, generator=g, device="cuda") < p_alive).to(torch.uint8)
     fl = abi.DMOE_FLAG_ALIVE_TOPK if alive_first else 0
-    out = [gate(abi.make_dims(T, D, 64, d, M, k, "bf16", "relu", f), x, Wg, bg, alive, T, k, dM)
+    out = []
+    ran = [kernels(lambda: out.append(gate(abi.make_dims(T, D, 64, d, M, k, "bf16", "relu", f), x, Wg, bg, alive, T, k, dM)))
            for f in (fl, fl | abi.DMOE_FLAG_GATE_EXACT)]
+    assert any("gate_topk_mfma" in n for n in ran[0]) and ran[1] == ["gate_topk_f64"], ran
     assert torch.equal(out[0][0], out[1][0])
     # |score error| <= gamma_32 sum |x w| (about 4e-6 * 0.64 sqrt(D)); a weight moves by at most 2 w d times that
     lim = 4.1e-6 * float((x[:64].float().abs() @ Wg.float().abs().t()).max()) * 1.5 + 2.0 ** -22 * float(out[1][3].abs().max())
     assert float((out[0][3] - out[1][3]).abs().max()) <= lim
     assert float((out[0][2] - out[1][2]).abs().max()) <= d * lim
     assert float((out[0][1] - out[1][1]).abs().max()) <= 2 * d * lim + 1e-6
+
+
+@pytest.mark.parametrize("inputs", ["ties", "near_ties", "span"])
+@pytest.mark.parametrize("T,D,d,M,k,p_alive,alive_first", [
+    (40000, 1024, 2, 16, 4, 0.9, False), (20000, 2048, 2, 32, 8, 0.9, False), (40000, 1024, 2, 30, 4, 0.7, True),
+    (17000, 2112, 3, 25, 4, 0.9, True),
+])
+def test_certified_route_rejects(T, D, d, M, k, p_alive, alive_first, inputs):
+    """Every third token is one the certificate cannot decide: equal gate rows (exact ties, the
+    lower flat index first), rows that differ in the last bit of one weight, or scores that span
+    more than 2^25.  Against the definition for a sample of tokens
+    and against the exact route for all; the certified tokens between them stay as they are."""
+    g = torch.Generator(device="cuda").manual_seed(T + M)
+    dM, N = d * M, M ** d
+    x = torch.randn(T, D, generator=g, device="cuda").to(torch.bfloat16)
+    Wg = (torch.randn(dM, D, generator=g, device="cuda") * D ** -0.5).to(torch.bfloat16)
+    bg = torch.randn(dM, generator=g, device="cuda").to(torch.bfloat16)
+    alive = (torch.rand(N, generator=g, device="cuda") < p_alive).to(torch.uint8)
+    third = torch.arange(0, T, 3, device="cuda")
+    if inputs == "span":
+        # column 0 of each dimension scores x[0] + 2^-34, and x[0] is 0 on those tokens
+        Wg[::M], bg[::M] = 0, 0
+        Wg[::M, 0], Wg[::M, 1] = 1.0, 2.0 ** -34
+        x[:, 1], x[third, 0] = 1.0, 0.0
+    else:
+        # on those tokens x is 0 but for its first 64 values, where rows u and u + 1 agree
+        keep = torch.zeros(D, dtype=torch.bool, device="cuda")
+        keep[:64] = True
+        x[third] = torch.where(keep, x[third], torch.zeros_like(x[third]))
+        for i in range(d):
+            for u in range(0, M - 1, 2):
+                Wg[i * M + u + 1, :64], bg[i * M + u + 1] = Wg[i * M + u, :64], bg[i * M + u]
+                if inputs == "near_ties":
+                    Wg[i * M + u + 1, 7] = Wg[i * M + u, 7] * (1 + 2.0 ** -7)
+        if inputs == "near_ties":
+            x[third, 7] = 2.0 ** -14
+    fl = abi.DMOE_FLAG_ALIVE_TOPK if alive_first else 0
+    dims = abi.make_dims(T, D, 64, d, M, k, "bf16", "relu", fl)
+    out = []
+    assert any("gate_topk_mfma" in n for n in kernels(lambda: out.append(gate(dims, x, Wg, bg, alive, T, k, dM))))
+    out.append(gate(abi.make_dims(T, D, 64, d, M, k, "bf16", "relu", fl | abi.DMOE_FLAG_GATE_EXACT), x, Wg, bg, alive, T, k,
+                    dM))
+    assert torch.equal(out[0][0], out[1][0])
+    # the tokens were rejected: their scores are the exact route's, which certified ones rarely are
+    rec = (out[0][3] == out[1][3]).all(1)
+    assert int(rec[third.cpu()].sum()) > 1024 and bool(rec[third.cpu()].all())
+    n = 600
+    _, ridx, _, rw = reference(x[:n], Wg, bg, alive, d, M, k, alive_first)
+    assert torch.equal(out[0][0][:n], ridx)
+    assert float((out[0][1][:n] - rw).abs().max()) <= 1e-4
 
 
 @pytest.mark.parametrize("dtype,T,D,d,M,k,p_alive,alive_first", [

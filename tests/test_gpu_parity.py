@@ -174,8 +174,9 @@ def test_token_permutation_equivariance():
 
 
 def test_gate_exact_flag_same_routing():
-    """DMOE_FLAG_GATE_EXACT computes every token's scores with exact fp64 accumulation
-    (the fallback path of the certified MFMA gate): same TopK, bit for bit."""
+    """DMOE_FLAG_GATE_EXACT computes every token's scores with exact fp64 accumulation: same TopK,
+    bit for bit.  A call of this size takes that route anyway; test_gpu_gate_routes.py compares it
+    with the certified one."""
     from paper_2002_04013_amd.abi import DMOE_FLAG_GATE_EXACT
     wl = CASES["bf16_skew"]
     say("[parity] exact-gate flag")
@@ -190,9 +191,9 @@ def test_gate_exact_flag_same_routing():
 
 
 def test_gate_exact_ties_fall_back():
-    """Duplicated gate rows make exactly tied scores and totals: no certificate is
-    possible, every affected token takes the exact path and ties go to the lower
-    flat index, as in the oracle."""
+    """Duplicated gate rows make exactly tied scores and totals: ties go to the lower flat index,
+    as in the oracle, on the exact route, which a call of this size takes; the certified route's
+    rejected tokens are in test_gpu_gate_routes.py."""
     wl = Workload("ties", 24, T=512, D=128, H=128, d=2, M=8, k=4, dtype="bf16", act="gelu", p_alive=0.9)
     say("[parity] exact ties in the gate")
     inp = make_inputs(wl, "cpu")
