@@ -94,6 +94,11 @@ enum { DMOE_FLAG_GATE_EXACT = 1, DMOE_FLAG_ALIVE_TOPK = 2 };
  * on the same stream).  Returns 0 for invalid dims. */
 size_t dmoe_workspace_bytes(const dmoe_dims* dims);
 
+/* The same for a layer that never calls dmoe_expert_ffblock_bwd: enough for every other
+ * entry point.  The block backward keeps up to 1024 pieces of 3 H fp32 column sums (48 MiB
+ * at H = 4096), most of the workspace of a layer of moderate size. */
+size_t dmoe_ffn_workspace_bytes(const dmoe_dims* dims);
+
 /* Static text for a return code. */
 const char* dmoe_strerror(int code);
 

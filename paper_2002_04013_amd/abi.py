@@ -24,7 +24,7 @@ EXPORTS = (
     "dmoe_expert_ffn_fwd", "dmoe_combine", "dmoe_combine_bwd", "dmoe_gate_topk_bwd",
     "dmoe_expert_ffn_bwd", "dmoe_dispatch_bwd", "dmoe_expert_ffn_bwd_recompute", "dmoe_expert_ffn_bwd_sgd",
     "dmoe_expert_ffblock_fwd", "dmoe_expert_ffblock_bwd", "dmoe_ln_act_fwd", "dmoe_ln_act_bwd",
-    "dmoe_trace_begin", "dmoe_trace_end", "dmoe_expert_ffn_fwd_noalloc",
+    "dmoe_trace_begin", "dmoe_trace_end", "dmoe_expert_ffn_fwd_noalloc", "dmoe_ffn_workspace_bytes",
 )
 
 # parameters of the feed-forward block expert, in dmoe_ffblock_params order
@@ -71,6 +71,7 @@ def load(path=LIB_PATH):
     pd = ctypes.POINTER(Dims)
     sig = {
         "dmoe_workspace_bytes": (ctypes.c_size_t, [pd]),
+        "dmoe_ffn_workspace_bytes": (ctypes.c_size_t, [pd]),
         "dmoe_strerror": (ctypes.c_char_p, [ctypes.c_int]),
         "dmoe_gate_topk": (ctypes.c_int, [pd] + [_P] * 10),
         "dmoe_dispatch": (ctypes.c_int, [pd] + [_P] * 10),
@@ -134,6 +135,11 @@ def _check(rc, name):
 
 def workspace_bytes(dims):
     return int(load().dmoe_workspace_bytes(ctypes.byref(dims)))
+
+
+def ffn_workspace_bytes(dims):
+    """Enough for every entry point but dmoe_expert_ffblock_bwd."""
+    return int(load().dmoe_ffn_workspace_bytes(ctypes.byref(dims)))
 
 
 def strerror(code):

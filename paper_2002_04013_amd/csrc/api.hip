@@ -62,11 +62,12 @@ Workspace workspace_layout(const Shape& s) {
   const size_t dbg_bytes = (size_t)((s.T + GD_TOK - 1) / GD_TOK) * s.dM * sizeof(float);
   w.gq_bytes = align256(std::max((size_t)(GQ_HEAD + s.T) * sizeof(int32_t), dbg_bytes));
   off += w.gq_bytes;
-  // LayerNorm backward: partial column sums of the experts its blocks split.  The regions from
+  // LayerNorm backward (block experts only): partial column sums of the experts its blocks split.  The regions from
   // part_off on belong to other calls, so they share their memory.  Blocks of 64 to 512 threads
   // hold a row (16 bytes a thread), a full grid is 512 x 512 threads, a block gets at least 8 rows,
   // or an expert's average: a block's experts follow one another (backward of 256 experts of one
   // row, 128 -> 256, 79 us with 8 rows a block, 61 with one).
+  w.ffn_total = off;
   w.ln_off = w.part_off;
   const int64_t chunks = s.H * (int64_t)s.esz / 16;
   if (chunks <= 512) {
@@ -117,6 +118,12 @@ extern "C" size_t dmoe_workspace_bytes(const dmoe_dims* dims) {
   Shape s;
   if (check_dims(dims, &s) != DMOE_OK) return 0;
   return workspace_layout(s).total;
+}
+
+extern "C" size_t dmoe_ffn_workspace_bytes(const dmoe_dims* dims) {
+  Shape s;
+  if (check_dims(dims, &s) != DMOE_OK) return 0;
+  return workspace_layout(s).ffn_total;
 }
 
 extern "C" const char* dmoe_strerror(int code) {

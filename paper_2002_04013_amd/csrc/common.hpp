@@ -178,7 +178,7 @@ struct Workspace {
   size_t gq_off, gq_bytes;         // gate forward: [0] count, [GQ_HEAD + i] tokens to recompute;
                                    // gate backward: the dg blocks' column sums [blocks][d M]
   size_t ln_off;                   // LayerNorm backward: partial column sums (over part and gq)
-  size_t total;
+  size_t total, ffn_total;         // with and without the LayerNorm backward's
   int64_t disp_blocks;             // dispatch blocks (pairs per block = DISP_CHUNK)
   int64_t gsplit, gsplit_tokens;   // gate backward token splits
   int64_t ln_blocks;               // LayerNorm backward blocks (H up to 512 16-byte chunks)

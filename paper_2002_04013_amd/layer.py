@@ -25,7 +25,7 @@ class DMoELayer:
         dev = torch.device(device)
         e = lambda *s, dt=None: torch.empty(s, dtype=dt or self.dt, device=dev)
         i32 = torch.int32
-        nws = abi.workspace_bytes(self.dims)
+        nws = abi.ffn_workspace_bytes(self.dims)
         if nws == 0:
             raise abi.DmoeError("unsupported layer shape")
         self.ws = torch.empty(nws, dtype=torch.uint8, device=dev)

@@ -40,6 +40,27 @@ def test_library_exports_every_declared_symbol(lib):
     assert sorted(lib.EXPORTS) == _declared()
 
 
+def test_feed_forward_workspace(lib):
+    """A layer without block experts does not pay for their backward's column sums: what it needs
+    is the dispatch histograms, three tile prefixes, the gate's partial products and its queue,
+    each rounded up to 256 bytes."""
+    up = lambda n: (n + 255) // 256 * 256
+    for T, D, H, d, M, k, dtype in ((4096, 1024, 4096, 2, 32, 4, "bf16"), (250, 1024, 4096, 2, 16, 4, "bf16"),
+                                    (2048, 512, 2048, 2, 4, 2, "f32"), (1, 64, 64, 1, 128, 1, "bf16"),
+                                    (30001, 192, 4096, 2, 64, 8, "bf16")):
+        N, dM, P = M ** d, d * M, T * k
+        split = max((T * ((D + 127) // 128) + 511) // 512, 256, 4 * dM)
+        split = (split + 63) // 64 * 64
+        want = (up((P + 1023) // 1024 * N * 4) + up(3 * (N + 1) * 4) + up((T + split - 1) // split * dM * D * 4)
+                + up(max((64 + T) * 4, (T + 127) // 128 * dM * 4)))
+        dims = lib.make_dims(T, D, H, d, M, k, dtype, "gelu")
+        assert lib.ffn_workspace_bytes(dims) == want
+        assert lib.workspace_bytes(dims) >= want
+    # rows wider than the block backward takes need no more
+    wide = lib.make_dims(4096, 4096, 16384, 2, 16, 4, "bf16", "gelu")
+    assert lib.ffn_workspace_bytes(wide) == lib.workspace_bytes(wide)
+
+
 def test_workspace_and_validation(lib):
     ok = lib.make_dims(4096, 1024, 4096, 2, 32, 4, "bf16", "gelu")
     assert lib.workspace_bytes(ok) > 0
@@ -55,6 +76,7 @@ def test_workspace_and_validation(lib):
     ]
     for dims in bad:
         assert lib.workspace_bytes(dims) == 0
+        assert lib.ffn_workspace_bytes(dims) == 0
     # empty batch is valid
     assert lib.workspace_bytes(lib.make_dims(0, 64, 256, 2, 4, 2, "f32", "relu")) > 0
 

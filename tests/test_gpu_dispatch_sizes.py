@@ -34,12 +34,13 @@ def test_dispatch(dtype, T, k, d, M, D, p_alive, one_expert):
         alive[N - 1] = 1
     x = torch.randn(T, D, generator=gen).to(dt)
     dims = abi.make_dims(T, D, 64, d, M, k, dtype, "relu")
-    ws = torch.full((abi.workspace_bytes(dims),), 255, dtype=torch.uint8, device=dev)
+    ws = torch.full((abi.ffn_workspace_bytes(dims) + 256,), 255, dtype=torch.uint8, device=dev)   # 256 past its end
     i32 = lambda *s: torch.full(s, -7, dtype=torch.int32, device=dev)
     counts, offsets, row_token, pos = i32(N), i32(N + 1), i32(P), i32(T, k)
     xp = torch.full((P, D), 9.0, dtype=dt, device=dev)
     abi.dmoe_dispatch(dims, x.to(dev), idx.to(dev), alive.to(dev), counts, offsets, row_token, pos, xp, ws)
     torch.cuda.synchronize()
+    assert bool((ws[-256:] == 255).all())
     e = idx.view(-1).long()
     e = torch.where(alive[e] != 0, e, torch.full_like(e, N))
     order = torch.sort(e, stable=True)[1]

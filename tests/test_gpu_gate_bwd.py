@@ -42,8 +42,8 @@ def test_gate_backward(dtype, T, D, d, M, k, p_alive):
     dw = torch.randn(T, k, generator=gen)
     alive = (torch.rand(N, generator=gen) < p_alive).to(torch.uint8)
     dims = abi.make_dims(T, D, 64, d, M, k, dtype, "relu")
-    # the workspace at exactly its stated size, its contents poisoned
-    ws = torch.full((abi.workspace_bytes(dims),), 255, dtype=torch.uint8, device=dev)
+    # the workspace at its stated size, its contents poisoned
+    ws = torch.full((abi.ffn_workspace_bytes(dims) + 256,), 255, dtype=torch.uint8, device=dev)   # 256 past its end
     dg = torch.empty(T, k, device=dev)
     dWg, dbg = torch.empty(dM, D, dtype=dt, device=dev), torch.empty(dM, dtype=dt, device=dev)
     abi.dmoe_gate_topk_bwd(dims, x.to(dev), idx.to(dev), w.to(dev), dw.to(dev), alive.to(dev), dg, dWg, dbg, ws)
@@ -56,6 +56,7 @@ def test_gate_backward(dtype, T, D, d, M, k, p_alive):
         dWg3, dbg3 = torch.empty_like(dWg), torch.empty_like(dbg)
         abi.dmoe_gate_topk_bwd(dims, x.to(dev), idx.to(dev), wd[0], wd[1], alive.to(dev), wd[which], dWg3, dbg3, ws)
         torch.cuda.synchronize()
+        assert bool((ws[-256:] == 255).all())
         assert torch.equal(wd[which], dg) and torch.equal(dWg, dWg3) and torch.equal(dbg, dbg3)
     wl = torch.where(alive[idx.long()] != 0, w, torch.zeros_like(w)).double()
     rdg = wl * (dw.double() - (wl * dw.double()).sum(1, keepdim=True))

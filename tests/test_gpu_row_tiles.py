@@ -67,7 +67,7 @@ def test_row_tile_shapes(name):
     offs = torch.tensor([0] + counts, dtype=torch.int32).cumsum(0).to(torch.int32)
     W1, b1, W2, b2 = rn(N, H, D, sc=D ** -0.5), rn(N, H), rn(N, D, H, sc=H ** -0.5), rn(N, D)
     x, dy = rn(P, D), rn(P, D)
-    ws = torch.full((abi.workspace_bytes(dims),), 255, dtype=torch.uint8, device=dev)
+    ws = torch.full((abi.ffn_workspace_bytes(dims) + 256,), 255, dtype=torch.uint8, device=dev)   # 256 past its end
     nan = lambda *s: torch.full(s, float("nan"), dtype=torch.bfloat16, device=dev)
     h, a, y, dh, dx = nan(P, H), nan(P, H), nan(P, D), nan(P, H), nan(P, D)
     dW1, db1, dW2, db2 = (torch.full_like(v, 7.0) for v in (W1, b1, W2, b2))
@@ -82,6 +82,7 @@ def test_row_tile_shapes(name):
     rW1, rb1, rW2, rb2 = (torch.full_like(v, 7.0) for v in (W1, b1, W2, b2))
     abi.dmoe_expert_ffn_bwd_recompute(dims, off, cnt, x, W1, b1, W2, dy, hr, ar, dxr, rW1, rb1, rW2, rb2, ws)
     torch.cuda.synchronize()
+    assert bool((ws[-256:] == 255).all())
     for t in (h, a, y, dh, dx):
         assert bool(t[rows:].isnan().all()), f"{name}: rows past the last expert were written"
     for u, v in ((h, h2), (a, a2), (y, y2), (dx, dxr)):
