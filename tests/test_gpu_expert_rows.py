@@ -26,13 +26,14 @@ from parity_util import RTOL, assert_close, say
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # many rows per expert: 288-row tiles with the extra block, 64-deep weight-gradient steps
+    # many rows per expert: counts around the 256- and 288-row tiles, 64-deep weight-gradient steps
+    # (with so few columns smaller row tiles run; test_gpu_row_tiles.py has these counts on 288-row ones)
     "fat": dict(d=2, M=4, D=320, H=576, seed=71,
                 counts=[288, 257, 256, 289, 0, 1, 31, 32, 33, 575, 576, 577, 512, 534, 490, 255]),
     # few rows per expert: 32-row tiles, 32-deep weight-gradient steps over a ring that wraps
     "skinny": dict(d=2, M=8, D=192, H=320, seed=72,
                    counts=[0, 1, 2, 3, 31, 32, 33, 63, 64, 65, 301, 7, 0, 16] + [5 + (3 * e) % 29 for e in range(50)]),
-    # fp32 layer: the register-staged fp32 GEMMs (32 x 64 tiles)
+    # fp32 layer: 32 x 64 tiles
     "f32": dict(d=2, M=3, D=64, H=128, seed=73, dtype="f32", counts=[0, 1, 31, 32, 33, 63, 64, 65, 97]),
 }
 
@@ -49,7 +50,10 @@ def _expert_rows(counts, D, H, N, seed, dt):
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_expert_calls_on_tile_edges(name):
-    c = CASES[name]
+    check_expert_calls(name, CASES[name])
+
+
+def check_expert_calls(name, c):
     d, M, D, H = c["d"], c["M"], c["D"], c["H"]
     N = M ** d
     counts = list(c["counts"]) + [0] * (N - len(c["counts"]))

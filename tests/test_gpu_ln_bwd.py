@@ -1,5 +1,5 @@
-"""The one-pass LayerNorm backward of the block experts at the edges of its row shares (at
-least 8 rows a block, two at a time): experts of odd counts, within one block, spread over
+"""The one-pass LayerNorm backward of the block experts, with either activation, at the edges of
+its row shares (at least 8 rows a block, or an expert's average below that, two at a time): experts of odd counts, within one block, spread over
 several, beginning and ending on block bounds, empty, more experts than blocks and fewer; row
 widths at each block size and at the widest.  Against fp64 on the GPU from the library's own
 stored inputs to each step (h, the incoming gradient rounded to the stored type), elementwise
@@ -15,21 +15,27 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("bf16", 64, 64, [8, 8, 16, 1, 0, 7, 9, 23]), ("bf16", 64, 576, [301, 0, 2, 5]),
     ("bf16", 128, 1088, [3] * 40 + [0, 17, 1, 33]), ("bf16", 64, 4096, [129, 0, 64, 3]),
+    ("bf16", 64, 128, [1, 2, 0, 1, 3, 1, 0, 2] * 4), ("f32", 64, 64, [0, 0, 1, 0] * 6),
     ("f32", 64, 64, [5, 0, 90, 1, 8, 8]), ("f32", 64, 320, [2] * 60 + [41]), ("f32", 64, 2048, [1, 70, 0, 9]),
 ]
 
 
+@pytest.mark.parametrize("act", ["gelu", "relu"])
 @pytest.mark.parametrize("dtype,D,F,counts", CASES)
-def test_block_backward_normalisation(dtype, D, F, counts):
+def test_block_backward_normalisation(dtype, D, F, counts, act):
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     N, rows = len(counts), sum(counts)
     P, dev = rows + 3, torch.device("cuda:0")
     g = torch.Generator(device="cuda").manual_seed(F + N)
     rn = lambda *s, sc=1.0: (torch.randn(*s, generator=g, device=dev) * sc).to(dt)
-    dims = abi.make_dims(P, D, F, 1, N, 1, dtype, "gelu")
+    dims = abi.make_dims(P, D, F, 1, N, 1, dtype, act)
     offs = torch.tensor([0] + counts, dtype=torch.int32).cumsum(0).to(torch.int32)
     par = dict(W1=rn(N, F, D, sc=D ** -0.5), b1=rn(N, F), g1=1 + rn(N, F, sc=0.3), be1=rn(N, F), W2=rn(N, F, F, sc=F ** -0.5),
                b2=rn(N, F), g2=1 + rn(N, F, sc=0.3), be2=rn(N, F), W3=rn(N, D, F, sc=F ** -0.5), b3=rn(N, D))
+    if act == "relu":                 # no z near the kink: |n| / 2 stays below 3
+        for n in ("1", "2"):
+            par["g" + n].fill_(0.5)
+            par["be" + n].copy_(3 * torch.sign(par["be" + n].float() + 1e-3))
     x, dy = rn(P, D), rn(P, D)
     nan = lambda *s, t=dt: torch.full(s, float("nan"), dtype=t, device=dev)
     acts = dict(h1=nan(P, F), a1=nan(P, F), st1=nan(P, 2, t=torch.float32), h2=nan(P, F), a2=nan(P, F),
@@ -54,7 +60,11 @@ def test_block_backward_normalisation(dtype, D, F, counts):
             rstd = 1.0 / torch.sqrt(h.var(1, unbiased=False, keepdim=True) + 1e-5)
             n = (h - h.mean(1, keepdim=True)) * rstd
             z = gam * n + bet
-            dz = da * (0.5 * (1 + torch.erf(z * 0.5 ** 0.5)) + z * torch.exp(-0.5 * z * z) * (2 * torch.pi) ** -0.5)
+            if act == "relu":
+                assert float(z.abs().min()) > 1e-3
+                dz = da * (z > 0)
+            else:
+                dz = da * (0.5 * (1 + torch.erf(z * 0.5 ** 0.5)) + z * torch.exp(-0.5 * z * z) * (2 * torch.pi) ** -0.5)
             dn = dz * gam
             want = rstd * (dn - dn.mean(1, keepdim=True) - n * (dn * n).mean(1, keepdim=True))
             rt = 2e-2 if dtype == "bf16" else 1e-5 * max(1.0, counts[e] ** 0.5)
