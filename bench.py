@@ -14,7 +14,8 @@ per-launch duration and roofline fraction and names the kernel that takes the mo
 time per step.  After the timed region a cold pass flushes the memory-side cache
 before each step and times the gate and the dispatch again.  The other workloads
 (1024- and 4096-expert layers, the LayerNorm block experts, the tiny fp32 layer)
-are then timed for a few steps each and reported under "workloads".
+are then timed for a few steps each and reported under "workloads".  The line is the
+record without its per-kernel tables and notes (a few KB); --record FILE writes all of it.
 """
 import argparse
 import gc
@@ -634,6 +635,26 @@ def summary(r, steps):
     return out
 
 
+def compact(result):
+    """The printed line: the record with its tables cut to what names a time or a fraction."""
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if k in d}
+
+    out = {k: v for k, v in result.items() if k not in ("calls_ms", "calls_timing", "cold_protocol", "paper_context")}
+    out["kernels"] = [pick(q, "name", "launches_per_step", "ms_per_launch", "bound", "frac")
+                      for q in result["kernels"][:6]]
+    out["workloads"] = {
+        n: {**pick(w, "dtype", "steps", "ms_per_step", "tokens_per_s", "graph_replay_ms_per_step", "calls_ms_untraced"),
+            "calls_frac": {c: r["frac"] for c, r in w["calls_roofline"].items()},
+            "cpu_tokens_per_s": w.get("cpu_baseline", {}).get("value")}
+        for n, w in result.get("workloads", {}).items()}
+    if "cpu_baseline" in result:
+        cpu = result["cpu_baseline"]
+        out["cpu_baseline"] = {**pick(cpu, "value", "unit", "cores", "kind"),
+                               "one_thread": pick(cpu.get("one_thread", {}), "value", "cores")}
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -643,6 +664,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extra", action="store_true", help="time only --workload (no other workloads)")
     ap.add_argument("--cold-steps", type=int, default=5)
+    ap.add_argument("--record", metavar="FILE", help="write the whole record, one JSON line, to FILE as well")
     ap.add_argument("--recompute", action="store_true",
                     help="backward regenerates h and a (dmoe_expert_ffn_bwd_recompute)")
     ap.add_argument("--alive-topk", action="store_true",
@@ -745,7 +767,10 @@ def main():
             gc.collect()
             torch.cuda.empty_cache()
         result["workloads"] = extra
-    print(json.dumps(result), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            f.write(json.dumps(result) + "\n")
+    print(json.dumps(compact(result)), flush=True)
 
 
 if __name__ == "__main__":

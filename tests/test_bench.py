@@ -92,3 +92,17 @@ def test_block_kernel_rooflines_closed_forms():
     assert ln[1] == 0 and ln[2] == 2 * P * F * e + 8 * P + 2 * wl.N * F * e
     r = bench.roofline_of(ln[1], ln[2], 1e-3, bench.PEAK_BF16_TFLOPS)
     assert r["bound"] == "hbm"
+
+
+def test_printed_line_is_short_and_keeps_the_headline():
+    import json
+
+    import bench
+    with open(os.path.join(ROOT, "profiles", "bench_wide.json")) as f:
+        full = json.loads(f.read())
+    line = bench.compact(full)
+    assert len(json.dumps(line)) < 8000 < len(json.dumps(full))
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config", "roofline"):
+        assert line[key] == full[key]
+    assert set(line["workloads"]) == set(full["workloads"])
