@@ -134,18 +134,19 @@ int dmoe_trace_end(void);
  *   g      [T, k] fp32   chosen totals g(x, f), or NULL
  *   scores [T, d*M] fp32 per-dimension decision scores g_i(x), or NULL
  * Selection compares the fp32 rounding of each exact score g_i(x)[u] and adds the d
- * fp32 values of a cell in fp64 in dim order.  bf16: scores are computed on MFMA
- * with a per-token error bound; a token whose TopK order is within the bound of a
- * tie is recomputed with exact fp64 accumulation, so the selection equals the one
- * of the exact scores; the returned scores, g and w carry the (bounded) MFMA error.
- * fp32, and bf16 with d*M > 96: exact fp64 accumulation for every token.
+ * fp32 values of a cell in fp64 in dim order.  fp32, bf16 with d*M > 96, and smaller
+ * bf16 calls (chosen by T, D and d*M): exact fp64 accumulation for every token.  Larger
+ * bf16 calls: scores are computed on bf16 matrix instructions with a per-token error
+ * bound; a token whose TopK order is within the bound of a tie is recomputed with exact
+ * fp64 accumulation, so the selection equals the one of the exact scores; the returned
+ * scores, g and w of the others carry the (bounded) error.
  * Inputs are expected to be finite.  A NaN score ranks below every other score of its
  * dimension, so an expert with one is chosen only when fewer than k are left; otherwise
  * the choice with NaN or infinite scores is unspecified (every returned index is still a
  * valid expert id), and w may be NaN when such an expert is chosen.
- * Uses workspace: bf16 with d*M <= 96, and DMOE_FLAG_ALIVE_TOPK with either dtype
- * (the queue of tokens to recompute; ws must not be NULL, else DMOE_EINVAL);
- * otherwise no. */
+ * Workspace: ws must not be NULL (else DMOE_EINVAL) for bf16 with d*M <= 96 and for
+ * DMOE_FLAG_ALIVE_TOPK with either dtype, whichever way the scores are computed; the
+ * larger bf16 calls keep the queue of tokens to recompute there.  Otherwise ws is not used. */
 int dmoe_gate_topk(const dmoe_dims* dims, const void* x, const void* Wg, const void* bg,
                    const uint8_t* alive, int32_t* idx, float* w, float* g, float* scores,
                    void* ws, void* stream);

@@ -22,7 +22,8 @@ int check_dims(const dmoe_dims* dims, Shape* s) {
   if (q.k > KMAX) return DMOE_EUNSUPPORTED;
   if ((int64_t)q.d * q.M > DM_MAX) return DMOE_EUNSUPPORTED;
   if (q.D % 64 || q.H % 64) return DMOE_EUNSUPPORTED;
-  // tile loads address a tile's rows with 32-bit byte offsets (256 rows x ld x 2 bytes)
+  // tile loads address a tile's rows with unsigned 32-bit byte offsets: 288 rows x ld x 2 bytes
+  // (bf16), 128 rows x ld x 4 (fp32)
   if (q.D > (1 << 22) || q.H > (1 << 22)) return DMOE_EUNSUPPORTED;
   // pair and row indices are 32-bit (T * k rows, with headroom for tile rounding)
   if (q.T > (int64_t)0x7fffffff || q.T * q.k > (int64_t)0x7fffffff / 2) return DMOE_EUNSUPPORTED;

@@ -4,8 +4,10 @@
 //   a2 = act(LN(h2; g2, be2)), y = a2 W3^T + b3,
 // LN(h; g, b) = g (h - mean) / sqrt(var + eps) + b over the F features of a row
 // (biased variance, eps = 1e-5).  The linear layers run on the grouped GEMMs; the
-// normalisation, its affine map and the activation are one row kernel, and the
-// backward of that step is a row kernel (input gradient) plus a per-expert column
+// normalisation, its affine map and the activation are one row kernel.  The backward of
+// that step inside the block is one pass over its rows (ln_bwd_kernel), with a reduction
+// of the column sums that its blocks share; the step's own entry point, which has no
+// workspace for those, takes a row kernel (input gradient) and a per-expert column
 // reduction (scale and shift gradients).
 #include "grouped.hpp"
 

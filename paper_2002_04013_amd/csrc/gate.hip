@@ -895,7 +895,9 @@ __device__ __forceinline__ void exact_scores(const GateArgs& a, int t, double* s
 }
 
 // The tokens the certificate rejects (bf16 MFMA scores): persistent blocks over the queue,
-// one token a pass (lowest latency), two blocks per compute unit.
+// one token a pass (lowest latency), two blocks per compute unit: 128 registers, of which the
+// scores' loads and the selection take all (6 spill with ALIVE, 4 without, outside the score
+// loop's loads: the call takes 17-20 us for the wide workload's queue with them).
 template <bool ALIVE>
 __global__ void __launch_bounds__(GX_NT) __attribute__((amdgpu_waves_per_eu(4)))
 gate_exact_sparse_kernel(GateArgs a, const int32_t* queue) {
