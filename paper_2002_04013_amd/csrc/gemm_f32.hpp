@@ -18,9 +18,9 @@
 //
 // Measured against the register-staged kernel it replaces (32 x 64 tiles of two waves,
 // scalar LDS reads), 8.6 GFLOP a launch: row-grouped 206 to 244 us -> 101 to 110 us,
-// weight gradients 202 to 205 us -> 93 us.  The MFMA pipes are busy 59% of the weight
-// gradient's time (74% while a unit holds blocks); the rest is the launch, the first
-// stages' latency and the last tiles, which run one to a unit.
+// weight gradients 202 to 205 us -> 88 to 93 us.  The MFMA pipes are busy 53 to 58% of a
+// row-grouped launch and 64% of a weight gradient (counters, 2.4 GHz); the rest is the launch,
+// the first stages' latency and the last tiles, which run one to a unit.
 #pragma once
 
 #include "gemm2.hpp"

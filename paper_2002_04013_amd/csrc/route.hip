@@ -13,10 +13,10 @@
 // These are small kernels whose cost is mostly their launches (about 4.6 us each in a
 // stream), so how many there are follows the size (launches / call, measured):
 //   * few pairs: steps 1 to 3 in one block, and step 4 too when it is a few rows
-//     (32 pairs over 1024 experts 23 us in five launches -> 7 us in one; 1000 pairs over 256
-//     experts 26 us -> 13 us in two);
+//     (32 pairs over 1024 experts 23 us in five launches -> 6 us in one; 1000 pairs over 256
+//     experts 26 us -> 12 us in two);
 //   * histograms of few entries: step 2 in every block of step 3, which reads them all
-//     (16384 pairs over 1024 experts, steps 1 to 3 21.5 us in four launches -> 14 us in two);
+//     (16384 pairs over 1024 experts, steps 1 to 3 21.5 us in four launches -> 16 us in two);
 //   * else four launches for steps 1 to 3 (a scatter block would read megabytes).
 #include "common.hpp"
 
