@@ -1,6 +1,7 @@
 // Structured gate, exact TopK over the expert grid and Eq. 1 weights
 // (Sec. 3.2, Eq. 1, App. C), plus the gate's backward pass.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -938,7 +939,7 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 //
 // LANE: one lane per token selects (select_token; its few undecided tokens go to select_wave),
 // in blocks of two token tiles and a wave per tile of columns and tokens.  The least work per
-// token, for calls of many tokens with few candidates (gate_f64_lane).
+// token, for calls of many tokens with few candidates (gate_route).
 template <typename E, bool ALIVE, bool LANE>
 __global__ void __launch_bounds__(LANE ? 512 : 1024) gate_topk_f64(GateArgs a, int CTN) {
   extern __shared__ __align__(16) unsigned char sm[];
@@ -1025,38 +1026,81 @@ __global__ void __launch_bounds__(LANE ? 512 : 1024) gate_topk_f64(GateArgs a, i
 // columns 94 / 69 us; T = 200, D = 8192, 96 columns 194 / 140 us; T = 1024, 15625 experts, a
 // fifth of them alive, k = 8 340 / 192 us; T = 4096, D = 1024, 64 columns 23 / 21 us.
 static int gate_f64_tiles(const Shape& s) { return (int)((s.dM + 15) / 16); }
-// A lane per token selects where the tokens are many, so that the work per token counts and
-// not its latency, and the selection is the larger part of the call (narrow d_model, few
-// columns, small k).  Measured in us, a wave per token / a lane per token: T = 65536, D = 64,
-// 32 columns, k = 4 64 / 33; k = 8 71 / 57; 64 columns, k = 4 73 / 57; 4 dimensions of 8
-// 71 / 47; D = 1024, 32 columns 174 / 144, 64 columns 271 / 277; T = 16384, D = 64, 32 columns,
-// k = 4 19 / 16, 4 dimensions of 8 21 / 25, k = 8 21 / 33; T = 8192 11 / 15.
-static bool gate_f64_lane(const Shape& s) {
-  if (s.dtype != DMOE_F32 || (s.flags & DMOE_FLAG_ALIVE_TOPK) || s.D > 1024) return false;
-  if (s.dM <= 32 && s.k <= 4) return s.T >= (s.d <= 2 ? 16384 : 32768);
-  return (s.dM <= 32 || (s.dM <= 64 && s.k <= 4)) && s.D <= 512 && s.T >= 65536;
-}
-static int gate_f64_tokens(const Shape& s) { return gate_f64_lane(s) ? 2 * GF_TOK : GF_TOK; }
-static int gate_f64_waves(const Shape& s) {
+static int gate_f64_block_waves(const Shape& s) {
   const int n = gate_f64_tiles(s);
-  if (gate_f64_lane(s)) return n * 2;
   return n * (((s.T + GF_TOK - 1) / GF_TOK <= 256 ? 16 : 8) / n);
 }
-static size_t gate_f64_lds_bytes(const Shape& s) {
+
+// The routes of a gate call, all with the same choice of experts: exact scores with a wave per
+// token selecting (every shape); for fp32 up to 64 columns also with a lane per token; for bf16
+// up to 96 columns also the certified route (three launches: queue clearing, scoring,
+// recomputation), unless DMOE_FLAG_GATE_EXACT.
+// The route with the lowest estimate is taken.  An estimate is a chain of latencies (the loads
+// of d_model, a lane's selection) or the work of all tokens, whichever is longer, with a soft
+// corner, plus a start; T and D in thousands, us.  A lane's selection inserts every column into
+// lists of `cap` places, then every candidate cell: cap d M and cap x cells steps.  The coefficients
+// are least-squares fits to 8100 calls in each route: 12 grids of 2 to 128 columns, d_model 64
+// to 4096, 2048 to 65536 tokens, k = 1, 2, 4, 8, bf16 plain and alive-first (nine of ten experts
+// alive), fp32 plain; those within a factor of 2.5 of another route count.
+// The choice is 0 to 5% above the best route (geometric means).  Lines on T and T d M D in its
+// place were 3 to 10% above it and, for narrow d_model, up to 3.3 times as slow as the certified
+// route.  Certified / wave / lane, us:
+//   bf16, d M = 2: T = 32768, D = 64, k = 1 10 / 33; T = 8192, D = 2048 20 / 21
+//   bf16, 2 x 16, k = 4: T = 4096, D = 1024 33 / 14; T = 16384 33 / 41; T = 32768, D = 64 28 / 38
+//   bf16, 4 x 8, k = 4: T = 16384, D = 64 35 / 23; D = 2048 53 / 65
+//   fp32, 2 x 2, k = 2: T = 8192, D = 64 - / 11 / 7; T = 16384, D = 512 - / 23 / 19, D = 2048 - / 45 / 57
+//   fp32, 2 x 32, k = 2: T = 8192, D = 64 - / 13 / 16; T = 65536, D = 512 - / 186 / 157
+// Alive-first the certified route depends on how many experts are alive, which the host does
+// not know (each token with fewer than k alive among its best cells is computed again: two
+// experts of which one is alive, k = 2, 18859 tokens 277 us, 20 with a wave per token), so there
+// it has to be the shorter one by a tenth.  A wave per token runs in rounds of two blocks to a
+// unit: a last round of a few tokens takes as long as one of half the blocks (D = 64, two columns,
+// 8192 tokens 10.7 us, 8330 15.5, 12288 14.8).
+enum GateRoute { GR_CERTIFIED, GR_WAVE, GR_LANE };
+static double soft_max(double a, double b) {
+  a *= a; b *= b;
+  return std::sqrt(std::sqrt(a * a + b * b));
+}
+static GateRoute gate_route(const Shape& s) {
+  static constexpr RankTable cells = make_rank_table();
+  const bool b16 = s.dtype == DMOE_BF16, alive = (s.flags & DMOE_FLAG_ALIVE_TOPK) != 0;
+  const bool cert = b16 && s.dM <= 3 * 32 && !(s.flags & DMOE_FLAG_GATE_EXACT);
+  const bool lane = !b16 && !alive && s.dM <= 64 && s.D <= 1024;
+  if (!cert && !lane) return GR_WAVE;
+  const double T = (double)s.T * 1e-3, D = (double)s.D * 1e-3, dM = (double)s.dM;
+  constexpr int64_t round = 2 * 256 * GF_TOK;
+  const int64_t last = s.T % round;
+  const double Tw = s.T > round && last > 0 && last < round / 2 ? (double)(s.T - last + round / 2) * 1e-3 : T;
+  const int n = gate_f64_tiles(s), te = n <= 2 ? n : n <= 4 ? 4 : 8;        // waves a tile of columns occupies
+  const double chain = D * te / ((s.T + GF_TOK - 1) / GF_TOK <= 256 ? 16 : 8);
+  const int cap = alive ? (s.k <= 4 ? 7 : KMAX + 3) : (s.k <= 4 ? 5 : KMAX + 1);
+  const int K1 = (int)std::min<int64_t>(s.N, alive ? cap : s.k + 1);
+  const double cols = 0.01 * cap * dM, cell = 0.01 * cap * (double)std::min<int64_t>(s.N, cells.cnt[s.d - 1][K1]);
+  if (lane) {
+    const double w = soft_max(3.99 + 55.7 * chain, Tw * (0.775 + 0.818 * D * te + 0.00592 * dM)) + 3.98;
+    const double l = soft_max(17.7 * D + 3.07 * cols + 11.8 * cell, T * (0.0422 + 0.953 * D * te + 0.155 * (cols + cell))) + 3.6;
+    return l < w ? GR_LANE : GR_WAVE;
+  }
+  const int CB = (int)((s.dM + 31) / 32);
+  const double De = D / gm_kw(s.D);
+  double w, c;
+  if (!alive) {
+    w = 1.05 * (soft_max(4.18 + 42.0 * chain, Tw * (0.798 + 0.624 * D * te + 0.00593 * dM)) + 3.94);
+    c = soft_max(3.6 + De * (2.83 + 7.59 * CB) + 3.79 * cols + 13.6 * cell,
+                 T * (D * (0.13 + 0.372 * CB) + 0.131 * (cols + cell))) + 7.02;
+  } else {
+    w = 0.9 * (soft_max(3.96 + 44.1 * chain, Tw * (0.902 + 0.628 * D * te + 0.0104 * dM)) + 4.63);
+    c = soft_max(8.03 + De * (2.38 + 8.07 * CB) + 3.29 * cols + 17.4 * cell,
+                 T * (D * (0.277 + 0.324 * CB) + 0.206 * (cols + cell)));
+  }
+  return c < w ? GR_CERTIFIED : GR_WAVE;
+}
+static int gate_f64_tokens(bool lane) { return lane ? 2 * GF_TOK : GF_TOK; }
+static int gate_f64_waves(const Shape& s, bool lane) { return lane ? gate_f64_tiles(s) * 2 : gate_f64_block_waves(s); }
+static size_t gate_f64_lds_bytes(const Shape& s, bool lane) {
   static_assert(GF_TOK % 2 == 0 && alignof(SelectScratch) <= 16, "s64 rows end on 16 bytes");
   const size_t part = GF_TOK * 17 * sizeof(double);
-  return gate_f64_tokens(s) * (s.dM + 1) * sizeof(double) + gate_f64_waves(s) * std::max(part, sizeof(SelectScratch));
-}
-// bf16 gates with at most 96 columns: exact scores for every token, or the certified route
-// (three launches: queue clearing, scoring, recomputation).  In microseconds the exact route
-// takes about 8, its padded matrix flops at 70 TFLOP/s, T / 1500 for the selection and the
-// read of x; the certified one 36 and the read of x.  Measured, exact against certified:
-// T = 3001, D = 960, 16 columns 15 / 38; T = 4096, D = 1024, 64 columns 24 / 58; T = 8192,
-// D = 4096, 16 columns 40 / 55; T = 32768, D = 1024, 16 columns 59 / 50; T = 32768,
-// D = 4096, 32 columns 193 / 97.
-static bool gate_f64_pays(const Shape& s) {
-  const double flops = 2.0 * (double)s.T * (double)s.D * 16.0 * gate_f64_tiles(s);
-  return flops / 70e6 + (double)s.T / 1500.0 <= 28.0;
+  return gate_f64_tokens(lane) * (s.dM + 1) * sizeof(double) + gate_f64_waves(s, lane) * std::max(part, sizeof(SelectScratch));
 }
 static size_t gate_mfma_lds_bytes(int dM, int kw) {
   const size_t ring = (size_t)kw * GM_RING * 4096 * (1 + (dM + 31) / 32);
@@ -1416,16 +1460,18 @@ extern "C" int dmoe_gate_topk(const dmoe_dims* dims, const void* x, const void* 
     if (!ws) return DMOE_EINVAL;
     if (!aligned16(ws)) return DMOE_EUNSUPPORTED;
   }
-  if (!mfma || (s.flags & DMOE_FLAG_GATE_EXACT) || gate_f64_pays(s)) {
+  const GateRoute route = gate_route(s);
+  if (route != GR_CERTIFIED) {
     // exact fp64 scores for every token
-    const int tok = gate_f64_tokens(s);
+    const bool lane = route == GR_LANE;
+    const int tok = gate_f64_tokens(lane);
     const dim3 grid((unsigned)((s.T + tok - 1) / tok));
     auto go = [&](auto EK) {
       using E = typename decltype(EK)::type;
       auto kern = alive_first ? gate_topk_f64<E, true, false> : gate_topk_f64<E, false, false>;
       if constexpr (sizeof(E) == 4)
-        if (gate_f64_lane(s)) kern = gate_topk_f64<E, false, true>;
-      DMOE_LAUNCH_NAMED("gate_topk_f64", kern, grid, dim3(64 * gate_f64_waves(s)), gate_f64_lds_bytes(s), st, a,
+        if (lane) kern = gate_topk_f64<E, false, true>;
+      DMOE_LAUNCH_NAMED("gate_topk_f64", kern, grid, dim3(64 * gate_f64_waves(s, lane)), gate_f64_lds_bytes(s, lane), st, a,
                         gate_f64_tiles(s));
     };
     if (s.dtype == DMOE_BF16) go(type_tag<bf16>{});

@@ -76,10 +76,12 @@ EXACT = [
     ("bf16", 130, 512, 2, 64, 8, "ties", 0.9, False), ("bf16", 63, 64, 2, 49, 8, "normal", 0.02, True),
     ("bf16", 200, 320, 3, 16, 4, "ties", 0.9, True), ("bf16", 77, 64, 2, 8, 3, "span", 0.9, False),
     ("bf16", 300, 128, 4, 8, 8, "ties", 0.9, False), ("bf16", 50, 2112, 3, 25, 8, "normal", 0.5, True),
-    # many tokens with few candidates: a lane per token selects
+    # few candidates for the tokens: a lane per token selects
     ("f32", 32801, 64, 2, 16, 4, "normal", 0.9, False), ("f32", 32768, 64, 2, 15, 3, "ties", 0.8, False),
     ("f32", 16385, 192, 1, 16, 1, "normal", 0.9, False), ("f32", 20000, 64, 2, 4, 4, "span", 0.9, False),
     ("f32", 16400, 1024, 2, 2, 4, "normal", 1.0, False), ("f32", 32800, 128, 4, 3, 4, "ties", 0.9, False),
+    ("f32", 33, 64, 1, 2, 1, "normal", 0.5, False), ("f32", 2049, 64, 2, 2, 3, "ties", 0.9, False),
+    ("f32", 9000, 64, 3, 3, 2, "span", 0.9, False),
     ("f32", 65537, 64, 2, 4, 8, "ties", 0.9, False), ("f32", 65600, 64, 1, 64, 4, "normal", 0.9, False),
     ("f32", 20, 64, 2, 40, 8, "rising", 0.2, True), ("bf16", 20, 64, 3, 25, 8, "rising", 0.003, True),
     ("f32", 20, 64, 2, 30, 8, "equal", 0.1, True), ("f32", 20, 64, 2, 64, 8, "ties", 0.05, True),
@@ -119,6 +121,8 @@ def test_exact_route_matches_the_definition(dtype, T, D, d, M, k, inputs, p_aliv
     # columns up to 32, one wave a block and two
     (44000, 64, 2, 4, 4, 0.9, False), (43001, 64, 1, 32, 8, 0.9, True), (33000, 2048, 2, 16, 4, 1.0, False),
     (40001, 2112, 2, 16, 8, 0.9, True),
+    # narrow d_model, as many cells as are chosen or ranked
+    (16400, 64, 2, 2, 4, 0.9, False), (12301, 64, 2, 2, 2, 0.9, True), (14001, 128, 1, 16, 1, 0.9, False),
     # up to 64
     (40000, 1024, 2, 32, 4, 0.95, False), (40000, 1024, 2, 32, 4, 0.9, True), (20000, 2112, 2, 17, 8, 0.9, False),
     (20000, 2048, 4, 11, 4, 0.9, True),
