@@ -530,13 +530,16 @@ __device__ __forceinline__ uint32_t shift_up(uint32_t v) {
 // totals adding the d decision scores in fp64 in dimension order, ranked (alive first when
 // ALIVE, total desc, flat asc).  The k best so far lie in lanes 0 .. k - 1, best first; the
 // few cells of a step that beat the k-th (a ballot) are inserted one by one, at their count of
-// better entries; the first 64 cells, most of which would be, are ranked by counting.  A step's alive flags are loaded RA_U steps at a time.
+// better entries; of the first 64 cells, most of which would be, the k best are taken by k rounds
+// of a maximum (ranking them by counting is 64 steps, which the four waves of a SIMD share).  A
+// step's alive flags are loaded RA_U steps at a time.
 // Reached where a ranking of the likely cells does not decide: fewer than k alive among them,
 // or totals that may round.  Bound by the latency of a step's and of an insertion's chain.  The
 // gate call with a fifth of the experts alive, D = 512, fp32, as k rounds over every cell /
 // with a sorted list of k cells in every lane / this form: T = 8192, 15625 experts, k = 8
-// 3409 / 1070 / 418 us; 14641 experts, k = 4 1495 / 700 / 329 us; 4096 experts, k = 8
-// 619 / 449 / 169 us.
+// 3412 / 1072 / 381 us; 14641 experts, k = 4 1498 / 702 / 294 us; 4096 experts, k = 8
+// 622 / 451 / 138 us.  T = 836, D = 1984, 256 experts, k = 6, 30% alive: 54 / 32 / 35 us (42 with
+// the first cells ranked by counting).
 constexpr int RA_U = 4;
 template <bool ALIVE>
 __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const float* dec, int M4, int* rf, int* ru) {
@@ -593,19 +596,15 @@ __device__ __forceinline__ void rank_all_wave(const GateArgs& a, const float* de
         ct = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(tt[q] >> 32), s) << 32) |
              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tt[q], s);
       };
-      if (q == 0 && f0 == 0) {                                       // the first cells: by counting
-        int better = f < N ? 0 : 64;
-        for (int s = 0; s < min(N, 64); ++s) {
-          uint32_t cl, cn;
-          uint64_t ct;
-          take(s, cl, ct, cn);
-          better += cell_gt(cl, ct, cn, l, tt[q], n);
-        }
+      if (q == 0 && f0 == 0) {                                       // the first cells: k rounds of a maximum
+        bool in = f < N;
         for (int j = 0; j < min(N, k); ++j) {
-          uint32_t cl, cn;
-          uint64_t ct;
-          take(__builtin_ctzll(__ballot(better == j)), cl, ct, cn);
-          if (lane == j) { el = cl; et = ct; en = cn; }
+          const bool alive = __ballot(in && l != 0u) != 0ull;
+          const bool cand = in && (!alive || l != 0u);
+          const uint64_t best = wave_max_u64(cand ? tt[q] : 0ull);   // no image is 0
+          const int s = __builtin_ctzll(__ballot(cand && tt[q] == best));
+          if (lane == j) { el = alive ? 1u : 0u; et = best; en = ~(uint32_t)s; }
+          in = in && lane != s;
         }
         kth();
         continue;
