@@ -20,49 +20,85 @@ namespace dmoe {
 //                          (GROUP_M m-tiles; the GEMMs of a call use at most two)
 //   act[e]               = number of experts before e that have rows (GROUP_K experts)
 // with the totals at [N]; act may be null.  A GEMM with NT n-tiles (GROUP_M) or MT*NT tiles
-// per expert (GROUP_K) scales these.  One block: thread q owns the experts [q EPT, (q+1) EPT),
-// the waves' sums are scanned by shuffles and meet in LDS once (a forward of 4096 experts, almost
-// all without rows, 20.4 us with 21 barriers for the three sums, 19.6 with one).
-static __global__ void __launch_bounds__(1024)
-tile_plan(const int32_t* offsets, int N, int BMa, int BMb, int32_t* plan_a, int32_t* plan_b, int32_t* act) {
-  __shared__ int part[3][16];
-  const int q = threadIdx.x, lane = q & 63, wave = q >> 6;
-  const int EPT = (N + 1023) / 1024;
-  const int e0 = min(N, q * EPT), e1 = min(N, e0 + EPT);
-  int mine[3] = {0, 0, 0}, run[3], total[3] = {0, 0, 0};
-  auto add = [&](int (&v)[3], int c) {
-    v[0] += (c + BMa - 1) / BMa;
-    v[1] += (c + BMb - 1) / BMb;
-    v[2] += c > 0;
-  };
-  for (int e = e0; e < e1; ++e) add(mine, offsets[e + 1] - offsets[e]);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    int incl = mine[i];
+// per expert (GROUP_K) scales these.  One block: wave w owns the experts [64 G w, 64 G (w + 1)),
+// 64 at a time, so that loads and stores are whole lines; a shuffle scan of every 64, the waves'
+// sums meet in LDS once.  Tile heights are multiples of 32, and a division by the multiple is a
+// multiplication.  (A thread owning G consecutive experts had strided accesses: 15625 experts
+// 29 us for one height, 31 for two, 39 with act; 15 now with all, and 3.9 where it was 4.8 for 64 experts.)
+constexpr int TP_WAVES = 16;
+struct TileHeight {
+  int mul; uint32_t inv;                           // in 32-row blocks, and 2^32 / mul rounded up
+  __device__ __forceinline__ int tiles(int rows) const {
+    // exact below 2^28 blocks: the error of inv is at most mul / 2^32 a block, mul <= 9
+    const uint32_t n = (uint32_t)((rows + 31) >> 5) + (uint32_t)(mul - 1);
+    return mul == 1 ? (int)n : (int)__umulhi(n, inv);
+  }
+};
+static TileHeight tile_height(int BM) {
+  const uint32_t mul = (uint32_t)(BM / 32);
+  return {(int)mul, mul > 1 ? (uint32_t)(((1ull << 32) + mul - 1) / mul) : 0u};
+}
+static __global__ void __launch_bounds__(64 * TP_WAVES)
+tile_plan(const int32_t* offsets, int N, TileHeight ha, TileHeight hb, int32_t* plan_a, int32_t* plan_b, int32_t* act) {
+  __shared__ int part[3][TP_WAVES];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int G = (N + 64 * TP_WAVES - 1) / (64 * TP_WAVES), base = 64 * G * wave;
+  struct Group { int ta, tb, ia, ib; uint64_t has; };   // this lane's tiles, and inclusive sums over the lanes
+  auto rows = [&](int e) { return e < N ? offsets[e + 1] - offsets[e] : 0; };
+  auto scan = [&](int c) {
+    Group g;
+    g.ta = g.ia = ha.tiles(c);
+    g.tb = g.ib = hb.tiles(c);
+    g.has = __ballot(c > 0);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
+      const int va = __shfl_up(g.ia, o, 64), vb = __shfl_up(g.ib, o, 64);
+      if (lane >= o) { g.ia += va; g.ib += vb; }
     }
-    if (lane == 63) part[i][wave] = incl;
-    run[i] = incl - mine[i];
+    return g;
+  };
+  Group first = scan(rows(base + lane));
+  int sa = 0, sb = 0, sn = 0;
+#pragma unroll 4
+  for (int i = 1; i < G; ++i) {
+    const int c = rows(base + 64 * i + lane);
+    sa += ha.tiles(c);
+    sb += hb.tiles(c);
+    sn += __popcll(__ballot(c > 0));
+  }
+  if (G > 1) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { sa += __shfl_xor(sa, o, 64); sb += __shfl_xor(sb, o, 64); }
+  }
+  if (lane == 63) {
+    part[0][wave] = first.ia + sa;
+    part[1][wave] = first.ib + sb;
+    part[2][wave] = __popcll(first.has) + sn;
   }
   __syncthreads();
-  const int waves = (int)blockDim.x >> 6;
+  int run[3] = {0, 0, 0}, total[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < 3; ++i)
-    for (int w = 0; w < waves; ++w) {
+#pragma unroll
+    for (int w = 0; w < TP_WAVES; ++w) {
       const int v = part[i][w];
-      if (w < wave) run[i] += v;
+      run[i] += w < wave ? v : 0;
       total[i] += v;
     }
-  for (int e = e0; e < e1; ++e) {
-    plan_a[e] = run[0];
-    plan_b[e] = run[1];
-    if (act) act[e] = run[2];
-    add(run, offsets[e + 1] - offsets[e]);
+  for (int i = 0; i < G; ++i) {
+    const int e = base + 64 * i + lane;
+    const Group g = i == 0 ? first : scan(rows(e));
+    if (e < N) {
+      plan_a[e] = run[0] + g.ia - g.ta;
+      plan_b[e] = run[1] + g.ib - g.tb;
+      if (act) act[e] = run[2] + __popcll(g.has & ((1ull << lane) - 1ull));
+    }
+    run[0] += __builtin_amdgcn_readlane(g.ia, 63);
+    run[1] += __builtin_amdgcn_readlane(g.ib, 63);
+    run[2] += __popcll(g.has);
   }
-  if (q == 0) {
+  if (threadIdx.x == 0) {
     plan_a[N] = total[0];
     plan_b[N] = total[1];
     if (act) act[N] = total[2];
@@ -75,7 +111,8 @@ static Plan plan_at(int32_t* mem, int64_t N, bool with_act) {
   return {mem, mem + N + 1, with_act ? mem + 2 * (N + 1) : nullptr};
 }
 static void run_tile_plan(const Shape& s, const int32_t* offsets, int BMa, int BMb, const Plan& pl, hipStream_t st) {
-  DMOE_LAUNCH(tile_plan, dim3(1), dim3(1024), 0, st, offsets, (int)s.N, BMa, BMb, pl.a, pl.b, pl.act);
+  DMOE_LAUNCH(tile_plan, dim3(1), dim3(64 * TP_WAVES), 0, st, offsets, (int)s.N, tile_height(BMa), tile_height(BMb), pl.a, pl.b,
+              pl.act);
 }
 
 // Column sums over each expert's rows, for the bias gradients (and the LayerNorm scale and
