@@ -238,7 +238,8 @@ ln_act_bwd_params_kernel(const E* h, const float* stats, const int32_t* offsets,
     }
   };
   constexpr int U = 4;
-  int r = r0 + (int)threadIdx.x / CL;
+  if (S == 1 && !cok) return;
+  int r = S == 1 ? r0 : cok ? r0 + (int)threadIdx.x / CL : r1;      // as in segment_colsum
   for (; r + (U - 1) * S < r1; r += U * S) {
     uint4 hv[U], dv[U];
     float2 st[U];
