@@ -135,7 +135,7 @@ int dmoe_trace_end(void);
  *   scores [T, d*M] fp32 per-dimension decision scores g_i(x), or NULL
  * Selection compares the fp32 rounding of each exact score g_i(x)[u] and adds the d
  * fp32 values of a cell in fp64 in dim order.  fp32, bf16 with d*M > 96, and smaller
- * bf16 calls (chosen by T, D and d*M): exact fp64 accumulation for every token.  Larger
+ * bf16 calls (by their sizes): exact fp64 accumulation for every token.  Other
  * bf16 calls: scores are computed on bf16 matrix instructions with a per-token error
  * bound; a token whose TopK order is within the bound of a tie is recomputed with exact
  * fp64 accumulation, so the selection equals the one of the exact scores; the returned
